@@ -436,8 +436,8 @@ int sw_device_status(int *gave_up);
  *                      otherwise a power of two in [64, 65536].
  *   SW_PARAM_KERNEL    0 = library default choice, 1 = force the vector-ALU
  *                      kernel, 2 = force the matrix-core (MFMA) kernel
- *                      (SW_ERR_UNSUPPORTED at call time if the shape has no such
- *                      kernel: it needs head_dim 128).
+ *                      (SW_ERR_UNSUPPORTED at call time unless head_dim is 128; the
+ *                      default choice takes it for head_dim 64 as well).
  *   SW_PARAM_COMBINE   how the chunks of a request are merged: 0 = library default
  *                      (the same launch where no request can have more than four
  *                      chunks, i.e. max_len <= 4 * chunk; a second kernel otherwise),

