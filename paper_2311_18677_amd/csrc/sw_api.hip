@@ -24,6 +24,26 @@ constexpr int kVersion = 200;   // 0.2.0
 // two on long prompts (batches of short prompts switch earlier, see causal_attn).
 constexpr long long kPrefillSharedMinGroups = 300;
 
+// Whether the shared-tile form with the key range in two halves serves a prompt call.  `groups`
+// counts the call's work in eight-wave workgroups of the whole form, avg_q its query tokens per
+// request: all the host knows of the lengths.  Up to about 200 groups the key-split kernel has
+// the shorter chains, from about 400 on there are workgroups enough for the whole form; in
+// between both leave the chip partly idle.  Measured, time without / with the halves:
+//   one prompt, 8 heads on one key/value head (groups): 4096 tokens (128) 56 / 69 us, 6144 (192)
+//   112 / 105, 8192 (256) 188 / 151, 12288 (384) 362 / 348, 14336 (448) 428 / 447; over the
+//   other head counts 1.01 to 1.46 times from 224 to 384 groups, 0.93 at 448;
+//   several of 3000 tokens and more: 1.07 to 1.11 at 320 groups where they are equally long and
+//   1.24 to 1.37 where they are not (the whole form waits for the longest), 0.96 at 384 for equal
+//   ones of 4096, 1.00 to 1.04 from 6144 on; below 300 groups unequal ones lose (0.81 to 1.03);
+//   several shorter ones lose or gain with their lengths (0.8 to 1.3), which the host does not know.
+// Groups of three heads make workgroups of six waves, which gain nothing (0.82 to 1.03).
+bool use_halves(long long groups, long long avg_q, int n_req, int columns)
+{
+    if (columns != 4) return false;
+    if (n_req == 1) return groups >= 208 && groups < 400;
+    return avg_q >= 3000 && groups >= 300 && groups < (avg_q < 5000 ? 345 : 400);
+}
+
 thread_local std::string t_last_error = "";
 
 int fail(int code, const std::string &msg)
@@ -736,7 +756,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     a.group = n_qh / n_kvh;
     a.head_dim = head_dim;
     a.max_len = max_len;
-    // Two kernels.  The shared-tile kernel stages every K/V tile once for the eight waves of
+    // Two kernels, the second in two forms.  The shared-tile kernel stages every K/V tile once for the eight waves of
     // a workgroup (the heads of a group, or more query positions of one head) and runs at a
     // steady 41-45 % of the matrix peak once its workgroups fill the chip more than once;
     // with fewer its time is that of the longest prompt's last block.  The key-split kernel
@@ -748,8 +768,8 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     // looks at the call's number of query tokens, which the host knows; inside either kernel
     // a request's result does not depend on the rest of its batch.
     int shared_hp, shared_qw;
-    sw_prefill_shape(n_req, n_kvh, a.group, max_q_len, &shared_hp, &shared_qw);
-    int which, knob_hp, knob_qw, knob_merge;
+    sw_prefill_shape(a.group, 8, &shared_hp, &shared_qw);
+    int which, knob_hp, knob_qw, knob_merge, halves_hp = 1, halves_qw = 1;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         which = g_prefill_kernel;
@@ -768,12 +788,17 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         const long long avg_q = q_bound / (n_req > 0 ? n_req : 1);
         const long long need = avg_q <= 256 ? 192 : (avg_q <= 1024 ? 256 : kPrefillSharedMinGroups);
         which = groups >= need ? 1 : 2;
+        sw_prefill_shape(a.group, 4, &halves_hp, &halves_qw);
+        if (use_halves(groups, avg_q, n_req, halves_hp * halves_qw)) which = 3;
     }
     int split_waves = 4;
     if (which == 2) {
         a.hp = 1;
         a.qw = 1;
         if (knob_qw == 2 || knob_qw == 4 || knob_qw == 8) split_waves = knob_qw;
+    } else if (which == 3) {
+        a.hp = halves_hp;
+        a.qw = halves_qw;
     } else {
         a.hp = shared_hp;
         a.qw = shared_qw;
@@ -843,6 +868,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     hipError_t e;
     e = which == 2 ? sw_launch_prefill_split(a, split_waves, (hipStream_t)stream_v, prof ? &ev : nullptr,
                                              merge_args.ws_o ? &merge_args : nullptr)
+      : which == 3 ? sw_launch_prefill_halves(a, (hipStream_t)stream_v, prof ? &ev : nullptr)
                    : sw_launch_prefill_mfma(a, (hipStream_t)stream_v, prof ? &ev : nullptr);
     if (e != hipSuccess) {
         if (prof) prof_abort(rec);

@@ -1,0 +1,393 @@
+// Prompt-phase (causal) attention, shared tiles with the key range in two halves (gfx950,
+// wave64), head_dim 128: the form for a few long prompts.
+//
+// The shared-tile kernel (sw_prefill_mfma.hip) stages every K/V tile once for the eight waves of
+// a workgroup, which is what keeps the L2 traffic low, but with few workgroups its time is the
+// chain of tiles of the longest prompt's last block: 0.9 us for every 32 positions, on a partly
+// idle chip.  The key-split kernel (sw_prefill_split.hip) has short chains but streams the key
+// range through L2 once per 32 queries and head.  Here four of the waves take the even tiles and four
+// the odd ones, for half as many (query head, 32 positions) columns: half the chain, twice the
+// workgroups -- late (long) blocks first, so that the short ones fill up behind them -- and a
+// tile still serves four waves.  The two groups' (maximum, sum, accumulator) triples are merged
+// through LDS at the end.
+//
+// Pipeline.  A step computes the FIRST product of tile i+1 beside the softmax of tile i:
+//
+//   wait, barrier | request K(i+4), V(i+3) | K(i+1) -> registers, part of the softmax |
+//   S(i+1) = K Q^T  with  P(i) = softmax(S(i)), V(i) -> registers | O += V(i) P(i)
+//
+// so the matrix cores have work while a wave's vector unit does the exponentials.  The tiles
+// are requested by inline assembly: with the builtin the compiler's wait-count pass holds the
+// transposing LDS reads until ALL outstanding requests have landed.  The waits below count
+// exactly instead; no other vector-memory operation is issued inside the loop.
+//
+// Measured (sw_prefill_attn, 8 heads on one key/value head; key-split / whole / this): one
+// prompt of 8192 tokens 188 / 238 / 151 us (910 TFLOP/s), of 12288 402 / 362 / 348.  What bounds it: staging two
+// tiles per step (32 KB through the compute unit's 64-byte-per-clock load path, 0.2 us of
+// 1.15 per step) on top of the matrix and vector work, and the LDS reads, which every wave does
+// for 32 queries only.
+#include "sw_prefill_common.h"
+
+#include <type_traits>
+
+namespace {
+
+using namespace sw_prefill;
+
+constexpr int kBufs = 4;          // steps' worth of K and of V tiles in the staging rings
+
+// The block table is read-only for the whole launch; reading it through the constant
+// address space lets wave-uniform entries come in over the scalar path.
+typedef const __attribute__((address_space(4))) int32_t *const_table_t;
+
+// 64 lanes x 16 bytes, global -> LDS, asynchronously: lane l's bytes (at base + off, base
+// wave-uniform) land at LDS offset lds_at + 16 l.  (No output register: nothing of the
+// instruction is outstanding for the register allocator.)
+__device__ __forceinline__ void request_1k(const char *base, unsigned off, unsigned lds_at)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
+                 :: "s"(base), "v"(off), "s"(lds_at) : "memory");
+}
+
+__device__ __forceinline__ void copy_scores(const float4_t (&from)[2][2], float4_t (&to)[2][2])
+{
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) to[nb][tb] = from[nb][tb];
+}
+
+// Causal mask of the scores of the tile at t0 (q0 = position of the wave's first query).
+__device__ __forceinline__ void mask_tile(float4_t (&s)[2][2], int q0, int t0, int n16, int gq)
+{
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (t0 + 16 * tb + 4 * gq + i > q0 + 16 * nb + n16) s[nb][tb][i] = -INFINITY;
+}
+
+// A tile's weights of one query block against the maximum behind neg_m (= -m * scale_log2e):
+// rounded to binary16 (the second product's operand), and the lane's sum of the ROUNDED values in
+// binary32, taken with the two-element dot product against ones: numerator and denominator of a
+// row are built from the same weights (why that matters: see pv_block in sw_prefill_common.h).
+__device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scale_log2e, float neg_m, Frag &p, float &psum)
+{
+    const half2_t ones = {(_Float16)1.f, (_Float16)1.f};
+    psum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float x = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1)], scale_log2e, neg_m));
+        const float y = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1) + 1], scale_log2e, neg_m));
+        const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
+        p.h[2 * j] = w[0];
+        p.h[2 * j + 1] = w[1];
+        psum = __builtin_amdgcn_fdot2(w, ones, psum, false);
+    }
+}
+
+// The exact pass of one query block: raises the running maximum where a score of the tile lies
+// more than kLazyBits above it, rescales what has been accumulated and computes the tile's
+// weights again.  (weights_block takes the maximum as it stands.)
+__device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_log2e, float lazy_raw,
+                                            float &m, float &l, float4_t (&o)[8], Frag &p, float &psum)
+{
+    float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    mt = quad_rows_max(mt);
+    const float m_new = mt > m + lazy_raw ? mt : m;
+    const float alpha = __builtin_amdgcn_exp2f((m - m_new) * scale_log2e);
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] *= alpha;
+    weights_block(s, scale_log2e, -m * scale_log2e, p, psum);
+}
+
+// Eight waves = 2 * (query heads per workgroup) * (waves per head): wave w works on tile
+// 2 * i + w / 4 of step i.
+// PAGED: K and V are block pools addressed through the request's row of the block table
+// (position t = row t % block_size of pool block table[t / block_size]).
+template <bool PAGED>
+__global__ __launch_bounds__(512, 1)
+void sw_prefill_halves_kernel(SwPrefillArgs a)
+{
+    constexpr int NW = 8;                             // waves
+    constexpr int KS = 2;                             // key tiles staged per step
+    constexpr int NC = NW / KS;                       // (query head, 32 positions) columns
+    constexpr int kStepBytes = KS * kTileBytes;       // the K (or V) tiles of one step
+    constexpr int kVBase = kBufs * kStepBytes;        // K ring, then V ring
+    // a step's 8 * KS one-kilobyte requests for K, and as many for V, are dealt round-robin to
+    // the waves; every wave issues C of each
+    constexpr int C = 8 * KS / NW;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kBufs * kStepBytes];
+
+    // blockIdx -> (item = (request, query block), key/value head, block of hp query heads)
+    const int q_block = kQPerWave * a.qw;        // query tokens per workgroup
+    const unsigned n_hb = (unsigned)(a.group / a.hp);
+    const unsigned hb = blockIdx.x % n_hb;
+    const unsigned rest = blockIdx.x / n_hb;
+    const int g = (int)(rest % (unsigned)a.n_kvh);
+    const QItem it = find_item(a, rest / (unsigned)a.n_kvh, q_block);
+    if (!it.valid) return;
+    const int r = it.r, qb = it.qb, L = it.L, NQ = it.NQ;   // NQ: the request's last NQ tokens are its queries
+    const long long q_first = it.q_first;
+    const int P0 = L - NQ;                       // position of query index 0
+    const int Q0 = qb * q_block;                 // first query index of the workgroup
+    if (Q0 >= NQ) return;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n16  = lane & 15;
+    const int gq   = lane >> 4;
+    const int kg   = wave / NC;                  // which of a step's KS tiles
+    const int col  = wave % NC;
+    const int hh   = (int)hb * a.hp + col % a.hp;    // query head within the group
+    const int sb   = col / a.hp;                 // which 32 query positions of the block
+    const int qw0  = Q0 + kQPerWave * sb;        // first query index of the wave ...
+    const int aw0  = P0 + qw0;                   // ... and its position
+    const int h    = g * a.group + hh;
+
+    // dense: the (request, head) slab; block table: the head's rows inside pool block 0
+    const long long slab = PAGED ? (long long)g * a.stride_kvh : (long long)r * a.stride_req + (long long)g * a.stride_kvh;
+    const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * slab;
+    const char *vslab = reinterpret_cast<const char *>(a.v) + 2 * slab;
+    const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
+    const int in_block = PAGED ? (1 << a.block_shift) - 1 : ~0;
+
+    // tiles the workgroup walks: up to the position of its last query
+    const int last_pos = P0 + min(Q0 + q_block, NQ) - 1;
+    const int n_steps = last_pos / (kTile * KS) + 1;
+    // steps this wave computes in: up to the position of its own last query
+    const int my_tiles = qw0 < NQ ? min(aw0 + kQPerWave - 1, L - 1) / kTile + 1 : 0;
+    const int my_steps = my_tiles > kg ? (my_tiles - kg + KS - 1) / KS : 0;
+
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+
+    // This wave's share of step `st`'s K (or V) requests -> ring slot B.  Request j brings rows
+    // 4(j%8) .. +3 of tile j/8 (K pieces XOR-swizzled by row, V pieces by pairs of rows).
+    auto request = [&](int st, auto buf_c, auto is_v_c) __attribute__((always_inline)) {
+        constexpr int B = decltype(buf_c)::value;
+        constexpr bool IS_V = decltype(is_v_c)::value;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int j = wave + NW * c;
+            const int n = j & 7;
+            const int t0 = (st * KS + (j >> 3)) * kTile;
+            const int rho = 4 * n + gq;
+            const int t = min(t0 + rho, L - 1);                      // rows past the prompt repeat its last row
+            const int piece = IS_V ? (n16 ^ v_swizzle(rho)) : (n16 ^ (rho & 15));
+            // block table: the four rows of a request share a pool block (blocks hold a
+            // multiple of four positions, tiles start at multiples of 32): one wave-uniform
+            // table read, the id clamped into the pool
+            long long block_off = 0;
+            if (PAGED) {
+                const int tu = min(t0 + 4 * n, L - 1);
+                int id = table[tu >> a.block_shift];
+                id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
+                block_off = 2 * (long long)id * a.stride_block;
+            }
+            request_1k((IS_V ? vslab : kslab) + block_off,
+                       (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)(piece << 4),
+                       lds0 + (IS_V ? kVBase : 0) + B * kStepBytes + (j >> 3) * kTileBytes + n * 1024);
+        }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    using KTile = std::false_type;
+    using VTile = std::true_type;
+
+    unsigned vt_off[8];
+    vt_offsets(n16, gq, vt_off);
+    float m[2] = {kNegBig, kNegBig};
+    float l[2] = {0.f, 0.f};                               // this lane's share of the weights' sums
+    const float lazy_raw = kLazyBits / a.scale_log2e;      // the threshold in raw score units
+    float4_t o[2][8];
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[nb][e] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+    // ---- first tiles and Q^T operands, awaited together
+    request(0, I0{}, KTile{});
+    if (n_steps > 1) request(1, I1{}, KTile{});
+    request(0, I0{}, VTile{});
+    Frag qreg[2][4];
+    load_q(a, q_first, qw0, NQ, h, n16, gq, qreg);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qreg[nb][kk].u));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (n_steps > 2) request(2, I2{}, KTile{});
+    if (n_steps > 1) request(1, I1{}, VTile{});
+    if (n_steps > 3) request(3, I3{}, KTile{});
+    if (n_steps > 2) request(2, I2{}, VTile{});
+
+    const unsigned char *kmine = lds + kg * kTileBytes;
+    const unsigned char *vmine = lds + kVBase + kg * kTileBytes;
+    const int t_mine = kg * kTile;
+
+    float4_t s0[2][2], s1[2][2];
+    {
+        Frag kop[2][4];
+        load_k_ops(kmine, n16, gq, kop);
+        qk_block(0, kop, qreg, s0);
+        qk_block(1, kop, qreg, s0);
+        if (t_mine + kTile > aw0) mask_tile(s0, aw0, t_mine, n16, gq);
+    }
+
+    // One step: softmax and second product of step i's tile (scores s), first product of step
+    // i+1's tile (into s_next) where the wave has one.  buf = i % kBufs.
+    auto compute = [&](int i, auto buf, auto more_c, float4_t (&s)[2][2], float4_t (&s_next)[2][2]) __attribute__((always_inline)) {
+        const int B = buf;
+        constexpr bool MORE = decltype(more_c)::value;
+        Frag kop[2][4];
+        if (MORE) load_k_ops(kmine + ((B + 1) % kBufs) * kStepBytes, n16, gq, kop);
+        Frag va[8];
+        load_vt(vmine + B * kStepBytes, vt_off, va);
+        if (MORE) {
+            qk_block(0, kop, qreg, s_next);
+            qk_block(1, kop, qreg, s_next);
+        }
+        // Optimistic pass: weights against the running maximum as it stands; the exact pass where
+        // some lane's weights sum to more than kSumBound (rare after the first tiles).
+        Frag p[2];
+        float psum[2];
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) weights_block(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
+        if (MORE) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);          // the K operands
+            __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);         // vector work under their latency
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one matrix instruction ...
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // ... one LDS read of V
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);      // ... three vector instructions
+            }
+        }
+        if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+                raise_block(s[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum[nb]);
+        }
+        l[0] += psum[0];
+        l[1] += psum[1];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            o[0][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[0].h, o[0][e], 0, 0, 0);
+            o[1][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[1].h, o[1][e], 0, 0, 0);
+        }
+        if (MORE) {
+            const int t_next = (i + 1) * (KS * kTile) + t_mine;
+            if (t_next + kTile > aw0) mask_tile(s_next, aw0, t_next, n16, gq);
+        }
+    };
+
+    // Waits for step i's tiles, lets everyone arrive, requests further ones.  buf = i % kBufs.
+    auto arrive = [&](int i, auto buf_c) __attribute__((always_inline)) {
+        constexpr int B = decltype(buf_c)::value;
+        // this wave's share of V(i) and K(i+1) has landed; what may still be in flight, in issue
+        // order: K(i+2), V(i+1), K(i+3), V(i+2) as far as they exist ...
+        const int left = n_steps - i;
+        if (left > 3)       __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * C) & 0xc07f);
+        else if (left == 3) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * C) & 0xc07f);
+        else if (left == 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(1 * C) & 0xc07f);
+        else                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
+        // ... and so has everyone's; every wave has also read K(i) and V(i-1), whose slots
+        // K(i+kBufs) and V(i+kBufs-1) may now overwrite
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (i + kBufs < n_steps) request(i + kBufs, std::integral_constant<int, B>{}, KTile{});
+        if (i + kBufs - 1 < n_steps) request(i + kBufs - 1, std::integral_constant<int, (B + kBufs - 1) % kBufs>{}, VTile{});
+    };
+    static_assert(kBufs == 4, "the loops below are unrolled by the number of buffers");
+    int i = 0;
+    for (;;) {
+        if (i + 1 >= my_steps) break;
+        arrive(i, I0{}); compute(i, I0{}, std::true_type{}, s0, s1); ++i;
+        if (i + 1 >= my_steps) { copy_scores(s1, s0); break; }
+        arrive(i, I1{}); compute(i, I1{}, std::true_type{}, s1, s0); ++i;
+        if (i + 1 >= my_steps) break;
+        arrive(i, I2{}); compute(i, I2{}, std::true_type{}, s0, s1); ++i;
+        if (i + 1 >= my_steps) { copy_scores(s1, s0); break; }
+        arrive(i, I3{}); compute(i, I3{}, std::true_type{}, s1, s0); ++i;
+    }
+    // the wave's last step, then the steps that are only other waves'
+    for (; i < n_steps; ++i) {
+        const int B = i & (kBufs - 1);
+        if (B == 0)      arrive(i, I0{});
+        else if (B == 1) arrive(i, I1{});
+        else if (B == 2) arrive(i, I2{});
+        else             arrive(i, I3{});
+        if (i < my_steps) compute(i, B, std::false_type{}, s0, s1);
+    }
+    l[0] = quad_rows_sum(l[0]);
+    l[1] = quad_rows_sum(l[1]);
+
+    // ---- this lane's query rows: dims 16e + 4gq .. +3 of query 16nb + n16
+    auto store_dims = [&](int nb, int e, float inv) __attribute__((always_inline)) {
+        const int qpos = qw0 + 16 * nb + n16;        // query index
+        const long long row = q_first + qpos;
+        if (qpos >= NQ || row < 0 || row >= a.n_tokens) return;
+        const half2_t lo = __builtin_convertvector((float2_t){o[nb][e][0] * inv, o[nb][e][1] * inv}, half2_t);
+        const half2_t hi = __builtin_convertvector((float2_t){o[nb][e][2] * inv, o[nb][e][3] * inv}, half2_t);
+        union { half2_t h[2]; unsigned long long u; } pk;
+        pk.h[0] = lo;
+        pk.h[1] = hi;
+        *reinterpret_cast<unsigned long long *>(reinterpret_cast<_Float16 *>(a.out) + (row * a.n_qh + h) * kD + 16 * e + 4 * gq) = pk.u;
+    };
+    // The two waves of a column hold the same queries and dims in the same lanes: each hands the
+    // accumulators of one query block to the other through LDS ([column][block][e][lane]) and
+    // finishes the other block.
+    static_assert(NC * 2 * 8 * 1024 + NC * 2 * 512 <= 2 * kBufs * kStepBytes, "the merge must fit in the staging area");
+    __syncthreads();                             // every wave is past its last tile
+    float4_t *mo = reinterpret_cast<float4_t *>(lds);
+    float2_t *mml = reinterpret_cast<float2_t *>(lds + NC * 2 * 8 * 1024);
+    auto send = [&](int nb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mo[((col * 2 + nb) * 8 + e) * 64 + lane] = o[nb][e];
+        mml[(col * 2 + nb) * 64 + lane] = float2_t{m[nb], l[nb]};
+    };
+    auto finish = [&](int nb) __attribute__((always_inline)) {
+        const float2_t other = mml[(col * 2 + nb) * 64 + lane];
+        const float mx = fmaxf(m[nb], other[0]);
+        const float f_own = __builtin_amdgcn_exp2f((m[nb] - mx) * a.scale_log2e);
+        const float f_other = __builtin_amdgcn_exp2f((other[0] - mx) * a.scale_log2e);
+        const float inv = 1.0f / fmaf(f_other, other[1], l[nb] * f_own);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float4_t y = mo[((col * 2 + nb) * 8 + e) * 64 + lane];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) o[nb][e][t] = fmaf(f_other, y[t], o[nb][e][t] * f_own);
+            store_dims(nb, e, inv);
+        }
+    };
+    if (kg == 0) send(1);
+    else         send(0);
+    __syncthreads();
+    if (kg == 0) finish(0);
+    else         finish(1);
+}
+
+}  // namespace
+
+hipError_t sw_launch_prefill_halves(const SwPrefillArgs &a_in, hipStream_t stream, const SwLaunchEvents *ev)
+{
+    SwPrefillArgs a = a_in;
+    if (a.head_dim != kD || a.hp < 1 || a.group % a.hp != 0 || a.qw < 1) return hipErrorInvalidValue;
+    bool compact;
+    const long long blocks = sw_prefill_items(a, kQPerWave * a.qw, &compact) * a.n_kvh * (a.group / a.hp);
+    a.compact = compact;
+    if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks);
+    if (a.hp * a.qw != 4) return hipErrorInvalidValue;
+    return a.block_table ? sw_launch(sw_prefill_halves_kernel<true>, grid, dim3(512), 0, stream, ev, a)
+                         : sw_launch(sw_prefill_halves_kernel<false>, grid, dim3(512), 0, stream, ev, a);
+}

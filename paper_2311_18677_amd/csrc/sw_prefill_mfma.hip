@@ -208,17 +208,16 @@ bool sw_prefill_mfma_supported(const SwPrefillArgs &a)
 }
 
 // How a workgroup is shaped: hp query heads of one group, qw waves (32 query positions
-// each) per head, eight waves in all where the group size allows: hp is the largest
-// divisor of the group size that is at most 8.  (Cutting small problems into smaller
-// workgroups was tried and measured slower: half the waves per staged tile, same chain of
-// dependent tiles.)
-void sw_prefill_shape(int n_req, int n_kvh, int group, int max_len, int *hp, int *qw)
+// each) per head, `cols` of them in all where the group size allows (eight here, four in the
+// form that halves the key range): hp is the largest divisor of the group size that is at most
+// cols.  (Cutting small problems into smaller workgroups was tried and measured slower: half
+// the waves per staged tile, same chain of dependent tiles.)
+void sw_prefill_shape(int group, int cols, int *hp, int *qw)
 {
-    (void)n_req; (void)n_kvh; (void)max_len;
-    int h = group < 8 ? group : 8;
+    int h = group < cols ? group : cols;
     while (h > 1 && group % h != 0) --h;
     *hp = h;
-    *qw = 8 / h > 0 ? 8 / h : 1;
+    *qw = cols / h > 0 ? cols / h : 1;
 }
 
 hipError_t sw_launch_prefill_mfma(const SwPrefillArgs &a_in, hipStream_t stream, const SwLaunchEvents *ev)

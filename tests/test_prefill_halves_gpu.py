@@ -1,0 +1,87 @@
+"""The prompt kernel that takes a long prompt's keys in two halves (the default for one prompt of
+208 to 399 eight-wave workgroups): one query head per workgroup column, two, four, ragged last
+tiles and query blocks, prompts with earlier context, block tables of every addressing kind, and
+keys scaled by 8 (maxima raised late, rows of a single key).
+Tolerance: the library's parity bound against the oracle; over block tables the same bits as dense."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2311_18677_amd import binding as sw
+from paper_2311_18677_amd import workloads as wl
+from helpers import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int16).reshape(-1)).to("cuda:0").view(torch.float16)
+
+
+def i32(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to("cuda:0")
+
+
+# (query heads, key/value heads, cached positions, of which queries, key scale)
+CASES = [(64, 64, 1030, 1030, 1.0), (64, 64, 1057, 1057, 8.0), (64, 32, 901, 901, 1.0), (64, 8, 863, 863, 1.0),
+         (64, 8, 1441, 865, 1.0), (40, 8, 1500, 1500, 1.0)]
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,L,nq,scale", CASES)
+def test_one_long_prompt_against_the_oracle(n_qh, n_kvh, L, nq, scale):
+    import torch
+    d, max_len = 128, L + 3
+    cfg = wl.Config("halves", 1, n_qh, n_kvh, d, max_len, ("fixed", (0,)),
+                    k_row_scale=(0.1, scale) if scale != 1.0 else ())
+    batch = wl.make_batch(cfg, seed=9000 + L, seq_lens=[L])
+    qt, starts, nqs = wl.make_mixed_queries(batch, [nq])
+    bufs = sw.upload_batch(batch, pad_bits=0x7E00)
+    lay = bufs["layout"]
+    out = torch.full((nq, n_qh, d), float("nan"), dtype=torch.float16, device="cuda:0")
+    q = dev(qt)
+    args = (bufs["seq_lens"], i32(starts), i32(nqs))
+    sw.sw_mixed_attn(q, bufs["k_cache"], bufs["v_cache"], *args, out, nq, 1, n_qh, n_kvh, d, max_len, nq)
+    torch.cuda.synchronize()
+    dense = out.cpu().numpy()
+    # the same rows from the oracle, a sample of them: the first and last of every 32-query block and
+    # of its neighbours, and a stride through the rest
+    rows = sorted({min(nq - 1, 32 * b + o) for b in range(0, nq // 32 + 1, 5) for o in (0, 15, 16, 31)} | set(range(0, nq, 61)) | {nq - 1})
+    for i in rows:
+        ref = oracle.decode_attn(qt[i:i + 1], bufs["k_host"], bufs["v_host"], np.array([L - nq + i + 1], dtype=np.int32),
+                                 1, n_qh, n_kvh, d, max_len, lay.stride_req, lay.stride_kvh, lay.stride_tok)
+        assert_parity(dense[i:i + 1], ref, "row %d" % i)
+    for bs in (4, 16, 64):
+        pb = sw.upload_paged_batch(batch, bs, pad_bits=0x7E00, seed=bs)
+        out2 = torch.full_like(out, float("nan"))
+        sw.sw_mixed_attn_paged(q, pb["k_pool"], pb["v_pool"], pb["block_table"], *args, out2, nq, 1, n_qh, n_kvh, d, bs,
+                               pb["max_blocks"], pb["n_blocks"], nq)
+        torch.cuda.synchronize()
+        assert np.array_equal(out2.cpu().numpy().view(np.uint16), dense.view(np.uint16)), bs
+
+
+def test_several_long_prompts_one_of_them_alone_in_its_last_steps():
+    """Lengths far apart: waves of finished query blocks keep arriving at the barrier."""
+    import torch
+    n_qh, n_kvh, d = 8, 1, 128
+    lens = [6400, 1, 3700]                        # 3367 tokens on average, 315 groups
+    cfg = wl.custom_config("halves3", 3, n_qh, n_kvh, d, max(lens))
+    batch = wl.make_batch(cfg, seed=77, seq_lens=lens)
+    qt, starts = wl.make_prefill_queries(batch)
+    bufs = sw.upload_batch(batch)
+    lay = bufs["layout"]
+    n_tokens = sum(lens)
+    out = torch.zeros(n_tokens, n_qh, d, dtype=torch.float16, device="cuda:0")
+    sw.sw_prefill_attn(dev(qt), bufs["k_cache"], bufs["v_cache"], bufs["seq_lens"], i32(starts), out, n_tokens, 3, n_qh,
+                       n_kvh, d, cfg.max_len)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    for r, i in ((0, 0), (0, 6399), (0, 4777), (1, 0), (2, 3699), (2, 31), (2, 2600)):
+        one = np.zeros(3, dtype=np.int32)
+        one[r] = i + 1
+        q3 = np.zeros((3, n_qh, d), dtype=np.float16)
+        q3[r] = qt[starts[r] + i]
+        ref = oracle.decode_attn(q3, bufs["k_host"], bufs["v_host"], one, 3, n_qh, n_kvh, d, cfg.max_len,
+                                 lay.stride_req, lay.stride_kvh, lay.stride_tok)
+        assert_parity(got[starts[r] + i][None], ref[r:r + 1], "request %d row %d" % (r, i))
