@@ -360,4 +360,87 @@ __device__ __forceinline__ void pv_block(int nb, const Frag (&va)[8], const Frag
     l[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones.h, p[nb].h, l[nb], 0, 0, 0);
 }
 
+// ---- pieces of the kernels that run a tile's softmax beside the next tile's first product
+
+__device__ __forceinline__ void copy_scores(const float4_t (&from)[2][2], float4_t (&to)[2][2])
+{
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) to[nb][tb] = from[nb][tb];
+}
+
+// Causal mask of the scores of the tile at t0 (q0 = position of the wave's first query).
+__device__ __forceinline__ void mask_tile(float4_t (&s)[2][2], int q0, int t0, int n16, int gq)
+{
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (t0 + 16 * tb + 4 * gq + i > q0 + 16 * nb + n16) s[nb][tb][i] = -INFINITY;
+}
+
+// A tile's weights of one query block against the maximum behind neg_m (= -m * scale_log2e):
+// rounded to binary16 (the second product's operand), and the lane's sum of the ROUNDED values in
+// binary32, taken with the two-element dot product against ones: numerator and denominator of a
+// row are built from the same weights (why that matters: see pv_block).
+__device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scale_log2e, float neg_m, Frag &p, float &psum)
+{
+    const half2_t ones = {(_Float16)1.f, (_Float16)1.f};
+    psum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float x = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1)], scale_log2e, neg_m));
+        const float y = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1) + 1], scale_log2e, neg_m));
+        const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
+        p.h[2 * j] = w[0];
+        p.h[2 * j + 1] = w[1];
+        psum = __builtin_amdgcn_fdot2(w, ones, psum, false);
+    }
+}
+
+// The exact pass of one query block: raises the running maximum where a score of the tile lies
+// more than kLazyBits above it, rescales what has been accumulated and computes the tile's
+// weights again.  (weights_block takes the maximum as it stands.)
+__device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_log2e, float lazy_raw,
+                                            float &m, float &l, float4_t (&o)[8], Frag &p, float &psum)
+{
+    float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    mt = quad_rows_max(mt);
+    const float m_new = mt > m + lazy_raw ? mt : m;
+    const float alpha = __builtin_amdgcn_exp2f((m - m_new) * scale_log2e);
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] *= alpha;
+    weights_block(s, scale_log2e, -m * scale_log2e, p, psum);
+}
+
+// 64 lanes x 16 bytes, global -> LDS, asynchronously: lane l's bytes (at base + off, base
+// wave-uniform) land at LDS offset lds_at + 16 l.  Inline assembly, because the compiler's
+// wait-count pass holds an LDS read that may alias a pending request of the builtin form (every
+// transposing read does) until all of them have landed; the kernels' own waits count exactly.
+// (No output register: nothing of the instruction is outstanding for the register allocator.)
+__device__ __forceinline__ void request_1k(const char *base, unsigned off, unsigned lds_at)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
+                 :: "s"(base), "v"(off), "s"(lds_at) : "memory");
+}
+
+// (the same with a full address per lane)
+__device__ __forceinline__ void request_1k_at(const void *src, unsigned lds_at)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(src), "s"(lds_at) : "memory");
+}
+
+// LDS offset of a __shared__ object, for the requests above.
+__device__ __forceinline__ unsigned lds_offset(const void *p)
+{
+    return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
+
 }  // namespace sw_prefill
