@@ -459,7 +459,8 @@ int sw_device_status(int *gave_up);
  *                      2 = the kernel that splits a query block's key range over the
  *                      waves of a workgroup.  The two differ by rounding only.
  *   SW_PARAM_MIXED_MERGE  mixed batches: where the chunks of the token-phase requests are
- *                      merged: 0 = library default, 1 = in a combine kernel of its own,
+ *                      merged: 0 = library default (which may also serve both phases in one
+ *                      launch, with the combine kernel after it), 1 = in a combine kernel of its own,
  *                      2 = by extra workgroups of the prompt kernel (one launch fewer;
  *                      only with the four-wave key-split prompt kernel).  Same bits.
  */

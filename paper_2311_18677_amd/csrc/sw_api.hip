@@ -116,7 +116,7 @@ int g_waves = 0;
 int g_prefill_hp = 0;   // prompt-phase kernel: query heads per workgroup
 int g_prefill_qw = 0;   //                      waves per query head (key-split kernel: waves per workgroup)
 int g_prefill_kernel = 0;   // 0 = default, 1 = shared-tile kernel, 2 = key-split kernel
-int g_mixed_merge = 0;      // mixed batches: 0 = default, 1 = combine kernel of its own, 2 = inside the prompt kernel
+int g_mixed_merge = 0;      // mixed batches: 0 = default, 1 = combine kernel after the token phase, 2 = inside the prompt kernel
 
 // per-kernel timing
 struct ProfRec { hipEvent_t ev[4]; bool has_combine; };
@@ -226,6 +226,20 @@ bool fused_fits(size_t slots, int head_dim)
     return slots * (size_t)head_dim * 8 < 0xffffff00ull;
 }
 
+// Mixed batches, four-wave key-split prompt kernel, token phase of more than four chunks: one
+// launch for both phases while the prompt's workgroups leave some of the chip's 512 places free,
+// or their chains are long and end one by one.  Measured, two launches against one, with 64
+// token-phase requests of 1000 to 2600 cached tokens, 8 query heads over one: beside one prompt
+// of 64 tokens 25.9 -> 20.0 us, of 256 24.8 -> 19.7, of 1500 30.0 -> 26.8; of 2000, 2500 and 3500
+// (32 to 64 requests) 35.9 -> 34.2, 41.8 -> 40.6, 55.2 -> 52.0; 40 requests of 1250 to 5000, 6 heads
+// over 2, 300 tokens 37.7 -> 27.2.  Where many short chains fill the chip the token phase still
+// waits: beside two prompts of 900 tokens 25.9 against 26.4, of 1500 36.1 against 36.7, 32
+// heads and 800 tokens 46.2 against 48.0.
+bool use_one_launch(long long prompt_groups, int max_q_len)
+{
+    return prompt_groups <= 440 || max_q_len >= 1600;
+}
+
 // Everything one step needs, dense or block-table.
 struct StepIn {
     const void *q, *k, *v;
@@ -243,6 +257,10 @@ struct StepIn {
     // mixed batches: if non-null and the step would launch the combine kernel, it does not;
     // the kernel's arguments go here instead and the caller sees to the merge
     SwArgs *defer_merge = nullptr;
+    // mixed batches: if non-null, the prompt phase's arguments; where one kernel can serve both
+    // phases the step launches that one, and *with_prompt says so
+    const SwPrefillArgs *prompt = nullptr;
+    bool *with_prompt = nullptr;
     // sw_decode_attn_static: two kernels over the library's static scratch array; no
     // allocation, no per-kernel timing
     bool static_ws = false;
@@ -413,18 +431,28 @@ int run_step(const StepIn &in)
         if (rc != SW_OK) return rc;
     }
 
-    const bool defer = in.defer_merge && !fused;
+    const bool one = in.prompt && !fused && which == 2 && sw_mixed_supported(a, *in.prompt);
+    const bool defer = in.defer_merge && !fused && !one;
     SwLaunchEvents ev_p = {nullptr, nullptr}, ev_c = {nullptr, nullptr};
     ProfRec rec;
-    int prc = in.static_ws ? SW_OK : prof_begin(rec, !fused && !defer, &prof);
+    int prc = in.static_ws ? SW_OK : prof_begin(rec, !fused && !defer && !one, &prof);
     if (prc != SW_OK) return prc;
     if (prof) {
         ev_p = {rec.ev[0], rec.ev[1]};
         ev_c = {rec.ev[2], rec.ev[3]};
     }
 
-    e = which == 2 ? sw_launch_decode_split(a, stream, prof ? &ev_p : nullptr)
+    e = one        ? sw_launch_mixed(a, *in.prompt, stream, prof ? &ev_p : nullptr)
+      : which == 2 ? sw_launch_decode_split(a, stream, prof ? &ev_p : nullptr)
                    : sw_launch_partial_valu(a, stream, prof ? &ev_p : nullptr);
+    if (e == hipSuccess && one) {
+        // a mixed call has two records, one per launch
+        if (prof) prof_commit(rec);
+        *in.with_prompt = true;
+        prc = prof_begin(rec, false, &prof);
+        if (prc != SW_OK) return prc;
+        if (prof) ev_c = {rec.ev[0], rec.ev[1]};
+    }
     if (e == hipSuccess && !fused && !defer) e = sw_launch_combine(a, stream, prof ? &ev_c : nullptr);
     if (e == hipSuccess && defer) *in.defer_merge = a;
     if (e != hipSuccess) {
@@ -835,7 +863,8 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     // takes the others.  Which family serves a request depends on that request alone.
     // (Running the two parts side by side on two streams was tried in both orders, the
     // token-phase kernels first and the prompt kernel first: 33.4 us against 32.1 us on one
-    // stream for 63 token-phase requests beside a 1500-token prompt -- no gain.)
+    // stream for 63 token-phase requests beside a 1500-token prompt -- no gain.  One launch
+    // with the workgroups of both does gain: see use_one_launch.)
     SwArgs merge_args = {};             // ws_o stays null unless the merge was left to the prompt kernel
     if (mixed) {
         StepIn in{};
@@ -853,9 +882,17 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         // With the four-wave key-split kernel to follow, the chunks of the token-phase requests
         // are merged by extra workgroups of that kernel: two launches instead of three.
         if (which == 2 && split_waves == 4 && max_q_len > 1 && knob_merge != 1) in.defer_merge = &merge_args;
-        rc = run_step(in);
-        if (rc != SW_OK) return rc;
         a.skip_single = 1;
+        bool with_prompt = false;
+        // Both phases in one launch, the combine kernel after it: the prompt's chains and the
+        // token phase's streams share the chip instead of waiting for one another.
+        const long long prompt_groups = std::max<long long>(0, n_tokens - n_req) / 32 * n_qh;
+        if (in.defer_merge && knob_merge == 0 && use_one_launch(prompt_groups, max_q_len)) {
+            in.prompt = &a;
+            in.with_prompt = &with_prompt;
+        }
+        rc = run_step(in);
+        if (rc != SW_OK || with_prompt) return rc;
         if (max_q_len == 1) return SW_OK;          // no request can have more than one query
     }
 

@@ -42,6 +42,7 @@
 #include "sw_worklist.h"
 #include "sw_fused.h"
 #include "sw_lane_ops.h"
+#include "sw_prefill_split_body.h"
 
 #include <type_traits>
 
@@ -80,17 +81,32 @@ union Frag {
     half8_t h;
 };
 
-// 64 lanes x 16 bytes, global -> LDS, asynchronously; stream_lds with the K/V stream's cache policy.
-// (Functions of their own: with arguments whose types depend on a template parameter the
-// compiler leaves the kernel without its host side.)
+// 64 lanes x 16 bytes, global -> LDS, asynchronously; stream_lds (a base and an offset per lane)
+// with the K/V stream's cache policy.  (Functions of their own: with builtin arguments whose types
+// depend on a template parameter the compiler leaves the kernel without its host side.)
+template <bool ASM>
 __device__ __forceinline__ void load_lds(const void *src, unsigned char *to)
 {
-    __builtin_amdgcn_global_load_lds(src, to, 16, 0, 0);
+    if constexpr (ASM) sw_prefill::request_1k_at(src, sw_prefill::lds_offset(to));
+    else               __builtin_amdgcn_global_load_lds(src, to, 16, 0, 0);
 }
 
-__device__ __forceinline__ void stream_lds(const void *src, unsigned char *to)
+template <bool ASM>
+__device__ __forceinline__ void stream_lds(const char *base, unsigned off, unsigned char *to)
 {
-    __builtin_amdgcn_global_load_lds(src, to, 16, 0, kStream);
+    if constexpr (ASM) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0 nt"
+                     :: "s"(base), "v"(off), "s"(sw_prefill::lds_offset(to)) : "memory");
+    } else {
+        __builtin_amdgcn_global_load_lds(base + off, to, 16, 0, kStream);
+    }
+}
+
+// No LDS read moves above a wait for assembly requests, which the compiler does not know of.
+template <bool ASM>
+__device__ __forceinline__ void landed()
+{
+    if constexpr (ASM) asm volatile("" ::: "memory");
 }
 
 // Keeps a wave-uniform value in scalar registers from here on: whatever it is computed or
@@ -104,9 +120,15 @@ __device__ __forceinline__ void sw_pin(T &x)
 // D = head_dim.  A staged K or V row is 2 * D bytes and one load instruction (64 lanes x 16
 // bytes) brings kRowsPerLoad whole rows: four at D = 128, eight at D = 64, where a wave's two
 // tiles are half as large and twice the waves fit a compute unit.
-template <int D, int WAVES, int PER, bool FUSED, bool PAGED>
-__global__ __launch_bounds__(64 * WAVES, D == 128 ? 2 : (FUSED ? 3 : 4))
-void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int chunk_shift, int n_kvh, SwArgs a_rest)
+// ASM: the rows are requested by inline assembly (see request_1k), for a kernel whose LDS
+// arrays are one object: the compiler would hold every LDS read until all requests have landed.
+// `block`: the workgroup's number among the token-phase workgroups; lds, sm_q, sm_m, sm_l, sm_flag:
+// WAVES * kWaveLds bytes, 16 * kRowBytes + 1024 bytes (Q rows, then the append variant's new K row
+// and new V row), and what the waves exchange.
+template <int D, int WAVES, int PER, bool FUSED, bool PAGED, bool ASM>
+__device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_req, int max_len, int chunk_shift, int n_kvh,
+                                                 const SwArgs &a_rest, unsigned block, unsigned char *lds, unsigned char *sm_q,
+                                                 float (*sm_m)[16], float (*sm_l)[16], int *sm_flag)
 {
     constexpr int kRowBytes    = 2 * D;                    // a staged row (K pieces XOR-swizzled, no padding)
     constexpr int kRowShift    = D == 128 ? 8 : 7;
@@ -126,15 +148,6 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     a.chunk_shift = chunk_shift;
     a.chunk = 1 << chunk_shift;
     a.n_kvh = n_kvh;
-
-    __shared__ __attribute__((aligned(16))) unsigned char lds[WAVES * kWaveLds];
-    // Q rows, then (append variant) the new K row and the new V row.  One array: the
-    // compiler sees no ordinary store into the new rows' part -- they arrive by
-    // global->LDS load only -- and must not take it for never written.
-    __shared__ __attribute__((aligned(16))) unsigned char sm_q[16 * kRowBytes + 1024];
-    __shared__ float sm_m[WAVES][16];
-    __shared__ float sm_l[WAVES][16];
-    __shared__ int sm_flag;
 
     // -- phase: workgroup started
     // First of all the lengths: asking for them needs nothing but the leading arguments, which
@@ -190,10 +203,10 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     // of eight; numbers past the last item find no work).
     // h0 = the tile's first head within the group, gn = how many it has.
     const unsigned n_ht = (unsigned)(a.group + 15) >> 4;
-    unsigned item = blockIdx.x;
+    unsigned item = block;
     int ht = 0;
     if (n_ht > 1) {
-        const unsigned x = blockIdx.x & 7u, y = blockIdx.x >> 3;
+        const unsigned x = block & 7u, y = block >> 3;
         ht = (int)(y % n_ht);
         item = (y / n_ht) * 8u + x;
     }
@@ -216,8 +229,8 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
 
     // Rows of requests with no cached position get +0; no item exists for them, so
     // workgroup b < n_req looks after request b.
-    if (FUSED && blockIdx.x < (unsigned)a.n_req && sw_scanned_len<PER>(a, scan, (int)blockIdx.x) == 0)
-        sw_zero_rows<D>(a, (int)blockIdx.x);
+    if (FUSED && block < (unsigned)a.n_req && sw_scanned_len<PER>(a, scan, (int)block) == 0)
+        sw_zero_rows<D>(a, (int)block);
     const SwWork w = sw_lookup<PER>(a, scan, item);
     // -- phase: item known
     if (!w.valid) return;
@@ -254,7 +267,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
         const int row = kRowsPerLoad * wave + lrow;
         if (row < gn) {            // at most 16 rows: the later waves may stage nothing
             const uint16_t *src = a.q + (sw_q_row(a, r) * a.n_qh + g * a.group + h0 + row) * D + 8 * (piece ^ swizzle(row));
-            load_lds(src, sm_q + wave * 1024);
+            load_lds<ASM>(src, sm_q + wave * 1024);
         }
     }
 
@@ -265,7 +278,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     const int new_pos = (w.new_pos >= t_begin && w.new_pos < t_end) ? w.new_pos : -1;
     if (new_pos >= 0 && wave == 0) {
         const uint16_t *src = ((lrow & 1) ? a.v_new : a.k_new) + ((long long)r * a.n_kvh + g) * D + 8 * piece;
-        load_lds(src, sm_new);
+        load_lds<ASM>(src, sm_new);
     }
 
     // Row addressing: a wave-uniform 64-bit base plus a 32-bit byte offset per lane.
@@ -335,8 +348,8 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
             const int rho = kRowsPerLoad * n + lrow;
             const int tk  = min(t0 + rho, t_end - 1);
             const char *from = kslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
-            stream_lds(from + ((((unsigned)tk & (unsigned)in_block) << kRowShift) | (unsigned)((piece ^ swizzle(rho)) << 4)),
-                       wlds + n * 1024);
+            stream_lds<ASM>(from, (((unsigned)tk & (unsigned)in_block) << kRowShift) | (unsigned)((piece ^ swizzle(rho)) << 4),
+                            wlds + n * 1024);
         }
     };
     // V tile -> LDS, asynchronously, whole rows in token order; at D = 64, where a row covers
@@ -350,7 +363,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
         for (int n = 0; n < kLoads; ++n) {
             const int tv = min(t0 + v_slot(kRowsPerLoad * n + lrow), t_end - 1);
             const char *from = vslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
-            stream_lds(from + ((((unsigned)tv & (unsigned)in_block) << kRowShift) | (unsigned)(piece << 4)), vlds + n * 1024);
+            stream_lds<ASM>(from, (((unsigned)tv & (unsigned)in_block) << kRowShift) | (unsigned)(piece << 4), vlds + n * 1024);
         }
     };
     auto issue_k = [&](int t0, const TileBlocks &tb) {
@@ -375,6 +388,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
         // ---- S^T = K Q^T : two 16-token blocks, four 32-dim steps.
         // Outstanding, oldest first: K(t0), V(t0), kLoads each.
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoads));
+        landed<ASM>();
         // -- phase: K tile landed
         // the new position lies in the chunk's last tile, which is some wave's last tile
         const bool has_new = !MORE && new_pos >= t0 && new_pos < t0 + kTile;     // wave-uniform
@@ -462,6 +476,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
         // Outstanding, oldest first: V(t0), then K(next) if there is a next tile, kLoads each.
         if (MORE) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoads));
         else      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        landed<ASM>();
         // -- phase: V tile landed
         if (has_new) {
             // all of the wave's loads have landed: patch the staged V row, then store
@@ -530,6 +545,7 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     if (ti < n_tiles) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kLoads) & 0xc07f);   // and lgkmcnt(0)
     else              __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);    // vmcnt(0),  lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
+    landed<ASM>();
 
     if (ti < n_tiles) {
         while (ti + WAVES < n_tiles) {
@@ -607,9 +623,9 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
     if (FUSED && !alone) {
         // the workgroup that drew the unit's last ticket folds the chunks: every other one has
         // sent its pieces before it drew its own
-        if (threadIdx.x == 0) sm_flag = sw_fused_is_merger(a, unit, ticket, (int)nc) ? 1 : 0;
+        if (threadIdx.x == 0) *sm_flag = sw_fused_is_merger(a, unit, ticket, (int)nc) ? 1 : 0;
         __syncthreads();
-        if (sm_flag == 0) return;
+        if (*sm_flag == 0) return;
 #pragma unroll
         for (int k = 0; k < kMine; ++k) {
             const int idx = threadIdx.x + k * 64 * WAVES;
@@ -618,6 +634,54 @@ void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int
         }
     }
     // -- phase: merged
+}
+
+template <int D, int WAVES, int PER, bool FUSED, bool PAGED>
+__global__ __launch_bounds__(64 * WAVES, D == 128 ? 2 : (FUSED ? 3 : 4))
+void sw_decode_split_kernel(const int32_t *seq_lens, int n_req, int max_len, int chunk_shift, int n_kvh, SwArgs a)
+{
+    constexpr int kRowBytes = 2 * D;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[WAVES * 2 * kTile * kRowBytes];
+    // Q rows, then (append variant) the new K row and the new V row.  One array: the
+    // compiler sees no ordinary store into the new rows' part -- they arrive by
+    // global->LDS load only -- and must not take it for never written.
+    __shared__ __attribute__((aligned(16))) unsigned char sm_q[16 * kRowBytes + 1024];
+    __shared__ float sm_m[WAVES][16];
+    __shared__ float sm_l[WAVES][16];
+    __shared__ int sm_flag;
+    decode_workgroup<D, WAVES, PER, FUSED, PAGED, false>(seq_lens, n_req, max_len, chunk_shift, n_kvh, a, blockIdx.x,
+                                                         lds, sm_q, sm_m, sm_l, &sm_flag);
+}
+
+// A mixed batch's two phases in one launch (paper section 2.4): workgroups 0 .. n_prompt - 1 are the
+// key-split prompt kernel's, the others the token phase's.  The prompt's workgroups are few
+// and each a long chain of dependent tiles that leaves memory idle, the token phase's stream the
+// caches: in two launches the one waited for the other.  Prompt first, since a workgroup of
+// it runs four times as long.  Both kinds use one LDS area (the sum of their arrays would leave
+// one workgroup per compute unit).  63 token-phase requests of 1000 to 2600 cached tokens, 8
+// heads over one, beside a prompt of 1500: 30.0 -> 26.8 us with the combine kernel; 10
+// requests of 1800 to 11100, 8 heads over 8, beside two prompts of 103: 77.6 -> 53.5.
+union MixedLds {
+    sw_split::SplitLds<4> prompt;
+    struct {
+        __attribute__((aligned(16))) unsigned char lds[4 * 2 * kTile * 256];
+        __attribute__((aligned(16))) unsigned char q[16 * 256 + 1024];
+        float m[4][16], l[4][16];
+        int flag;
+    } token;
+};
+
+template <int PER, bool PAGED>
+__global__ __launch_bounds__(256, 2)
+void sw_mixed_kernel(const int32_t *seq_lens, int n_req, int max_len, int chunk_shift, int n_kvh, unsigned n_prompt,
+                     SwArgs d, SwPrefillArgs p)
+{
+    __shared__ MixedLds sm;
+    if (blockIdx.x < n_prompt)
+        sw_split::prompt_workgroup<4, PAGED>(p, blockIdx.x, sm.prompt);
+    else
+        decode_workgroup<128, 4, PER, false, PAGED, true>(seq_lens, n_req, max_len, chunk_shift, n_kvh, d, blockIdx.x - n_prompt,
+                                                          sm.token.lds, sm.token.q, sm.token.m, sm.token.l, &sm.token.flag);
 }
 
 }  // namespace
@@ -653,15 +717,54 @@ static hipError_t launch_per(const SwArgs &a, dim3 grid, hipStream_t stream, con
     }
 }
 
+static long long decode_blocks(const SwArgs &a)
+{
+    const long long blocks = (long long)a.n_req * a.n_kvh * a.n_chunks;
+    const int n_ht = (a.group + 15) / 16;
+    return n_ht > 1 ? (blocks + 7) / 8 * 8 * n_ht : blocks;      // see the kernel's numbering of head tiles
+}
+
 hipError_t sw_launch_decode_split(const SwArgs &a, hipStream_t stream, const SwLaunchEvents *ev)
 {
     if (!sw_decode_split_supported(a)) return hipErrorNotSupported;
-    long long blocks = (long long)a.n_req * a.n_kvh * a.n_chunks;
-    const int n_ht = (a.group + 15) / 16;
-    if (n_ht > 1) blocks = (blocks + 7) / 8 * 8 * n_ht;      // see the kernel's numbering of head tiles
+    const long long blocks = decode_blocks(a);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     if (a.head_dim == 128)
         return a.waves == 4 ? launch_per<128, 4>(a, grid, stream, ev) : launch_per<128, 8>(a, grid, stream, ev);
     return a.waves == 4 ? launch_per<64, 4>(a, grid, stream, ev) : launch_per<64, 8>(a, grid, stream, ev);
+}
+
+// Workgroups of the mixed kernel's prompt part (the prompt kernel's own grid), and whether its
+// (request, query block) items are numbered compactly.
+static long long mixed_prompt_blocks(const SwPrefillArgs &p, bool *compact)
+{
+    const long long pairs = sw_prefill_items(p, sw_prefill::kQPerWave, compact) * p.n_kvh;
+    return (pairs + 7) / 8 * 8 * p.group;
+}
+
+bool sw_mixed_supported(const SwArgs &d, const SwPrefillArgs &p)
+{
+    bool compact;
+    const long long n_prompt = mixed_prompt_blocks(p, &compact);
+    return d.head_dim == 128 && p.head_dim == 128 && sw_decode_split_supported(d) && d.waves == 4 && !d.units && !d.k_new
+        && sw_worklist_per(d.n_req) > 0 && n_prompt > 0 && n_prompt + decode_blocks(d) <= 0x7fffffffLL;
+}
+
+hipError_t sw_launch_mixed(const SwArgs &d, const SwPrefillArgs &p_in, hipStream_t stream, const SwLaunchEvents *ev)
+{
+    if (!sw_mixed_supported(d, p_in)) return hipErrorNotSupported;
+    SwPrefillArgs p = p_in;
+    bool compact;
+    const unsigned np = (unsigned)mixed_prompt_blocks(p, &compact);
+    p.compact = compact;
+    const dim3 grid((unsigned)(np + decode_blocks(d)));
+#define SW_MIXED_CASE(P) \
+    if (sw_worklist_per(d.n_req) == P) \
+        return d.block_table \
+            ? sw_launch(sw_mixed_kernel<P, true>, grid, dim3(256), 0, stream, ev, d.seq_lens, d.n_req, d.max_len, d.chunk_shift, d.n_kvh, np, d, p) \
+            : sw_launch(sw_mixed_kernel<P, false>, grid, dim3(256), 0, stream, ev, d.seq_lens, d.n_req, d.max_len, d.chunk_shift, d.n_kvh, np, d, p);
+    SW_MIXED_CASE(1) SW_MIXED_CASE(4) SW_MIXED_CASE(16)
+#undef SW_MIXED_CASE
+    return hipErrorInvalidValue;
 }

@@ -164,6 +164,9 @@ hipError_t sw_launch_partial_valu(const SwArgs &a, hipStream_t stream, const SwL
 // Matrix-core kernel, K and V staged through LDS (head_dim 128, groups up to 64, 4 or 8 waves).
 bool       sw_decode_split_supported(const SwArgs &a);
 hipError_t sw_launch_decode_split(const SwArgs &a, hipStream_t stream, const SwLaunchEvents *ev);
+// A mixed batch's token phase (two-kernel form, partial results to the workspace) and prompt phase in one launch.
+bool       sw_mixed_supported(const SwArgs &d, const SwPrefillArgs &p);
+hipError_t sw_launch_mixed(const SwArgs &d, const SwPrefillArgs &p, hipStream_t stream, const SwLaunchEvents *ev);
 // Merge of the chunks' partial results, normalisation and rounding to binary16.
 hipError_t sw_launch_combine(const SwArgs &a, hipStream_t stream, const SwLaunchEvents *ev);
 // Bound on the (request, block of q_block query tokens) items of a prompt-phase call, which
