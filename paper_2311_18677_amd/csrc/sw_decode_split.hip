@@ -109,6 +109,14 @@ __device__ __forceinline__ void landed()
     if constexpr (ASM) asm volatile("" ::: "memory");
 }
 
+// Two binary16 values, those that are not finite replaced by zero.
+__device__ __forceinline__ unsigned finite_halves(unsigned u)
+{
+    if ((u & 0x00007c00u) == 0x00007c00u) u &= 0xffff0000u;
+    if ((u & 0x7c000000u) == 0x7c000000u) u &= 0x0000ffffu;
+    return u;
+}
+
 // Keeps a wave-uniform value in scalar registers from here on: whatever it is computed or
 // loaded from has been waited for at this point.
 template <typename T>
@@ -379,8 +387,10 @@ __device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_
     // then V).  MORE says whether the wave has a further tile, whose loads are
     // then issued from here; it is a compile-time flag so that the waits in
     // between can count exactly which loads are still outstanding.
-    auto process_tile = [&](int t0, int t0_next, auto more_c) {
+    // CAREFUL: infinities in V, see the second walk below.
+    auto process_tile = [&](int t0, int t0_next, auto more_c, auto careful_c) {
         constexpr bool MORE = decltype(more_c)::value;
+        constexpr bool CAREFUL = decltype(careful_c)::value;
         // block ids of the next tile: requested first, needed only after QK
         TileBlocks nb;
         if (MORE) nb = find_blocks(t0_next);
@@ -462,7 +472,12 @@ __device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_
         Frag phi, plo;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const half2_t hi = __builtin_convertvector((float2_t){p[2 * j], p[2 * j + 1]}, half2_t);
+            half2_t hi = __builtin_convertvector((float2_t){p[2 * j], p[2 * j + 1]}, half2_t);
+            if (CAREFUL) {
+                // a weight below binary16's range is a weight all the same where its row is infinite
+                if (p[2 * j] > 0.f && hi[0] == (_Float16)0.f) hi[0] = (_Float16)0x1p-24f;
+                if (p[2 * j + 1] > 0.f && hi[1] == (_Float16)0.f) hi[1] = (_Float16)0x1p-24f;
+            }
             const half2_t lo = __builtin_convertvector(
                 (float2_t){p[2 * j] - (float)hi[0], p[2 * j + 1] - (float)hi[1]}, half2_t);
             phi.h[2 * j] = hi[0];
@@ -527,17 +542,22 @@ __device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_
             for (int j = 0; j < 4; ++j)
                 va.u[j] = __builtin_amdgcn_perm(vreg[2 * j + 1][w2], vreg[2 * j][w2], sel);
             o[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va.h, phi.h, o[e], 0, 0, 0);
+            if (CAREFUL) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) va.u[j] = finite_halves(va.u[j]);
+            }
             o[e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va.h, plo.h, o[e], 0, 0, 0);
         }
     };
 
 
     int ti = wave;
-    if (ti < n_tiles) {
-        const TileBlocks fb = find_blocks(t_begin + ti * kTile);
-        issue_k(t_begin + ti * kTile, fb);
-        issue_v(t_begin + ti * kTile, fb);
-    }
+    auto issue_tile = [&](int t0) {
+        const TileBlocks fb = find_blocks(t0);
+        issue_k(t0, fb);
+        issue_v(t0, fb);
+    };
+    if (ti < n_tiles) issue_tile(t_begin + ti * kTile);
     // -- phase: first loads issued
     // Q (and the new rows) must be in LDS before any wave goes on; the tile loads stay in flight
     // across the barrier.  Vector-memory operations complete in issue order, so
@@ -549,10 +569,33 @@ __device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_
 
     if (ti < n_tiles) {
         while (ti + WAVES < n_tiles) {
-            process_tile(t_begin + ti * kTile, t_begin + (ti + WAVES) * kTile, std::true_type{});
+            process_tile(t_begin + ti * kTile, t_begin + (ti + WAVES) * kTile, std::true_type{}, std::false_type{});
             ti += WAVES;
         }
-        process_tile(t_begin + ti * kTile, 0, std::false_type{});
+        process_tile(t_begin + ti * kTile, 0, std::false_type{}, std::false_type{});
+        if constexpr (D == 64) {
+            // An infinity in V times hi + lo is NaN wherever lo is not positive.  Finite rows leave
+            // finite sums (a weight is at most 2^kLazyBits), so where a sum is not finite the wave
+            // walks its tiles again, one at a time, with infinities in the hi product only: weight
+            // times value as the vector unit has it, which served this head size before.  (At
+            // head_dim 128 the pair's NaN is what the library has always given.)
+            float4_t spoiled = o[0] * 0.f;
+#pragma unroll
+            for (int e = 1; e < kBlocks; ++e) spoiled += o[e] * 0.f;
+            const float any = (spoiled[0] + spoiled[1]) + (spoiled[2] + spoiled[3]);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(any != 0.f) != 0, 0)) {
+                m = kNegBig;
+                l = 0.f;
+#pragma unroll
+                for (int e = 0; e < kBlocks; ++e) o[e] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (ti = wave; ti < n_tiles; ti += WAVES) {
+                    __builtin_amdgcn_s_waitcnt(0);      // nothing outstanding on the areas that are refilled
+                    issue_tile(t_begin + ti * kTile);
+                    process_tile(t_begin + ti * kTile, 0, std::false_type{}, std::true_type{});
+                }
+            }
+        }
     }
 
     // -- phase: tiles done
