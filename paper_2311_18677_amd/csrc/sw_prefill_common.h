@@ -401,6 +401,24 @@ __device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scal
     }
 }
 
+// What that rounding left of the weights, in binary16 again, and the lane's sum of it: with p it
+// makes the weights good to about 22 bits.
+__device__ __forceinline__ void rest_block(const float4_t (&s)[2], float scale_log2e, float neg_m, const Frag &p, Frag &rest,
+                                           float &rsum)
+{
+    const half2_t ones = {(_Float16)1.f, (_Float16)1.f};
+    rsum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float x = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1)], scale_log2e, neg_m)) - (float)p.h[2 * j];
+        const float y = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1) + 1], scale_log2e, neg_m)) - (float)p.h[2 * j + 1];
+        const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
+        rest.h[2 * j] = w[0];
+        rest.h[2 * j + 1] = w[1];
+        rsum = __builtin_amdgcn_fdot2(w, ones, rsum, false);
+    }
+}
+
 // The exact pass of one query block: raises the running maximum where a score of the tile lies
 // more than kLazyBits above it, rescales what has been accumulated and computes the tile's
 // weights again.  (weights_block takes the maximum as it stands.)

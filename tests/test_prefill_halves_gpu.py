@@ -85,3 +85,36 @@ def test_several_long_prompts_one_of_them_alone_in_its_last_steps():
         ref = oracle.decode_attn(q3, bufs["k_host"], bufs["v_host"], one, 3, n_qh, n_kvh, d, cfg.max_len,
                                  lay.stride_req, lay.stride_kvh, lay.stride_tok)
         assert_parity(got[starts[r] + i][None], ref[r:r + 1], "request %d row %d" % (r, i))
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,L,nq", [(64, 32, 901, 901), (64, 8, 863, 863), (16, 1, 3500, 3500), (64, 8, 3500, 865)])
+def test_no_further_from_64_bits_than_the_key_split_kernel(n_qh, n_kvh, L, nq):
+    """A row's weights are rounded to binary16 relative to a maximum of each wave's, whose own key's
+    weight is exact: four maxima in the key-split kernel, two here, which takes its waves' first
+    tiles with the rounding's rest.  Both norms are over n = nq * n_qh * d values whose roundings are
+    independent: each is good to one part in sqrt(2 n), and four of that are let pass."""
+    import torch
+    d, max_len = 128, L
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(L + nq)
+    lay = sw.sw_kv_layout(1, n_kvh, d, max_len)
+    k, v = (torch.randn(lay.total_elems, generator=gen, dtype=torch.float16, device="cuda:0") for _ in range(2))
+    q = torch.randn(nq, n_qh, d, generator=gen, dtype=torch.float16, device="cuda:0")
+    later = torch.arange(L, device="cuda:0")[None, :] > (L - nq + torch.arange(nq, device="cuda:0"))[:, None]
+    ref = torch.empty(nq, n_qh, d, dtype=torch.float64, device="cuda:0")
+    rows = [x.as_strided((n_kvh, L, d), (lay.stride_kvh, lay.stride_tok, 1)).double() for x in (k, v)]
+    for h in range(n_qh):
+        g = h // (n_qh // n_kvh)
+        scores = (q[:, h].double() @ rows[0][g].t().contiguous()) / d ** 0.5
+        ref[:, h] = torch.softmax(scores.masked_fill_(later, -float("inf")), dim=-1) @ rows[1][g]
+    err = {}
+    try:
+        for kernel in (0, 2):
+            sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, kernel)
+            out = torch.zeros_like(q)
+            sw.sw_mixed_attn(q, k, v, i32([L]), i32([0]), i32([nq]), out, nq, 1, n_qh, n_kvh, d, max_len, nq)
+            torch.cuda.synchronize()
+            err[kernel] = float((out.double() - ref).norm() / ref.norm())
+    finally:
+        sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, 0)
+    assert 0 < err[0] <= err[2] * (1 + 4 / (2 * nq * n_qh * d) ** 0.5), err
