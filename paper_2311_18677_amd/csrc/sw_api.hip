@@ -24,24 +24,27 @@ constexpr int kVersion = 200;   // 0.2.0
 // two on long prompts (batches of short prompts switch earlier, see causal_attn).
 constexpr long long kPrefillSharedMinGroups = 300;
 
-// Whether the shared-tile form with the key range in two halves serves a prompt call.  `groups`
-// counts the call's work in eight-wave workgroups of the whole form, avg_q its query tokens per
-// request: all the host knows of the lengths.  Up to about 200 groups the key-split kernel has
-// the shorter chains, from about 400 on there are workgroups enough for the whole form; in
-// between both leave the chip partly idle.  Measured, time without / with the halves:
-//   one prompt, 8 heads on one key/value head (groups): 4096 tokens (128) 56 / 69 us, 6144 (192)
-//   112 / 105, 8192 (256) 188 / 151, 12288 (384) 362 / 348, 14336 (448) 428 / 447; over the
-//   other head counts 1.01 to 1.46 times from 224 to 384 groups, 0.93 at 448;
-//   several of 3000 tokens and more: 1.07 to 1.11 at 320 groups where they are equally long and
-//   1.24 to 1.37 where they are not (the whole form waits for the longest), 0.96 at 384 for equal
-//   ones of 4096, 1.00 to 1.04 from 6144 on; below 300 groups unequal ones lose (0.81 to 1.03);
-//   several shorter ones lose or gain with their lengths (0.8 to 1.3), which the host does not know.
+// Whether the shared-tile form with the key range in two halves serves a prompt call.  `blocks` is
+// the number of its workgroups, one to a compute unit at a time; `groups` counts the work in
+// workgroups of the whole form, `whole_waves` waves each; avg_q: query tokens per request;
+// from_start: the queries are known to begin (nearly) at position 0.
+//   One request, up to two rounds of workgroups (432 to 512 blocks): the chains are half as long as
+//   the whole form's and tiles are shared, which the key-split kernel does not do.  Time of the
+//   other kernels over this one's, 1 to 64 heads: 1.02 to 1.25 for prompts from 865 tokens on, up
+//   to 1.26 behind earlier context; groups of five and seven, where the whole form's workgroups
+//   have as few waves, 1.06 to 1.7.  Below 432: 1.15 down to 0.99.
+//   Above two rounds the third is partly empty: behind earlier context (all chains alike) 0.92 to
+//   1.14, with short prompts 0.82 to 1.01.  Prompts of 4000 tokens and more have chains uneven
+//   enough to fill it: 1.03 to 1.25 up to 720 blocks, down to 0.96 at 790.
+//   Several requests: their lengths decide, which the host does not know (8 heads on one, 300 to
+//   340 groups: two of equal length 1.08 to 1.17, one twice the other 0.93 to 0.98).  Only where
+//   the whole form has fewer than eight waves does this one win throughout (1.01 to 2.1).
 // Groups of three heads make workgroups of six waves, which gain nothing (0.82 to 1.03).
-bool use_halves(long long groups, long long avg_q, int n_req, int columns)
+bool use_halves(long long blocks, long long groups, long long avg_q, int n_req, int columns, int whole_waves, bool from_start)
 {
     if (columns != 4) return false;
-    if (n_req == 1) return groups >= 208 && groups < 400;
-    return avg_q >= 3000 && groups >= 300 && groups < (avg_q < 5000 ? 345 : 400);
+    if (n_req > 1) return whole_waves < 8 && avg_q >= 3000 && groups >= 300 && groups < (avg_q < 5000 ? 345 : 400);
+    return blocks >= 432 && (blocks <= 512 || (blocks <= 720 && avg_q >= 4000 && from_start));
 }
 
 thread_local std::string t_last_error = "";
@@ -808,8 +811,8 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     if (which == 0) {
         // (in a mixed batch most requests are usually token-phase requests, one row each,
         // which the prompt kernel never sees: leave one row per request out of the estimate)
-        long long q_bound = std::min<long long>(n_tokens, (long long)n_req * max_q_len);
-        if (mixed) q_bound = std::max<long long>(0, q_bound - n_req);
+        const long long q_all = std::min<long long>(n_tokens, (long long)n_req * max_q_len);
+        const long long q_bound = mixed ? std::max<long long>(0, q_all - n_req) : q_all;
         const long long groups = (q_bound / (32 * shared_qw)) * n_kvh * (a.group / shared_hp);
         // short prompts make short chains of tiles, so fewer workgroups already suffice
         // (measured: 24 x 256 and 16 x 512 tokens gain 17-25 % from the shared-tile kernel)
@@ -817,7 +820,10 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         const long long need = avg_q <= 256 ? 192 : (avg_q <= 1024 ? 256 : kPrefillSharedMinGroups);
         which = groups >= need ? 1 : 2;
         sw_prefill_shape(a.group, 4, &halves_hp, &halves_qw);
-        if (use_halves(groups, avg_q, n_req, halves_hp * halves_qw)) which = 3;
+        const long long q_block = 32 * halves_qw;
+        const long long blocks = (q_all + q_block - 1) / q_block * n_kvh * (a.group / halves_hp);
+        const bool from_start = !mixed || max_len <= q_all + q_all / 8;
+        if (use_halves(blocks, groups, avg_q, n_req, halves_hp * halves_qw, shared_hp * shared_qw, from_start)) which = 3;
     }
     int split_waves = 4;
     if (which == 2) {
