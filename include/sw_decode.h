@@ -453,7 +453,8 @@ int sw_device_status(int *gave_up);
  *   SW_PARAM_PREFILL_WAVES  prompt-phase kernel: waves (32 query positions each) per
  *                      head in a workgroup (0 = library default; ignored if heads *
  *                      waves would exceed 8).  For the key-split kernel: waves per
- *                      workgroup, 2, 4 or 8.
+ *                      workgroup, 2, 4 or 8.  (With either set, the default choice is
+ *                      between the two kernels below.)
  *   SW_PARAM_PREFILL_KERNEL  0 = library default, 1 = the kernel that shares staged
  *                      K/V tiles among the waves of a workgroup (up to 8 heads of a group),
  *                      2 = the kernel that splits a query block's key range over the

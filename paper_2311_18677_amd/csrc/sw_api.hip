@@ -823,7 +823,9 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         const long long q_block = 32 * halves_qw;
         const long long blocks = (q_all + q_block - 1) / q_block * n_kvh * (a.group / halves_hp);
         const bool from_start = !mixed || max_len <= q_all + q_all / 8;
-        if (use_halves(blocks, groups, avg_q, n_req, halves_hp * halves_qw, shared_hp * shared_qw, from_start)) which = 3;
+        // (the caller's heads and waves are the other two kernels' shapes)
+        if (knob_hp == 0 && knob_qw == 0 &&
+            use_halves(blocks, groups, avg_q, n_req, halves_hp * halves_qw, shared_hp * shared_qw, from_start)) which = 3;
     }
     int split_waves = 4;
     if (which == 2) {

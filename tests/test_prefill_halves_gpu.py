@@ -122,6 +122,30 @@ def test_one_long_prompt_against_the_oracle(n_qh, n_kvh, L, nq, scale):
         assert np.array_equal(out2.cpu().numpy().view(np.uint16), dense.view(np.uint16)), bs
 
 
+@pytest.mark.parametrize("n_qh,n_kvh,n,key,value,kernel", [
+    (8, 1, 8192, sw.SW_PARAM_PREFILL_WAVES, 8, 2), (8, 1, 8192, sw.SW_PARAM_PREFILL_HEADS, 8, 2),
+    (64, 32, 901, sw.SW_PARAM_PREFILL_WAVES, 2, 2), (8, 1, 9700, sw.SW_PARAM_PREFILL_HEADS, 2, 1),
+    (8, 1, 9700, sw.SW_PARAM_PREFILL_WAVES, 1, 1),
+])
+def test_chosen_heads_and_waves_count(n_qh, n_kvh, n, key, value, kernel):
+    """A call that this kernel would serve, with the caller's heads or waves: the kernel whose shape
+    they are, with them."""
+    import torch
+    call, out = random_call(n_qh, n_kvh, [n], [n], n, False)
+    assert serving_kernel(call, out) == 3
+    try:
+        sw.sw_set_param(key, value)
+        assert serving_kernel(call, out) == kernel
+        if kernel == 2 and key == sw.SW_PARAM_PREFILL_WAVES:       # other waves, other sums
+            chosen = out.clone()
+            sw.sw_set_param(key, 4)
+            call()
+            torch.cuda.synchronize()
+            assert not torch.equal(chosen.view(torch.int16), out.view(torch.int16))
+    finally:
+        sw.sw_set_param(key, 0)
+
+
 def test_several_long_prompts_one_of_them_alone_in_its_last_steps():
     """Lengths far apart: waves of finished query blocks keep arriving at the barrier."""
     import torch
