@@ -231,16 +231,23 @@ bool fused_fits(size_t slots, int head_dim)
 
 // Mixed batches, four-wave key-split prompt kernel, token phase of more than four chunks: one
 // launch for both phases while the prompt's workgroups leave some of the chip's 512 places free,
-// or their chains are long and end one by one.  Measured, two launches against one, with 64
-// token-phase requests of 1000 to 2600 cached tokens, 8 query heads over one: beside one prompt
-// of 64 tokens 25.9 -> 20.0 us, of 256 24.8 -> 19.7, of 1500 30.0 -> 26.8; of 2000, 2500 and 3500
-// (32 to 64 requests) 35.9 -> 34.2, 41.8 -> 40.6, 55.2 -> 52.0; 40 requests of 1250 to 5000, 6 heads
-// over 2, 300 tokens 37.7 -> 27.2.  Where many short chains fill the chip the token phase still
-// waits: beside two prompts of 900 tokens 25.9 against 26.4, of 1500 36.1 against 36.7, 32
-// heads and 800 tokens 46.2 against 48.0.
-bool use_one_launch(long long prompt_groups, int max_q_len)
+// or their chains are long and end one by one.  `units`: (request, key/value head) pairs.
+// Measured, two launches against one, with 64 token-phase requests of 1000 to 2600 cached tokens,
+// 8 query heads over one: beside one prompt of 64 tokens 25.9 -> 20.0 us, of 256 24.8 -> 19.7, of
+// 1500 30.0 -> 26.8; of 2000, 2500 and 3500 (32 to 64 requests) 35.9 -> 34.2, 41.8 -> 40.6, 55.2 ->
+// 52.0; 40 requests of 1250 to 5000, 6 heads over 2, 300 tokens 37.7 -> 27.2.  Where many short
+// chains fill the chip the token phase still waits: beside two prompts of 900 tokens 25.9 against
+// 26.4, of 1500 36.1 against 36.7, 32 heads and 800 tokens 46.2 against 48.0.  The more units the
+// token phase has, the more of the call is its own streaming, which places held by prompts only
+// thin out: time of two launches over one's with 250 prompt workgroups 1.02 to 1.25 at up to 200
+// units, 0.99 to 1.05 at 256, 0.98 at 512 and more; with 60 of them 1.01 to 1.09 at 800; with
+// long chains 1.0 to 1.4 up to a product of 100000, 0.96 to 1.0 beyond.  (Within the lines it is
+// down to 0.96 where the token phase by itself just fits the places: 16 heads over one, 64
+// requests of 1000 to 2600 and several prompts of 60 to 130 tokens.)
+bool use_one_launch(long long prompt_groups, long long units, int max_q_len)
 {
-    return prompt_groups <= 440 || max_q_len >= 1600;
+    if (prompt_groups <= 440 && prompt_groups * units <= 60000) return true;
+    return max_q_len >= 1600 && prompt_groups <= 900 && prompt_groups * units <= 100000;
 }
 
 // Everything one step needs, dense or block-table.
@@ -895,7 +902,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         // Both phases in one launch, the combine kernel after it: the prompt's chains and the
         // token phase's streams share the chip instead of waiting for one another.
         const long long prompt_groups = std::max<long long>(0, n_tokens - n_req) / 32 * n_qh;
-        if (in.defer_merge && knob_merge == 0 && use_one_launch(prompt_groups, max_q_len)) {
+        if (in.defer_merge && knob_merge == 0 && use_one_launch(prompt_groups, (long long)n_req * n_kvh, max_q_len)) {
             in.prompt = &a;
             in.with_prompt = &with_prompt;
         }

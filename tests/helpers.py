@@ -1,4 +1,6 @@
 """Shared test helpers: the parity rule and the oracle call on packed caches."""
+import ctypes
+
 import numpy as np
 
 import oracle
@@ -38,3 +40,43 @@ def assert_parity(out_f16, ref, what=""):
     assert max_abs <= MAX_ABS, "%s: max abs error %.3e > %.1e" % (what, max_abs, MAX_ABS)
     assert rel <= MAX_REL_L2, "%s: max row rel-L2 %.3e > %.1e" % (what, rel, MAX_REL_L2)
     return max_abs, rel, whole
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint), ("y", ctypes.c_uint), ("z", ctypes.c_uint)]
+
+
+class _KernelNodeParams(ctypes.Structure):                  # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def launches(call):
+    """[(workgroups, threads of one)] of the kernels that call(stream) enqueues, in order: the call is
+    recorded into a graph, which is read and dropped.  (One call before, to size the workspace.)"""
+    import torch
+    from paper_2311_18677_amd import binding as sw
+    hip = ctypes.CDLL(sw.LIB_PATH)                          # symbols of the runtime it is linked to
+
+    def ok(rc):
+        assert rc == 0, "HIP error %d" % rc
+
+    stream = torch.cuda.Stream()
+    call(stream)
+    stream.synchronize()
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    ok(hip.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 1))       # thread-local
+    try:
+        call(stream)
+    finally:
+        ok(hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)))
+    ok(hip.hipGraphGetNodes(graph, None, ctypes.byref(n)))
+    nodes = (ctypes.c_void_p * n.value)()
+    ok(hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)))
+    got = []
+    for node in nodes:
+        p = _KernelNodeParams()
+        ok(hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)))
+        got.append((p.grid.x, p.block.x))
+    ok(hip.hipGraphDestroy(graph))
+    return got
