@@ -442,17 +442,38 @@ __device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_
 // wait-count pass holds an LDS read that may alias a pending request of the builtin form (every
 // transposing read does) until all of them have landed; the kernels' own waits count exactly.
 // (No output register: nothing of the instruction is outstanding for the register allocator.)
+// The compiler's hazard pass does not know the instruction either.  The wait state it needs after
+// M0 is written is here; the five after a vector instruction (v_readfirstlane) wrote the scalar
+// base are settled()'s, which every base must have passed.  (All five in each request cost 2 to
+// 7 % of the key-split kernel's time.)
+// (M0 is a register the compiler keeps for itself; it takes the clobber, and so no value of its own
+// across the statement, with a warning.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void request_1k(const char *base, unsigned off, unsigned lds_at)
 {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
-                 :: "s"(base), "v"(off), "s"(lds_at) : "memory");
+                 :: "s"(base), "v"(off), "s"(lds_at) : "m0", "memory");
 }
 
-// (the same with a full address per lane)
+// (the same with a full address per lane, in vector registers)
 __device__ __forceinline__ void request_1k_at(const void *src, unsigned lds_at)
 {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(src), "s"(lds_at) : "memory");
+                 :: "v"(src), "s"(lds_at) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+
+// Bases for the requests above, in scalar registers and long enough ago: whatever instruction
+// computed them, requests may use them from here on.
+__device__ __forceinline__ void settled(const char *&base) { asm volatile("s_nop 4" : "+s"(base)); }
+
+template <int N>
+__device__ __forceinline__ void settled(const char *(&base)[N])
+{
+#pragma unroll
+    for (int n = 0; n < N; ++n) asm volatile("" : "+s"(base[n]));
+    asm volatile("s_nop 4");
 }
 
 // LDS offset of a __shared__ object, for the requests above.

@@ -95,6 +95,8 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     const long long slab = PAGED ? (long long)g * a.stride_kvh : (long long)r * a.stride_req + (long long)g * a.stride_kvh;
     const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * slab;
     const char *vslab = reinterpret_cast<const char *>(a.v) + 2 * slab;
+    settled(kslab);
+    settled(vslab);
     const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
     const int in_block = PAGED ? (1 << a.block_shift) - 1 : ~0;
 
@@ -130,7 +132,9 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
                 id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
                 block_off = 2 * (long long)id * a.stride_block;
             }
-            request_1k((IS_V ? vslab : kslab) + block_off,
+            const char *base = (IS_V ? vslab : kslab) + block_off;
+            if (PAGED) settled(base);
+            request_1k(base,
                        (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)(piece << 4),
                        lds0 + (IS_V ? kVBase : 0) + B * kStepBytes + (j >> 3) * kTileBytes + n * 1024);
         }

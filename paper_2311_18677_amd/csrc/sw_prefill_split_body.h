@@ -85,6 +85,8 @@ __device__ __forceinline__ void prompt_workgroup(const SwPrefillArgs &a, unsigne
     const long long slab = PAGED ? (long long)g * a.stride_kvh : (long long)r * a.stride_req + (long long)g * a.stride_kvh;
     const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * slab;
     const char *vslab = reinterpret_cast<const char *>(a.v) + 2 * slab;
+    settled(kslab);
+    settled(vslab);
     const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
     const int in_block = PAGED ? (1 << a.block_shift) - 1 : ~0;
 
@@ -178,15 +180,22 @@ __device__ __forceinline__ void prompt_workgroup(const SwPrefillArgs &a, unsigne
                 request_1k(kslab, tile + (n >> 2) * 4096 + koff[n & 3], k_at + n * 1024);
         } else if (PAGED && t0 + kTile <= L) {
             const long long in_blk = (long long)(((unsigned)t0 & (unsigned)in_block) << 8);
+            const char *base[8];
 #pragma unroll
-            for (int n = 0; n < 8; ++n)
-                request_1k(kslab + (tb.off[n] + in_blk), pk_off[n], k_at + n * 1024);
+            for (int n = 0; n < 8; ++n) base[n] = kslab + (tb.off[n] + in_blk);
+            settled(base);
+#pragma unroll
+            for (int n = 0; n < 8; ++n) request_1k(base[n], pk_off[n], k_at + n * 1024);
         } else {
+            const char *base[8];
+#pragma unroll
+            for (int n = 0; n < 8; ++n) base[n] = kslab + tb.off[n];
+            settled(base);
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
                 const int rho = 4 * n + gq;
                 const int t = min(t0 + rho, L - 1);      // rows past the context repeat its last row (masked)
-                request_1k(kslab + tb.off[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ (rho & 15)) << 4),
+                request_1k(base[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ (rho & 15)) << 4),
                            k_at + n * 1024);
             }
         }
@@ -199,15 +208,22 @@ __device__ __forceinline__ void prompt_workgroup(const SwPrefillArgs &a, unsigne
                 request_1k(vslab, tile + (n >> 1) * 2048 + voff[n & 1], v_at + n * 1024);
         } else if (PAGED && t0 + kTile <= L) {
             const long long in_blk = (long long)(((unsigned)t0 & (unsigned)in_block) << 8);
+            const char *base[8];
 #pragma unroll
-            for (int n = 0; n < 8; ++n)
-                request_1k(vslab + (tb.off[n] + in_blk), pv_off[n], v_at + n * 1024);
+            for (int n = 0; n < 8; ++n) base[n] = vslab + (tb.off[n] + in_blk);
+            settled(base);
+#pragma unroll
+            for (int n = 0; n < 8; ++n) request_1k(base[n], pv_off[n], v_at + n * 1024);
         } else {
+            const char *base[8];
+#pragma unroll
+            for (int n = 0; n < 8; ++n) base[n] = vslab + tb.off[n];
+            settled(base);
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
                 const int rho = 4 * n + gq;
                 const int t = min(t0 + rho, L - 1);
-                request_1k(vslab + tb.off[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ v_swizzle(rho)) << 4),
+                request_1k(base[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ v_swizzle(rho)) << 4),
                            v_at + n * 1024);
             }
         }
