@@ -184,3 +184,53 @@ def test_an_appended_infinite_row(bs):
     assert_same_kind(bufs["out"].cpu().numpy(), ref, "append")
     assert np.array_equal(bufs["k_cache"].cpu().numpy().view(np.uint16), k_ref)
     assert np.array_equal(bufs["v_cache"].cpu().numpy().view(np.uint16), v_ref)
+
+
+@pytest.mark.parametrize("waves", [4, 8])
+@pytest.mark.parametrize("combine", [1, 2])
+@pytest.mark.parametrize("n_req,n_qh,n_kvh", [(64, 4, 2), (65, 4, 2), (256, 3, 1), (257, 3, 1), (1024, 2, 1), (1025, 2, 1)])
+def test_every_size_class_of_the_batch(n_req, n_qh, n_kvh, combine, waves):
+    """The lengths are scanned in a form per size class (64, 256 and 1024 requests); four and eight waves
+    walk the tiles of a chunk."""
+    import torch
+    lens = [(37 * r + 11 * (r // 7)) % 301 for r in range(n_req)]          # zeros among them, up to five chunks of 64
+    cfg = wl.custom_config("d64s", n_req, n_qh, n_kvh, D, 300)
+    batch = wl.make_batch(cfg, seed=6800 + n_req, seq_lens=lens)
+    bufs = sw.upload_batch(batch, pad_bits=0x7E00)
+    lay = bufs["layout"]
+    ref = oracle.decode_attn(batch.q, bufs["k_host"], bufs["v_host"], batch.seq_lens, n_req, n_qh, n_kvh, D,
+                             cfg.max_len, lay.stride_req, lay.stride_kvh, lay.stride_tok)
+    sw.sw_set_param(sw.SW_PARAM_COMBINE, combine)
+    sw.sw_set_param(sw.SW_PARAM_WAVES, waves)
+    try:
+        for chunk in (64, 256):                       # a chunk of 64 runs four waves whatever is asked for
+            sw.sw_set_param(sw.SW_PARAM_CHUNK, chunk)
+            bufs["out"].fill_(float("nan"))
+            sw.run_batch(bufs, cfg)
+            torch.cuda.synchronize()
+            dense = bufs["out"].cpu().numpy()
+            assert_parity(dense, ref, "chunk %d" % chunk)
+            pb = sw.upload_paged_batch(batch, 8, pad_bits=0x7E00, seed=n_req)
+            sw.run_paged_batch(pb, cfg)
+            torch.cuda.synchronize()
+            assert np.array_equal(pb["out"].cpu().numpy().view(np.uint16), dense.view(np.uint16)), chunk
+    finally:
+        for key in (sw.SW_PARAM_COMBINE, sw.SW_PARAM_WAVES, sw.SW_PARAM_CHUNK):
+            sw.sw_set_param(key, 0)
+
+
+def test_the_default_takes_the_matrix_core_kernel():
+    """No parameter forces it at this head size; the two kernels round differently."""
+    import torch
+    cfg = wl.custom_config("d64k", 8, 8, 2, D, 600)
+    bufs = sw.upload_batch(wl.make_batch(cfg, seed=6900, seq_lens=[600, 599, 512, 300, 257, 100, 33, 5]))
+    bits = []
+    try:
+        for kernel in (1, 0):
+            sw.sw_set_param(sw.SW_PARAM_KERNEL, kernel)
+            sw.run_batch(bufs, cfg)
+            torch.cuda.synchronize()
+            bits.append(bufs["out"].cpu().numpy().view(np.uint16).copy())
+    finally:
+        sw.sw_set_param(sw.SW_PARAM_KERNEL, 0)
+    assert not np.array_equal(bits[0], bits[1])
