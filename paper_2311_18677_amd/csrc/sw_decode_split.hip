@@ -98,7 +98,7 @@ __device__ __forceinline__ void stream_lds(const char *base, unsigned off, unsig
 {
     if constexpr (ASM) {
         // (wait states: see request_1k)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0 nt"
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %0 nt"
                      :: "s"(base), "v"(off), "s"(sw_prefill::lds_offset(to)) : "m0", "memory");
     } else {
         __builtin_amdgcn_global_load_lds(base + off, to, 16, 0, kStream);
@@ -302,10 +302,6 @@ __device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_
     // of four positions, and only then, its two halves have bases of their own.
     const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * ((long long)r * a.stride_req + (long long)g * a.stride_kvh);
     const char *vslab = reinterpret_cast<const char *>(a.v) + 2 * ((long long)r * a.stride_req + (long long)g * a.stride_kvh);
-    if constexpr (ASM && !PAGED) {
-        sw_prefill::settled(kslab);
-        sw_prefill::settled(vslab);
-    }
     // the table is read-only for the whole launch: read it through the constant address
     // space so that wave-uniform entries come in over the scalar path
     const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
@@ -359,18 +355,11 @@ __device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_
     const bool halves = PAGED && kQuads == 2 && a.block_shift == 2;
     auto issue_k_from = [&](int t0, const TileBlocks &tb, auto halves_c) {
         constexpr bool HALVES = decltype(halves_c)::value;
-        const char *base[kLoads];
-        if constexpr (ASM && PAGED) {
-#pragma unroll
-            for (int n = 0; n < kLoads; ++n) base[n] = kslab + tb.off[kQuads * n];
-            sw_prefill::settled(base);
-        }
 #pragma unroll
         for (int n = 0; n < kLoads; ++n) {
             const int rho = kRowsPerLoad * n + lrow;
             const int tk  = min(t0 + rho, t_end - 1);
-            const char *from = ASM && PAGED ? base[n]
-                                            : kslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
+            const char *from = kslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
             stream_lds<ASM>(from, (((unsigned)tk & (unsigned)in_block) << kRowShift) | (unsigned)((piece ^ swizzle(rho)) << 4),
                             wlds + n * 1024);
         }
@@ -382,17 +371,10 @@ __device__ __forceinline__ void decode_workgroup(const int32_t *seq_lens, int n_
     auto v_slot = [](int row) { return D == 128 ? row : row ^ ((row >> 2) & 1); };      // its own inverse
     auto issue_v_from = [&](int t0, const TileBlocks &tb, auto halves_c) {
         constexpr bool HALVES = decltype(halves_c)::value;
-        const char *base[kLoads];
-        if constexpr (ASM && PAGED) {
-#pragma unroll
-            for (int n = 0; n < kLoads; ++n) base[n] = vslab + tb.off[kQuads * n];
-            sw_prefill::settled(base);
-        }
 #pragma unroll
         for (int n = 0; n < kLoads; ++n) {
             const int tv = min(t0 + v_slot(kRowsPerLoad * n + lrow), t_end - 1);
-            const char *from = ASM && PAGED ? base[n]
-                                            : vslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
+            const char *from = vslab + (HALVES && lrow >= 4 ? tb.off[kQuads * n + kQuads - 1] : tb.off[kQuads * n]);
             stream_lds<ASM>(from, (((unsigned)tv & (unsigned)in_block) << kRowShift) | (unsigned)(piece << 4), vlds + n * 1024);
         }
     };

@@ -444,16 +444,23 @@ __device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_
 // (No output register: nothing of the instruction is outstanding for the register allocator.)
 // The compiler's hazard pass does not know the instruction either.  The wait state it needs after
 // M0 is written is here; the five after a vector instruction (v_readfirstlane) wrote the scalar
-// base are settled()'s, which every base must have passed.  (All five in each request cost 2 to
-// 7 % of the key-split kernel's time.)
+// base are here unless SETTLED, whose bases have passed settled(): they stay the same from tile to
+// tile.  (All five in each request cost 2 to 7 % of the key-split kernel's time over dense caches;
+// over block tables, where every request has a base of its own, they cost nothing measurable.)
 // (M0 is a register the compiler keeps for itself; it takes the clobber, and so no value of its own
 // across the statement, with a warning.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+template <bool SETTLED>
 __device__ __forceinline__ void request_1k(const char *base, unsigned off, unsigned lds_at)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
-                 :: "s"(base), "v"(off), "s"(lds_at) : "m0", "memory");
+    if constexpr (SETTLED) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
+                     :: "s"(base), "v"(off), "s"(lds_at) : "m0", "memory");
+    } else {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %0"
+                     :: "s"(base), "v"(off), "s"(lds_at) : "m0", "memory");
+    }
 }
 
 // (the same with a full address per lane, in vector registers)
@@ -467,14 +474,6 @@ __device__ __forceinline__ void request_1k_at(const void *src, unsigned lds_at)
 // Bases for the requests above, in scalar registers and long enough ago: whatever instruction
 // computed them, requests may use them from here on.
 __device__ __forceinline__ void settled(const char *&base) { asm volatile("s_nop 4" : "+s"(base)); }
-
-template <int N>
-__device__ __forceinline__ void settled(const char *(&base)[N])
-{
-#pragma unroll
-    for (int n = 0; n < N; ++n) asm volatile("" : "+s"(base[n]));
-    asm volatile("s_nop 4");
-}
 
 // LDS offset of a __shared__ object, for the requests above.
 __device__ __forceinline__ unsigned lds_offset(const void *p)

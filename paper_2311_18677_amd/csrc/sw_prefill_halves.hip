@@ -132,9 +132,7 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
                 id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
                 block_off = 2 * (long long)id * a.stride_block;
             }
-            const char *base = (IS_V ? vslab : kslab) + block_off;
-            if (PAGED) settled(base);
-            request_1k(base,
+            request_1k<!PAGED>((IS_V ? vslab : kslab) + block_off,
                        (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)(piece << 4),
                        lds0 + (IS_V ? kVBase : 0) + B * kStepBytes + (j >> 3) * kTileBytes + n * 1024);
         }

@@ -177,25 +177,18 @@ __device__ __forceinline__ void prompt_workgroup(const SwPrefillArgs &a, unsigne
             const unsigned tile = (unsigned)t0 << 8;
 #pragma unroll
             for (int n = 0; n < 8; ++n)
-                request_1k(kslab, tile + (n >> 2) * 4096 + koff[n & 3], k_at + n * 1024);
+                request_1k<true>(kslab, tile + (n >> 2) * 4096 + koff[n & 3], k_at + n * 1024);
         } else if (PAGED && t0 + kTile <= L) {
             const long long in_blk = (long long)(((unsigned)t0 & (unsigned)in_block) << 8);
-            const char *base[8];
 #pragma unroll
-            for (int n = 0; n < 8; ++n) base[n] = kslab + (tb.off[n] + in_blk);
-            settled(base);
-#pragma unroll
-            for (int n = 0; n < 8; ++n) request_1k(base[n], pk_off[n], k_at + n * 1024);
+            for (int n = 0; n < 8; ++n)
+                request_1k<false>(kslab + (tb.off[n] + in_blk), pk_off[n], k_at + n * 1024);
         } else {
-            const char *base[8];
-#pragma unroll
-            for (int n = 0; n < 8; ++n) base[n] = kslab + tb.off[n];
-            settled(base);
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
                 const int rho = 4 * n + gq;
                 const int t = min(t0 + rho, L - 1);      // rows past the context repeat its last row (masked)
-                request_1k(base[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ (rho & 15)) << 4),
+                request_1k<false>(kslab + tb.off[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ (rho & 15)) << 4),
                            k_at + n * 1024);
             }
         }
@@ -205,25 +198,18 @@ __device__ __forceinline__ void prompt_workgroup(const SwPrefillArgs &a, unsigne
             const unsigned tile = (unsigned)t0 << 8;
 #pragma unroll
             for (int n = 0; n < 8; ++n)
-                request_1k(vslab, tile + (n >> 1) * 2048 + voff[n & 1], v_at + n * 1024);
+                request_1k<true>(vslab, tile + (n >> 1) * 2048 + voff[n & 1], v_at + n * 1024);
         } else if (PAGED && t0 + kTile <= L) {
             const long long in_blk = (long long)(((unsigned)t0 & (unsigned)in_block) << 8);
-            const char *base[8];
 #pragma unroll
-            for (int n = 0; n < 8; ++n) base[n] = vslab + (tb.off[n] + in_blk);
-            settled(base);
-#pragma unroll
-            for (int n = 0; n < 8; ++n) request_1k(base[n], pv_off[n], v_at + n * 1024);
+            for (int n = 0; n < 8; ++n)
+                request_1k<false>(vslab + (tb.off[n] + in_blk), pv_off[n], v_at + n * 1024);
         } else {
-            const char *base[8];
-#pragma unroll
-            for (int n = 0; n < 8; ++n) base[n] = vslab + tb.off[n];
-            settled(base);
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
                 const int rho = 4 * n + gq;
                 const int t = min(t0 + rho, L - 1);
-                request_1k(base[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ v_swizzle(rho)) << 4),
+                request_1k<false>(vslab + tb.off[n], (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)((n16 ^ v_swizzle(rho)) << 4),
                            v_at + n * 1024);
             }
         }
