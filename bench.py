@@ -343,7 +343,8 @@ def main_prefill(args):
         call(sets[i % n_sets], stream)
     k_us_sum, c_us_sum, n_rec = sw.sw_prof_stop()
     if mixed:
-        # two records per call: the token-phase kernels (partial + merge), then the prompt kernel
+        # two records per call: the launch of both phases, then the combine kernel -- or, with the phases in
+        # launches of their own, the token-phase kernels, then the prompt kernel (the merge in one of the two)
         kernel_us = (k_us_sum + c_us_sum) / prof_calls
         n_rec = prof_calls
     else:
@@ -444,8 +445,8 @@ def main_prefill(args):
         line["config"]["algorithmic_bytes_per_step"] = kv
         line["roofline"] = {"bound": "hbm", "achieved": gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                             "frac": gbps / HBM_PEAK_GBPS, "traffic": None,
-                            "kernel": "token-phase partial kernel, then the prompt kernel with the merge of the token-phase "
-                                      "chunks riding along (sum of the kernels' times)",
+                            "kernel": "both phases' kernels and the merge of the token-phase chunks (sum of the "
+                                      "kernels' times)",
                             "kernel_us": kernel_us, "bytes_per_launch": kv, "launches_timed": n_rec,
                             "tflops": achieved}
         if cpu_baseline:

@@ -254,11 +254,12 @@ int sw_advance_lens(int32_t *seq_lens, int n_req, int max_len, void *stream);
  * sw_decode_attn.  Which of the library's prompt kernels runs depends on the call's
  * size (n_tokens, n_req, the head counts); they sum in different orders, so a prompt's
  * result may differ in the last bits between a small and a large batch.  Under any of
- * them it does not depend on the other requests of the batch.  The launch is sized by the smaller of n_req * max_len and about
- * n_tokens + 64 * n_req query tokens, so a batch of a few long and many short prompts
- * costs what its tokens cost.  Weights enter the second matrix product rounded to binary16 (the
- * normaliser sums them in binary32 before that rounding); results differ from the fp64
- * definition by about 1e-3 absolute at most for values of order one.
+ * them it does not depend on the other requests of the batch.  The launch is sized by
+ * the smaller of n_req * max_len and about n_tokens + 64 * n_req query tokens, so a
+ * batch of a few long and many short prompts costs what its tokens cost.  Weights enter
+ * the second matrix product rounded to binary16 (the normaliser is the sum, in binary32,
+ * of the rounded weights); results differ from the fp64 definition by about 1e-3
+ * absolute at most for values of order one.
  */
 int sw_prefill_attn(const void *q, const void *k_cache, const void *v_cache,
                     const int32_t *seq_lens, const int32_t *q_starts, void *out, long long n_tokens,
@@ -455,7 +456,9 @@ int sw_device_status(int *gave_up);
  *                      waves would exceed 8).  For the key-split kernel: waves per
  *                      workgroup, 2, 4 or 8.  (With either set, the default choice is
  *                      between the two kernels below.)
- *   SW_PARAM_PREFILL_KERNEL  0 = library default, 1 = the kernel that shares staged
+ *   SW_PARAM_PREFILL_KERNEL  0 = library default (one of these two, or, for one or a few
+ *                      long prompts, the first one's form with the keys in two halves,
+ *                      which no value forces), 1 = the kernel that shares staged
  *                      K/V tiles among the waves of a workgroup (up to 8 heads of a group),
  *                      2 = the kernel that splits a query block's key range over the
  *                      waves of a workgroup.  The two differ by rounding only.
@@ -484,7 +487,10 @@ int sw_get_param(int key, int *value);
  * the recorded events and reports, in microseconds summed over the recorded
  * calls, the device time of the partial kernel and of the combine kernel
  * (0 when the chunks are merged in the same launch),
- * and how many calls were recorded.  Pointers are host memory.
+ * and how many calls were recorded.  A mixed call makes two records, and both count as
+ * "partial": with its phases in one launch that launch and the combine kernel, otherwise
+ * the token-phase kernel and the prompt kernel (the merge is in the latter, or the
+ * combine kernel's time is reported as such).  Pointers are host memory.
  */
 int sw_prof_start(int capacity);
 int sw_prof_stop(double *partial_us_sum, double *combine_us_sum, int *n_calls);

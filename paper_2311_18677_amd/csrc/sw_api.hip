@@ -202,9 +202,14 @@ int default_chunk(int n_req, int n_kvh, int max_len)
     return chunk;
 }
 
-// Which partial kernel serves a shape when the caller has not forced one: the matrix-core kernel
-// was the faster one on every shape tried at either head size, from 4 requests of up to 128
-// positions to 200 of 1500, one to sixteen heads on a key/value head (1.0 to 3.7 times).
+// Which partial kernel serves a shape when the caller has not forced one: the matrix-core kernel.
+// Vector-ALU kernel's time over its, at head_dim 64 from 1 to 300 requests of 16 to 30000 positions:
+// 1.1 to 6 with several heads to a key/value head, 1.0 to 2.6 with one -- but for tiny caches in
+// very large batches without sharing, where a workgroup has little to read and what it does to stage
+// and merge tiles counts (300 requests, 32 heads, max_len 16 / 64 / 128 / 200: 0.84 / 0.89 / 0.94 /
+// 0.99; 14 heads 0.89 / 0.92 / 0.99 / 1.01; 46 requests of 32 heads 0.92 / 0.99 / 1.06; 75 to 131 of
+// them 1.4 to 1.8).  No line is drawn there: a choice by the number of requests would make a
+// request's bits depend on its batch.
 int default_kernel(const SwArgs &a)
 {
     return sw_decode_split_supported(a) ? 2 : 1;
@@ -794,16 +799,15 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     a.group = n_qh / n_kvh;
     a.head_dim = head_dim;
     a.max_len = max_len;
-    // Two kernels, the second in two forms.  The shared-tile kernel stages every K/V tile once for the eight waves of
-    // a workgroup (the heads of a group, or more query positions of one head) and runs at a
-    // steady 41-45 % of the matrix peak once its workgroups fill the chip more than once;
-    // with fewer its time is that of the longest prompt's last block.  The key-split kernel
-    // gives every (32 queries, head) pair a workgroup of its own and splits its keys among
-    // the waves: four times the workgroups, each a quarter as long, but no tile is shared.
-    // Measured crossover: about 300 eight-wave workgroups, i.e. query tokens x heads of
-    // about 77000 (one 12288-token prompt or ten 1024-token prompts at 8 heads); less for
-    // batches of short prompts.  The choice
-    // looks at the call's number of query tokens, which the host knows; inside either kernel
+    // Two kernels, the first in two forms (the other: see use_halves).  The shared-tile kernel
+    // stages every K/V tile once for the eight waves of a workgroup (the heads of a group, or
+    // more query positions of one head) and runs at a steady 41-45 % of the matrix peak once
+    // its workgroups fill the chip more than once; with fewer its time is that of the longest
+    // prompt's last block.  The key-split kernel gives every (32 queries, head) pair a workgroup
+    // of its own and splits its keys among the waves: four times the workgroups, each a quarter
+    // as long, but no tile is shared.  Measured crossover: about 300 eight-wave workgroups, i.e.
+    // query tokens x heads of about 77000 (one 12288-token prompt or ten 1024-token prompts at 8
+    // heads); less for batches of short prompts.  The choice looks at the call's number of query tokens, which the host knows; inside either kernel
     // a request's result does not depend on the rest of its batch.
     int shared_hp, shared_qw;
     sw_prefill_shape(a.group, 8, &shared_hp, &shared_qw);

@@ -31,9 +31,12 @@
 // compute unit; at 64 it owns 8 KB and four (three in the single-launch form, whose merge needs
 // registers) fit, so as many bytes are in flight.  At head_dim 64 the vector-ALU kernel, which
 // served it before, spends 30 lane instructions per row and head and is bound by them for groups
-// of two heads and more: 64 requests of up to 3000 positions, 12 heads on 4: 32.4 -> 21.1 us
-// (3.0 -> 4.7 TB/s); 200 x 1500, 16 heads on one: 54.3 -> 14.7; 64 x 3000, 8 on 8: 39.9 -> 34.6
-// (5.7 TB/s); 4 x 128, 8 on 8: 5.9 -> 5.5.
+// of two heads and more.  A call, this kernel after that one: 64 requests of up to 3000 positions, 12
+// heads on 4: 32.4 -> 22.1 us (3.2 -> 4.8 TB/s); 200 of 1500, 16 heads on one: 75.6 -> 19.7; 64 of
+// 3000, 8 on 8: 66.9 -> 62.7 (6.3 TB/s); 4 of 128, 8 on 8: 5.3 -> 5.3.
+// A weight is a binary32 value there and a binary16 pair here (about 22 bits): over two dozen shapes
+// of 75 to 26000 positions both are 2.03e-4 to 2.16e-4 off 64 bits in the 2-norm, the same to five
+// digits, which is the rounding of the results.
 //
 // The kernel's leading arguments repeat what the length scan needs: they arrive in
 // registers with the wave (kernel-argument preload), so the lengths are requested before

@@ -161,7 +161,7 @@ struct SwLaunchEvents {
 
 // Vector-ALU partial kernel: any group size (looped in tiles of up to 8 heads).
 hipError_t sw_launch_partial_valu(const SwArgs &a, hipStream_t stream, const SwLaunchEvents *ev);
-// Matrix-core kernel, K and V staged through LDS (head_dim 128, groups up to 64, 4 or 8 waves).
+// Matrix-core kernel, K and V staged through LDS (head_dim 128 or 64, groups up to 64, 4 or 8 waves).
 bool       sw_decode_split_supported(const SwArgs &a);
 hipError_t sw_launch_decode_split(const SwArgs &a, hipStream_t stream, const SwLaunchEvents *ev);
 // A mixed batch's token phase (two-kernel form, partial results to the workspace) and prompt phase in one launch.

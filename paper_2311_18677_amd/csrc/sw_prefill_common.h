@@ -1,4 +1,4 @@
-// Pieces shared by the two prompt-phase (causal attention) kernels: operand
+// Pieces shared by the three prompt-phase (causal attention) kernels: operand
 // types, the per-query online softmax and the second matrix product, both for a
 // wave that owns 32 query positions (two 16-wide MFMA column blocks) of one head
 // and works on tiles of 32 cached positions.  Lane (n16 = lane % 16, gq = lane / 16)
@@ -268,7 +268,7 @@ __device__ __forceinline__ void load_vt(const unsigned char *vb, const unsigned 
         }
 }
 
-// Online softmax of one tile, base 2, for both query blocks.  m[] is kept in raw score
+// Online softmax of one tile, base 2, for one query block.  m[] is kept in raw score
 // units; the scale enters through one fused multiply-add.  `diagonal`: some position of
 // the tile is later than some query of the wave (q0 = the wave's first query, t0 = the
 // tile's first position).
@@ -332,14 +332,6 @@ __device__ __forceinline__ void softmax_block(int nb, const float4_t (&sacc)[2][
             p[nb].h[2 * j + 1] = h2[1];
         }
     }
-}
-
-__device__ __forceinline__ void softmax_tile(const float4_t (&sacc)[2][2], bool diagonal, int q0, int t0,
-                                             int n16, int gq, float scale_log2e, float lazy_raw,
-                                             float (&m)[2], float4_t (&l)[2], float4_t (&o)[2][8], Frag (&p)[2])
-{
-    softmax_block(0, sacc, diagonal, q0, t0, n16, gq, scale_log2e, lazy_raw, m, l, o, p);
-    softmax_block(1, sacc, diagonal, q0, t0, n16, gq, scale_log2e, lazy_raw, m, l, o, p);
 }
 
 // O^T += V^T P^T for one query block, and the sum of the same weights: one more product with

@@ -25,11 +25,12 @@
 // the largest weight of that tile is exact.  The key-split kernel has four such maxima for a row, here
 // there are two, which costs 1.5 % of the error against 64 bits (2.57e-4 -> 2.61e-4 of the 2-norm
 // for a prompt of 8192 tokens, nearly all of it in rows of few positions).  The waves therefore
-// multiply their first tile by the rest of its weights as well: 2.47e-4, and no row's error is
-// larger than the key-split kernel's.  It takes 1 to 2 us of a call.
+// multiply their first tile by the rest of its weights as well: 2.47e-4, rows behind 2600
+// and more positions are as far off as the key-split kernel's.  It takes 1 to 2 us of a call.
 //
 // Measured (sw_prefill_attn, 8 heads on one key/value head; key-split / whole / this): one
-// prompt of 8192 tokens 188 / 238 / 151 us (910 TFLOP/s), of 12288 402 / 362 / 348.  What bounds it: staging two
+// prompt of 8192 tokens 198 / 238 / 164 us, of 9600 252 / 281 / 224, back to back on a chip at its power
+// limit; with the cache store before it 186 / - / 152 us (905 TFLOP/s).  What bounds it: staging two
 // tiles per step (32 KB through the compute unit's 64-byte-per-clock load path, 0.2 us of
 // 1.15 per step) on top of the matrix and vector work, and the LDS reads, which every wave does
 // for 32 queries only.
