@@ -268,90 +268,6 @@ __device__ __forceinline__ void load_vt(const unsigned char *vb, const unsigned 
         }
 }
 
-// Online softmax of one tile, base 2, for one query block.  m[] is kept in raw score
-// units; the scale enters through one fused multiply-add.  `diagonal`: some position of
-// the tile is later than some query of the wave (q0 = the wave's first query, t0 = the
-// tile's first position).
-__device__ __forceinline__ void softmax_block(int nb, const float4_t (&sacc)[2][2], bool diagonal, int q0, int t0,
-                                              int n16, int gq, float scale_log2e, float lazy_raw,
-                                              float (&m)[2], float4_t (&l)[2], float4_t (&o)[2][8], Frag (&p)[2])
-{
-    {
-        float s[8];
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[4 * tb + i] = sacc[nb][tb][i];
-        if (diagonal) {
-            const int qpos = q0 + 16 * nb + n16;
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (t0 + 16 * tb + 4 * gq + i > qpos) s[4 * tb + i] = -INFINITY;
-        }
-        // Optimistic pass: weights against the running maximum as it stands.  While every
-        // lane's eight weights sum to at most 8 * 2^kLazyBits nothing has to change -- no
-        // weight exceeds that bound (fine for binary16, whose precision is relative) and the
-        // tile's own maximum is never needed.  A larger (or infinite, or NaN) sum in any
-        // lane sends the whole wave through the exact pass below; sums above the bound
-        // imply a score more than 2^kLazyBits above the maximum, so that pass raises it.
-        float neg_m = -m[nb] * scale_log2e;
-        float pj[8];
-        float psum = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            pj[j] = __builtin_amdgcn_exp2f(fmaf(s[j], scale_log2e, neg_m));
-            psum += pj[j];
-        }
-        if (__builtin_amdgcn_ballot_w64(!(psum <= kSumBound)) != 0) {       // rare after the first tiles
-            float mt = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])),
-                             fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
-            mt = quad_rows_max(mt);
-            const bool raise = mt > m[nb] + lazy_raw;
-            const float m_new = raise ? mt : m[nb];
-            const float alpha = __builtin_amdgcn_exp2f((m[nb] - m_new) * scale_log2e);
-            m[nb] = m_new;
-            l[nb] *= alpha;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[nb][e] *= alpha;
-            neg_m = -m[nb] * scale_log2e;
-            psum = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                pj[j] = __builtin_amdgcn_exp2f(fmaf(s[j], scale_log2e, neg_m));
-                psum += pj[j];
-            }
-        }
-        // (psum only decides whether the maximum must be raised; the sum that normalises the
-        // row is taken from the rounded weights, by the matrix cores, in pv_block)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const half2_t h2 = __builtin_convertvector((float2_t){pj[2 * j], pj[2 * j + 1]}, half2_t);
-            p[nb].h[2 * j] = h2[0];
-            p[nb].h[2 * j + 1] = h2[1];
-        }
-    }
-}
-
-// O^T += V^T P^T for one query block, and the sum of the same weights: one more product with
-// an all-ones operand leaves, in every element of l[nb], the tile's sum over ALL 32 keys of
-// the binary16 weights of query n16.  Numerator and denominator of a row are thus built from
-// the same rounded weights, w~_i = w_i (1 + d_i): the row's error is sum_i w_i d_i (v_i - out),
-// which vanishes where one key dominates (its v is the row) -- with the exact sum as
-// denominator it would be sum_i w_i d_i v_i, up to 2^-11 |v| for such a row, which alone
-// exceeds the error bound once |v| reaches 4.
-__device__ __forceinline__ void pv_block(int nb, const Frag (&va)[8], const Frag (&p)[2], float4_t (&o)[2][8],
-                                         float4_t (&l)[2])
-{
-    Frag ones;
-    ones.u = uint4_t{0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};      // eight binary16 ones
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[nb].h, o[nb][e], 0, 0, 0);
-    l[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones.h, p[nb].h, l[nb], 0, 0, 0);
-}
-
 // ---- pieces of the kernels that run a tile's softmax beside the next tile's first product
 
 __device__ __forceinline__ void copy_scores(const float4_t (&from)[2][2], float4_t (&to)[2][2])
@@ -374,13 +290,36 @@ __device__ __forceinline__ void mask_tile(float4_t (&s)[2][2], int q0, int t0, i
                 if (t0 + 16 * tb + 4 * gq + i > q0 + 16 * nb + n16) s[nb][tb][i] = -INFINITY;
 }
 
+// Sum of two binary16 values onto a binary32 one, each exactly as it is (v_fma_mix_f32 with one
+// for the other factor; opaque, or the compiler takes the product away and converts by itself).
+// Neither the two-element dot product, which does it in one instruction -- dot products wait until
+// the SIMD's matrix pipe is empty: 64 of them made no headway beside another wave's matrix
+// instructions, where 64 mixed multiply-adds took 430 cycles for 312 alone -- nor one more matrix
+// product with ones in V's place, which the shared-tile kernel took before: two of its 34 matrix
+// instructions a tile, on a chip whose clock gives way under them (one prompt of 32768 tokens, 8 heads
+// on one, with its cache store: 2043 -> 1945 us; of 16384 532 -> 503; 16 of 100 to 1900 96 -> 90.5).
+__device__ __forceinline__ float add_halves(half2_t w, float one, float sum)
+{
+    sum = __builtin_fmaf((float)w[0], one, sum);
+    return __builtin_fmaf((float)w[1], one, sum);
+}
+
+__device__ __forceinline__ float opaque_one()
+{
+    float one = 1.f;
+    asm("" : "+s"(one));
+    return one;
+}
+
 // A tile's weights of one query block against the maximum behind neg_m (= -m * scale_log2e):
 // rounded to binary16 (the second product's operand), and the lane's sum of the ROUNDED values in
-// binary32, taken with the two-element dot product against ones: numerator and denominator of a
-// row are built from the same weights (why that matters: see pv_block).
+// binary32: numerator and denominator of a row are built from the same rounded weights, w~_i =
+// w_i (1 + d_i).  The row's error is then sum_i w_i d_i (v_i - out), which vanishes where one key
+// dominates (its v is the row) -- with the exact sum as denominator it would be sum_i w_i d_i v_i, up
+// to 2^-11 |v| for such a row, which alone exceeds the error bound once |v| reaches 4.
 __device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scale_log2e, float neg_m, Frag &p, float &psum)
 {
-    const half2_t ones = {(_Float16)1.f, (_Float16)1.f};
+    const float one = opaque_one();
     psum = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -389,7 +328,7 @@ __device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scal
         const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
         p.h[2 * j] = w[0];
         p.h[2 * j + 1] = w[1];
-        psum = __builtin_amdgcn_fdot2(w, ones, psum, false);
+        psum = add_halves(w, one, psum);
     }
 }
 
@@ -398,7 +337,7 @@ __device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scal
 __device__ __forceinline__ void rest_block(const float4_t (&s)[2], float scale_log2e, float neg_m, const Frag &p, Frag &rest,
                                            float &rsum)
 {
-    const half2_t ones = {(_Float16)1.f, (_Float16)1.f};
+    const float one = opaque_one();
     rsum = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -407,7 +346,7 @@ __device__ __forceinline__ void rest_block(const float4_t (&s)[2], float scale_l
         const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
         rest.h[2 * j] = w[0];
         rest.h[2 * j + 1] = w[1];
-        rsum = __builtin_amdgcn_fdot2(w, ones, rsum, false);
+        rsum = add_halves(w, one, rsum);
     }
 }
 
@@ -427,6 +366,51 @@ __device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] *= alpha;
     weights_block(s, scale_log2e, -m * scale_log2e, p, psum);
+}
+
+// Online softmax of one tile, base 2, for one query block.  m[] is kept in raw score
+// units; the scale enters through one fused multiply-add.  `diagonal`: some position of
+// the tile is later than some query of the wave (q0 = the wave's first query, t0 = the
+// tile's first position).
+__device__ __forceinline__ void softmax_block(int nb, const float4_t (&sacc)[2][2], bool diagonal, int q0, int t0,
+                                              int n16, int gq, float scale_log2e, float lazy_raw,
+                                              float (&m)[2], float (&l)[2], float4_t (&o)[2][8], Frag (&p)[2])
+{
+    {
+        float s[8];
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[4 * tb + i] = sacc[nb][tb][i];
+        if (diagonal) {
+            const int qpos = q0 + 16 * nb + n16;
+#pragma unroll
+            for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (t0 + 16 * tb + 4 * gq + i > qpos) s[4 * tb + i] = -INFINITY;
+        }
+        // Optimistic pass: weights against the running maximum as it stands.  While every
+        // lane's eight weights sum to at most 8 * 2^kLazyBits nothing has to change -- no
+        // weight exceeds that bound (fine for binary16, whose precision is relative) and the
+        // tile's own maximum is never needed.  A larger (or infinite, or NaN) sum in any
+        // lane sends the whole wave through the exact pass below; sums above the bound
+        // imply a score more than 2^kLazyBits above the maximum, so that pass raises it.
+        float4_t sv[2] = {float4_t{s[0], s[1], s[2], s[3]}, float4_t{s[4], s[5], s[6], s[7]}};
+        float psum;
+        weights_block(sv, scale_log2e, -m[nb] * scale_log2e, p[nb], psum);
+        if (__builtin_amdgcn_ballot_w64(!(psum <= kSumBound)) != 0)       // rare after the first tiles
+            raise_block(sv, scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum);
+        l[nb] += psum;
+    }
+}
+
+// O^T += V^T P^T for one query block.
+__device__ __forceinline__ void pv_block(int nb, const Frag (&va)[8], const Frag (&p)[2], float4_t (&o)[2][8])
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[nb].h, o[nb][e], 0, 0, 0);
 }
 
 // 64 lanes x 16 bytes, global -> LDS, asynchronously: lane l's bytes (at base + off, base
