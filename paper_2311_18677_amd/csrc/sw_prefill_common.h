@@ -292,14 +292,18 @@ __device__ __forceinline__ void mask_tile(float4_t (&s)[2][2], int q0, int t0, i
 
 // Sum of two binary16 values onto a binary32 one, each exactly as it is (v_fma_mix_f32 with one
 // for the other factor; opaque, or the compiler takes the product away and converts by itself).
-// Neither the two-element dot product, which does it in one instruction -- dot products wait until
+// Not one more matrix product with ones in V's place, which the shared-tile kernel took before: two of
+// its 34 matrix instructions a tile, on a chip whose clock gives way under them (one prompt of 32768
+// tokens, 8 heads on one, with its cache store: 2043 -> 1945 us; of 16384 532 -> 503; 16 of 100 to 1900
+// 96 -> 90.5).
+// DOT: the two-element dot product, which does it in one instruction and rounds alike, but waits until
 // the SIMD's matrix pipe is empty: 64 of them made no headway beside another wave's matrix
-// instructions, where 64 mixed multiply-adds took 430 cycles for 312 alone -- nor one more matrix
-// product with ones in V's place, which the shared-tile kernel took before: two of its 34 matrix
-// instructions a tile, on a chip whose clock gives way under them (one prompt of 32768 tokens, 8 heads
-// on one, with its cache store: 2043 -> 1945 us; of 16384 532 -> 503; 16 of 100 to 1900 96 -> 90.5).
+// instructions, where 64 mixed multiply-adds took 430 cycles for 312 alone.  For the key-split
+// kernel, whose long chains have a SIMD to themselves (2 heads on one, 4096 tokens: 31.0 us against 31.3).
+template <bool DOT>
 __device__ __forceinline__ float add_halves(half2_t w, float one, float sum)
 {
+    if constexpr (DOT) return __builtin_amdgcn_fdot2(w, half2_t{(_Float16)1.f, (_Float16)1.f}, sum, false);
     sum = __builtin_fmaf((float)w[0], one, sum);
     return __builtin_fmaf((float)w[1], one, sum);
 }
@@ -317,6 +321,7 @@ __device__ __forceinline__ float opaque_one()
 // w_i (1 + d_i).  The row's error is then sum_i w_i d_i (v_i - out), which vanishes where one key
 // dominates (its v is the row) -- with the exact sum as denominator it would be sum_i w_i d_i v_i, up
 // to 2^-11 |v| for such a row, which alone exceeds the error bound once |v| reaches 4.
+template <bool DOT = false>
 __device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scale_log2e, float neg_m, Frag &p, float &psum)
 {
     const float one = opaque_one();
@@ -328,7 +333,7 @@ __device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scal
         const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
         p.h[2 * j] = w[0];
         p.h[2 * j + 1] = w[1];
-        psum = add_halves(w, one, psum);
+        psum = add_halves<DOT>(w, one, psum);
     }
 }
 
@@ -346,13 +351,14 @@ __device__ __forceinline__ void rest_block(const float4_t (&s)[2], float scale_l
         const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
         rest.h[2 * j] = w[0];
         rest.h[2 * j + 1] = w[1];
-        rsum = add_halves(w, one, rsum);
+        rsum = add_halves<false>(w, one, rsum);
     }
 }
 
 // The exact pass of one query block: raises the running maximum where a score of the tile lies
 // more than kLazyBits above it, rescales what has been accumulated and computes the tile's
 // weights again.  (weights_block takes the maximum as it stands.)
+template <bool DOT = false>
 __device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_log2e, float lazy_raw,
                                             float &m, float &l, float4_t (&o)[8], Frag &p, float &psum)
 {
@@ -365,7 +371,7 @@ __device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_
     l *= alpha;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] *= alpha;
-    weights_block(s, scale_log2e, -m * scale_log2e, p, psum);
+    weights_block<DOT>(s, scale_log2e, -m * scale_log2e, p, psum);
 }
 
 // Online softmax of one tile, base 2, for one query block.  m[] is kept in raw score

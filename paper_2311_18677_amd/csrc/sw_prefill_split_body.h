@@ -254,7 +254,7 @@ __device__ __forceinline__ void prompt_workgroup(const SwPrefillArgs &a, unsigne
         Frag p[2];
         float psum[2];
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) weights_block(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
+        for (int nb = 0; nb < 2; ++nb) weights_block<true>(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
         if (MORE) {
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
@@ -265,7 +265,7 @@ __device__ __forceinline__ void prompt_workgroup(const SwPrefillArgs &a, unsigne
         if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
-                raise_block(s[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum[nb]);
+                raise_block<true>(s[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum[nb]);
         }
         l[0] += psum[0];
         l[1] += psum[1];
