@@ -11,13 +11,13 @@
 // tile still serves four waves.  The two groups' (maximum, sum, accumulator) triples are merged
 // through LDS at the end.
 //
-// Pipeline.  A step computes the FIRST product of tile i+1 beside the softmax of tile i:
-//
-//   wait, barrier | request K(i+4), V(i+3) | K(i+1) -> registers, part of the softmax |
-//   S(i+1) = K Q^T  with  P(i) = softmax(S(i)), V(i) -> registers | O += V(i) P(i)
-//
-// so the matrix cores have work while a wave's vector unit does the exponentials.  The tiles
-// are requested by inline assembly: with the builtin the compiler's wait-count pass holds the
+// A step of a wave is one tile: first product, softmax, second product, one after the other; the two
+// waves of a SIMD fill each other's gaps.  (With the first product of the next tile beside the softmax
+// of this one a step took 1.06 us instead of 0.95: that form has all eight waves wait for the same
+// LDS reads behind the barrier, before their first matrix instruction.)  K operands are read two
+// 32-dim steps, V operands three 16-dim blocks ahead of their products, and no further: all sixteen
+// of either held at once cost 30 registers and 4 us of a call.
+// The tiles are requested by inline assembly: with the builtin the compiler's wait-count pass holds the
 // transposing LDS reads until ALL outstanding requests have landed.  The waits below count
 // exactly instead; no other vector-memory operation is issued inside the loop.
 //
@@ -28,12 +28,10 @@
 // multiply their first tile by the rest of its weights as well: 2.47e-4, rows behind 2600
 // and more positions are as far off as the key-split kernel's.  It takes 1 to 2 us of a call.
 //
-// Measured (sw_prefill_attn, 8 heads on one key/value head; key-split / whole / this): one
-// prompt of 8192 tokens 198 / 238 / 164 us, of 9600 252 / 281 / 224, back to back on a chip at its power
-// limit; with the cache store before it 186 / - / 152 us (905 TFLOP/s).  What bounds it: staging two
-// tiles per step (32 KB through the compute unit's 64-byte-per-clock load path, 0.2 us of
-// 1.15 per step) on top of the matrix and vector work, and the LDS reads, which every wave does
-// for 32 queries only.
+// Measured (8 heads on one key/value head, with the cache store before it): one prompt of 8192
+// tokens 147 us where the next tile's product ran beside the softmax 156, key-split 186.  What bounds
+// it: a SIMD's matrix and vector instructions, which share its issue slots (1290 cycles a step
+// for two waves, of about 2100), and staging two tiles per step (16 us of a call).
 #include "sw_prefill_common.h"
 
 #include <type_traits>
@@ -42,7 +40,7 @@ namespace {
 
 using namespace sw_prefill;
 
-constexpr int kBufs = 4;          // steps' worth of K and of V tiles in the staging rings
+constexpr int kBufs = 3;          // steps' worth of K and of V tiles in the staging rings
 
 // The block table is read-only for the whole launch; reading it through the constant
 // address space lets wave-uniform entries come in over the scalar path.
@@ -141,7 +139,6 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
     using KTile = std::false_type;
     using VTile = std::true_type;
 
@@ -158,8 +155,11 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
 
     // ---- first tiles and Q^T operands, awaited together
     request(0, I0{}, KTile{});
-    if (n_steps > 1) request(1, I1{}, KTile{});
     request(0, I0{}, VTile{});
+    if (n_steps > 1) {
+        request(1, I1{}, KTile{});
+        request(1, I1{}, VTile{});
+    }
     Frag qreg[2][4];
     load_q(a, q_first, qw0, NQ, h, n16, gq, qreg);
 #pragma unroll
@@ -167,56 +167,74 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qreg[nb][kk].u));
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if (n_steps > 2) request(2, I2{}, KTile{});
-    if (n_steps > 1) request(1, I1{}, VTile{});
-    if (n_steps > 3) request(3, I3{}, KTile{});
-    if (n_steps > 2) request(2, I2{}, VTile{});
 
     const unsigned char *kmine = lds + kg * kTileBytes;
     const unsigned char *vmine = lds + kVBase + kg * kTileBytes;
     const int t_mine = kg * kTile;
 
-    float4_t s0[2][2], s1[2][2];
-    {
-        Frag kop[2][4];
-        load_k_ops(kmine, n16, gq, kop);
-        qk_block(0, kop, qreg, s0);
-        qk_block(1, kop, qreg, s0);
-        if (t_mine + kTile > aw0) mask_tile(s0, aw0, t_mine, n16, gq);
-    }
-
-    // One step: softmax and second product of step i's tile (scores s), first product of step
-    // i+1's tile (into s_next) where the wave has one.  buf = i % kBufs; START: i may be 0.
-    auto compute = [&](int i, auto buf, auto more_c, auto start_c, float4_t (&s)[2][2], float4_t (&s_next)[2][2]) __attribute__((always_inline)) {
-        const int B = buf;
-        constexpr bool MORE = decltype(more_c)::value;
-        constexpr bool START = decltype(start_c)::value;
-        Frag kop[2][4];
-        if (MORE) load_k_ops(kmine + ((B + 1) % kBufs) * kStepBytes, n16, gq, kop);
-        Frag va[8];
-        load_vt(vmine + B * kStepBytes, vt_off, va);
-        if (MORE) {
-            qk_block(0, kop, qreg, s_next);
-            qk_block(1, kop, qreg, s_next);
+    // Operand of the second product: dims 16e .. 16e+15 of the tile's V rows (see load_vt).
+    auto v_operand = [&](const unsigned char *vb, int e) __attribute__((always_inline)) {
+        Frag v;
+#pragma unroll
+        for (int hk = 0; hk < 2; ++hk) {
+            union { short4_t s; unsigned int u[2]; } x;
+            x.s = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(vb + vt_off[e] + hk * 16 * kRowBytes));
+            v.u[2 * hk] = x.u[0];
+            v.u[2 * hk + 1] = x.u[1];
         }
-        // Optimistic pass: weights against the running maximum as it stands; the exact pass where
+        return v;
+    };
+
+    // Step i, staged in ring slot B (= i % kBufs, as a compile-time constant).
+    auto step = [&](int i, auto buf_c) __attribute__((always_inline)) {
+        constexpr int B = decltype(buf_c)::value;
+        // this wave's share of step i has landed (that of step i + 1 may be in flight) ...
+        if (i + 1 < n_steps) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * C) & 0xc07f);
+        else                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
+        // ... and so has everyone's; every wave has also finished reading step i - 1,
+        // whose slot step i + 2 may now overwrite
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (i + 2 < n_steps) {
+            request(i + 2, std::integral_constant<int, (B + 2) % kBufs>{}, KTile{});
+            request(i + 2, std::integral_constant<int, (B + 2) % kBufs>{}, VTile{});
+        }
+        if (i >= my_steps) return;
+        const unsigned char *kb = kmine + B * kStepBytes;
+        const unsigned char *vb = vmine + B * kStepBytes;
+
+        // ---- S^T = K Q^T
+        float4_t s[2][2];
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) s[nb][0] = s[nb][1] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const int off = n16 * kRowBytes + (((4 * kk + gq) ^ n16) << 4);   // row n16, piece 4kk+gq
+            Frag k0, k1;
+            k0.u = *reinterpret_cast<const uint4_t *>(kb + off);
+            k1.u = *reinterpret_cast<const uint4_t *>(kb + 16 * kRowBytes + off);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                s[nb][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k0.h, qreg[nb][kk].h, s[nb][0], 0, 0, 0);
+                s[nb][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k1.h, qreg[nb][kk].h, s[nb][1], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);          // LDS reads of two 32-dim steps ...
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);      // ... products of one ...
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);      // ... reads of the one after next
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+        const int t0 = i * (KS * kTile) + t_mine;
+        if (t0 + kTile > aw0) mask_tile(s, aw0, t0, n16, gq);
+
+        // ---- Optimistic pass: weights against the running maximum as it stands; the exact pass where
         // some lane's weights sum to more than kSumBound (rare after the first tiles).
         Frag p[2];
         float psum[2];
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb) weights_block(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
-        if (MORE) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);          // the K operands
-            __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);         // vector work under their latency
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one matrix instruction ...
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // ... one LDS read of V
-                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);      // ... three vector instructions
-            }
-        }
         if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
@@ -224,21 +242,33 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
         }
         l[0] += psum[0];
         l[1] += psum[1];
+
+        // ---- O^T += V^T P^T
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            o[0][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[0].h, o[0][e], 0, 0, 0);
-            o[1][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[1].h, o[1][e], 0, 0, 0);
+            const Frag v = v_operand(vb, e);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v.h, p[nb].h, o[nb][e], 0, 0, 0);
         }
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);          // LDS reads of three 16-dim blocks ahead
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
         // The wave's first tile: what the rounding left of its weights as well (an infinity in V
         // stays out of that product, where its sign would be the rest's).
-        if (START && i == 0) {
+        if (B == 0 && i == 0) {
             const half2_t none = {(_Float16)0.f, (_Float16)0.f};
             half2_t spoiled = none;
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 8; ++e) {
+                const Frag v = v_operand(vb, e);
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    spoiled = __builtin_elementwise_fma((half2_t){va[e].h[2 * j], va[e].h[2 * j + 1]}, none, spoiled);
+                    spoiled = __builtin_elementwise_fma((half2_t){v.h[2 * j], v.h[2 * j + 1]}, none, spoiled);
+            }
             if (__builtin_amdgcn_ballot_w64(!(spoiled[0] + spoiled[1] == (_Float16)0.f)) == 0) {
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb) {
@@ -248,53 +278,16 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
                     l[nb] += rsum;
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, rest.h, o[nb][e], 0, 0, 0);
+                        o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v_operand(vb, e).h, rest.h, o[nb][e], 0, 0, 0);
                 }
             }
         }
-        if (MORE) {
-            const int t_next = (i + 1) * (KS * kTile) + t_mine;
-            if (t_next + kTile > aw0) mask_tile(s_next, aw0, t_next, n16, gq);
-        }
     };
-
-    // Waits for step i's tiles, lets everyone arrive, requests further ones.  buf = i % kBufs.
-    auto arrive = [&](int i, auto buf_c) __attribute__((always_inline)) {
-        constexpr int B = decltype(buf_c)::value;
-        // this wave's share of V(i) and K(i+1) has landed; what may still be in flight, in issue
-        // order: K(i+2), V(i+1), K(i+3), V(i+2) as far as they exist ...
-        const int left = n_steps - i;
-        if (left > 3)       __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * C) & 0xc07f);
-        else if (left == 3) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * C) & 0xc07f);
-        else if (left == 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(1 * C) & 0xc07f);
-        else                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
-        // ... and so has everyone's; every wave has also read K(i) and V(i-1), whose slots
-        // K(i+kBufs) and V(i+kBufs-1) may now overwrite
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (i + kBufs < n_steps) request(i + kBufs, std::integral_constant<int, B>{}, KTile{});
-        if (i + kBufs - 1 < n_steps) request(i + kBufs - 1, std::integral_constant<int, (B + kBufs - 1) % kBufs>{}, VTile{});
-    };
-    static_assert(kBufs == 4, "the loops below are unrolled by the number of buffers");
-    int i = 0;
-    for (;;) {
-        if (i + 1 >= my_steps) break;
-        arrive(i, I0{}); compute(i, I0{}, std::true_type{}, std::true_type{}, s0, s1); ++i;
-        if (i + 1 >= my_steps) { copy_scores(s1, s0); break; }
-        arrive(i, I1{}); compute(i, I1{}, std::true_type{}, std::false_type{}, s1, s0); ++i;
-        if (i + 1 >= my_steps) break;
-        arrive(i, I2{}); compute(i, I2{}, std::true_type{}, std::false_type{}, s0, s1); ++i;
-        if (i + 1 >= my_steps) { copy_scores(s1, s0); break; }
-        arrive(i, I3{}); compute(i, I3{}, std::true_type{}, std::false_type{}, s1, s0); ++i;
-    }
-    // the wave's last step, then the steps that are only other waves'
-    for (; i < n_steps; ++i) {
-        const int B = i & (kBufs - 1);
-        if (B == 0)      arrive(i, I0{});
-        else if (B == 1) arrive(i, I1{});
-        else if (B == 2) arrive(i, I2{});
-        else             arrive(i, I3{});
-        if (i < my_steps) compute(i, B, std::false_type{}, std::true_type{}, s0, s1);
+    static_assert(kBufs == 3, "the loop below is unrolled by the number of buffers");
+    for (int i = 0; i < n_steps; i += kBufs) {
+        step(i, I0{});
+        if (i + 1 < n_steps) step(i + 1, I1{});
+        if (i + 2 < n_steps) step(i + 2, I2{});
     }
     l[0] = quad_rows_sum(l[0]);
     l[1] = quad_rows_sum(l[1]);
