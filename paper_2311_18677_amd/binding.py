@@ -1,4 +1,5 @@
-"""Thin ctypes binding of include/sw_decode.h (argument marshalling only).
+"""Thin binding of include/sw_decode.h (argument marshalling only; the entry points that enqueue
+work natively, in csrc/sw_python.cpp, the others by ctypes).
 
 Every step of the decode-attention path runs in the HIP kernels of
 libsw_decode.so.  There is no fallback: if the library has not been built the
@@ -76,6 +77,10 @@ def load():
     # runtime instance: torch is imported first, and the library's dependency on
     # libamdhip64.so.7 then binds to the copy torch has already loaded.
     import torch  # noqa: F401
+    try:
+        from . import sw_native
+    except ImportError as e:
+        raise RuntimeError("sw_native.so is not built (%s); run `python -m paper_2311_18677_amd.build`" % e)
     lib = ctypes.CDLL(LIB_PATH)
     vp, ci = ctypes.c_void_p, ctypes.c_int
     lib.sw_kv_layout.restype = ci
@@ -136,6 +141,8 @@ def load():
     lib.sw_prof_stop.restype = ci
     lib.sw_prof_stop.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double),
                                  ctypes.POINTER(ci)]
+    # the entry points of a serving loop, called without ctypes (csrc/sw_python.cpp)
+    lib.native = sw_native.Library({name: ctypes.cast(getattr(lib, name), vp).value for name in sw_native.NAMES})
     _lib = lib
     return lib
 
@@ -183,17 +190,17 @@ def sw_kv_layout(n_req, n_kvh, head_dim, max_len, check=True):
 def sw_decode_attn(q, k_cache, v_cache, seq_lens, out, n_req, n_qh, n_kvh, head_dim, max_len,
                    stream=None, check=True):
     """One decode step's attention; enqueues on `stream` and returns without waiting."""
-    rc = load().sw_decode_attn(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), _ptr(out),
-                               n_req, n_qh, n_kvh, head_dim, max_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_decode_attn(q, k_cache, v_cache, seq_lens, out, n_req, n_qh, n_kvh, head_dim, max_len,
+                                      stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_decode_attn_static(q, k_cache, v_cache, seq_lens, out, n_req, n_qh, n_kvh, head_dim, max_len,
                           stream=None, check=True):
     """sw_decode_attn over the library's static scratch array: allocates nothing."""
-    rc = load().sw_decode_attn_static(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), _ptr(out),
-                                      n_req, n_qh, n_kvh, head_dim, max_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_decode_attn_static(q, k_cache, v_cache, seq_lens, out, n_req, n_qh, n_kvh, head_dim,
+                                             max_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_kv_paged_layout(n_blocks, n_kvh, head_dim, block_size, check=True):
@@ -209,81 +216,73 @@ def sw_kv_paged_layout(n_blocks, n_kvh, head_dim, block_size, check=True):
 def sw_decode_attn_paged(q, k_pool, v_pool, block_table, seq_lens, out, n_req, n_qh, n_kvh,
                          head_dim, block_size, max_blocks, n_blocks, stream=None, check=True):
     """One decode step's attention over block pools; enqueues on `stream`."""
-    rc = load().sw_decode_attn_paged(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_table),
-                                     _ptr(seq_lens), _ptr(out), n_req, n_qh, n_kvh, head_dim,
-                                     block_size, max_blocks, n_blocks, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_decode_attn_paged(q, k_pool, v_pool, block_table, seq_lens, out, n_req, n_qh, n_kvh,
+                                            head_dim, block_size, max_blocks, n_blocks, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_decode_attn_append(q, k_new, v_new, k_cache, v_cache, seq_lens, out, n_req, n_qh, n_kvh,
                           head_dim, max_len, stream=None, check=True):
     """Store the newest token's K/V rows in the cache and attend over it, in one pass."""
-    rc = load().sw_decode_attn_append(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache),
-                                      _ptr(v_cache), _ptr(seq_lens), _ptr(out),
-                                      n_req, n_qh, n_kvh, head_dim, max_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_decode_attn_append(q, k_new, v_new, k_cache, v_cache, seq_lens, out, n_req, n_qh,
+                                             n_kvh, head_dim, max_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_decode_attn_paged_append(q, k_new, v_new, k_pool, v_pool, block_table, seq_lens, out,
                                 n_req, n_qh, n_kvh, head_dim, block_size, max_blocks, n_blocks,
                                 stream=None, check=True):
     """sw_decode_attn_append over block pools."""
-    rc = load().sw_decode_attn_paged_append(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_pool),
-                                            _ptr(v_pool), _ptr(block_table), _ptr(seq_lens),
-                                            _ptr(out), n_req, n_qh, n_kvh, head_dim,
-                                            block_size, max_blocks, n_blocks, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_decode_attn_paged_append(q, k_new, v_new, k_pool, v_pool, block_table, seq_lens, out,
+                                                   n_req, n_qh, n_kvh, head_dim, block_size, max_blocks,
+                                                   n_blocks, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_advance_lens(seq_lens, n_req, max_len, stream=None, check=True):
     """End of a model step: every length grows by one, saturating at max_len (on the device)."""
-    rc = load().sw_advance_lens(_ptr(seq_lens), n_req, max_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_advance_lens(seq_lens, n_req, max_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_prefill_attn(q, k_cache, v_cache, seq_lens, q_starts, out, n_tokens, n_req, n_qh, n_kvh,
                     head_dim, max_len, stream=None, check=True):
     """Prompt-phase (causal) attention of every prompt token over its request's cache."""
-    rc = load().sw_prefill_attn(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens),
-                                _ptr(q_starts), _ptr(out), int(n_tokens), n_req, n_qh, n_kvh,
-                                head_dim, max_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_prefill_attn(q, k_cache, v_cache, seq_lens, q_starts, out, n_tokens, n_req, n_qh,
+                                       n_kvh, head_dim, max_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_mixed_attn(q, k_cache, v_cache, seq_lens, q_starts, q_lens, out, n_tokens, n_req, n_qh, n_kvh,
                   head_dim, max_len, max_q_len, stream=None, check=True):
     """Mixed-batch causal attention: the last q_lens[r] cached tokens of request r are its queries."""
-    rc = load().sw_mixed_attn(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), _ptr(q_starts),
-                              _ptr(q_lens), _ptr(out), int(n_tokens), n_req, n_qh, n_kvh, head_dim,
-                              max_len, max_q_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_mixed_attn(q, k_cache, v_cache, seq_lens, q_starts, q_lens, out, n_tokens, n_req,
+                                     n_qh, n_kvh, head_dim, max_len, max_q_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_kv_pack(k_pool, v_pool, block_table, seq_lens, k_dense, v_dense, n_req, n_kvh, head_dim,
                max_len, block_size, max_blocks, n_blocks, stream=None, check=True):
     """Block pools -> dense caches (every request's valid rows)."""
-    rc = load().sw_kv_pack(_ptr(k_pool), _ptr(v_pool), _ptr(block_table), _ptr(seq_lens),
-                           _ptr(k_dense), _ptr(v_dense), n_req, n_kvh, head_dim, max_len,
-                           block_size, max_blocks, n_blocks, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_kv_pack(k_pool, v_pool, block_table, seq_lens, k_dense, v_dense, n_req, n_kvh,
+                                  head_dim, max_len, block_size, max_blocks, n_blocks, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_kv_unpack(k_dense, v_dense, block_table, seq_lens, k_pool, v_pool, n_req, n_kvh, head_dim,
                  max_len, block_size, max_blocks, n_blocks, stream=None, check=True):
     """Dense caches -> the pool blocks the table names."""
-    rc = load().sw_kv_unpack(_ptr(k_dense), _ptr(v_dense), _ptr(block_table), _ptr(seq_lens),
-                             _ptr(k_pool), _ptr(v_pool), n_req, n_kvh, head_dim, max_len,
-                             block_size, max_blocks, n_blocks, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_kv_unpack(k_dense, v_dense, block_table, seq_lens, k_pool, v_pool, n_req, n_kvh,
+                                    head_dim, max_len, block_size, max_blocks, n_blocks, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_kv_span_plan(block_table, seq_lens, span_first, span_blocks, n_spans, n_req, block_size,
                     max_blocks, n_blocks, stream=None, check=True):
     """Runs of consecutive pool block ids per request (the transfers a layer needs)."""
-    rc = load().sw_kv_span_plan(_ptr(block_table), _ptr(seq_lens), _ptr(span_first),
-                                _ptr(span_blocks), _ptr(n_spans), n_req, block_size, max_blocks,
-                                n_blocks, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_kv_span_plan(block_table, seq_lens, span_first, span_blocks, n_spans, n_req,
+                                       block_size, max_blocks, n_blocks, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_release():
@@ -330,42 +329,38 @@ def sw_prof_stop():
 def sw_prefill_attn_paged(q, k_pool, v_pool, block_table, seq_lens, q_starts, out, n_tokens, n_req, n_qh,
                           n_kvh, head_dim, block_size, max_blocks, n_blocks, stream=None, check=True):
     """Prompt-phase (causal) attention over block pools + block table."""
-    rc = load().sw_prefill_attn_paged(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_table),
-                                      _ptr(seq_lens), _ptr(q_starts), _ptr(out), int(n_tokens), n_req,
-                                      n_qh, n_kvh, head_dim, block_size, max_blocks, n_blocks,
-                                      _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_prefill_attn_paged(q, k_pool, v_pool, block_table, seq_lens, q_starts, out, n_tokens,
+                                             n_req, n_qh, n_kvh, head_dim, block_size, max_blocks, n_blocks,
+                                             stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_mixed_attn_paged(q, k_pool, v_pool, block_table, seq_lens, q_starts, q_lens, out, n_tokens, n_req,
                         n_qh, n_kvh, head_dim, block_size, max_blocks, n_blocks, max_q_len,
                         stream=None, check=True):
     """Mixed-batch attention over block pools + block table."""
-    rc = load().sw_mixed_attn_paged(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_table),
-                                    _ptr(seq_lens), _ptr(q_starts), _ptr(q_lens), _ptr(out),
-                                    int(n_tokens), n_req, n_qh, n_kvh, head_dim, block_size, max_blocks,
-                                    n_blocks, max_q_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_mixed_attn_paged(q, k_pool, v_pool, block_table, seq_lens, q_starts, q_lens, out,
+                                           n_tokens, n_req, n_qh, n_kvh, head_dim, block_size, max_blocks,
+                                           n_blocks, max_q_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_kv_store(k_rows, v_rows, k_cache, v_cache, seq_lens, q_starts, q_lens, n_tokens, n_req, n_kvh,
                 head_dim, max_len, max_q_len, stream=None, check=True):
     """Store the new tokens' K/V rows at their positions in the dense caches (q_lens None: all)."""
-    rc = load().sw_kv_store(_ptr(k_rows), _ptr(v_rows), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens),
-                            _ptr(q_starts), _ptr(q_lens), int(n_tokens), n_req, n_kvh, head_dim, max_len,
-                            max_q_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_kv_store(k_rows, v_rows, k_cache, v_cache, seq_lens, q_starts, q_lens, n_tokens,
+                                   n_req, n_kvh, head_dim, max_len, max_q_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_kv_store_paged(k_rows, v_rows, k_pool, v_pool, block_table, seq_lens, q_starts, q_lens, n_tokens,
                       n_req, n_kvh, head_dim, block_size, max_blocks, n_blocks, max_q_len,
                       stream=None, check=True):
     """The same into block pools + block table."""
-    rc = load().sw_kv_store_paged(_ptr(k_rows), _ptr(v_rows), _ptr(k_pool), _ptr(v_pool),
-                                  _ptr(block_table), _ptr(seq_lens), _ptr(q_starts), _ptr(q_lens),
-                                  int(n_tokens), n_req, n_kvh, head_dim, block_size, max_blocks,
-                                  n_blocks, max_q_len, _stream(stream))
-    return _check(rc) if check else rc
+    rc = load().native.sw_kv_store_paged(k_rows, v_rows, k_pool, v_pool, block_table, seq_lens, q_starts,
+                                         q_lens, n_tokens, n_req, n_kvh, head_dim, block_size, max_blocks,
+                                         n_blocks, max_q_len, stream)
+    return _check(rc) if check and rc else rc
 
 
 def sw_stream_read(src, n_bytes, sink, workgroups=0, stream=None, check=True):

@@ -1,4 +1,4 @@
-"""Build libsw_decode.so (hand-written HIP for gfx950) in-tree with hipcc.
+"""Build libsw_decode.so (hand-written HIP for gfx950) and sw_native.so (its Python caller) in-tree.
 
     python -m paper_2311_18677_amd.build
 
@@ -8,6 +8,7 @@ what is already built.
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsw_decode.so")
+NATIVE = os.path.join(HERE, "sw_native.so")          # the Python side of a call (csrc/sw_python.cpp)
 SOURCES = ["sw_api.hip", "sw_partial_valu.hip", "sw_decode_split.hip", "sw_combine.hip", "sw_lens.hip", "sw_prefill_mfma.hip", "sw_kv_handoff.hip", "sw_prefill_split.hip", "sw_prefill_halves.hip", "sw_calibrate.hip", "sw_kv_store.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -42,8 +44,20 @@ def _compile(src):
     return obj
 
 
+def _build_native():
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "sw_python.cpp"), "-o", tmp]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("%s failed on sw_python.cpp:\n%s" % (cmd[0], res.stderr))
+    os.replace(tmp, NATIVE)
+
+
 def build(verbose=False):
     os.makedirs(OBJ_DIR, exist_ok=True)
+    _build_native()
     with ThreadPoolExecutor(max_workers=4) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp.%d" % os.getpid()

@@ -1,0 +1,100 @@
+"""The native caller of the entry points (csrc/sw_python.cpp): every argument arrives in its place,
+converted as the ctypes prototypes convert it; what is no address or integer is refused."""
+import ctypes
+
+import pytest
+
+from paper_2311_18677_amd import binding as sw
+
+
+def recorder(name):
+    """(native function, list of the calls it made) for one entry point of the library."""
+    from paper_2311_18677_amd import sw_native
+    types = getattr(sw.load(), name).argtypes
+    calls = []
+
+    def record(*args):
+        calls.append(args)
+        return -7
+    fn = ctypes.CFUNCTYPE(ctypes.c_int, *types)(record)
+    at = ctypes.cast(fn, ctypes.c_void_p).value
+    lib = sw_native.Library({n: at for n in sw_native.NAMES})
+    lib_call = getattr(lib, name)
+    return (lambda *a, keep=fn: lib_call(*a)), calls, types
+
+
+class Tensor:
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+
+class Stream:
+    cuda_stream = 0x7700000012345678
+
+
+def names():
+    from paper_2311_18677_amd import sw_native
+    return sw_native.NAMES
+
+
+@pytest.mark.parametrize("name", names())
+def test_every_argument_in_its_place(name):
+    call, calls, types = recorder(name)
+    args, want = [], []
+    for i, t in enumerate(types):
+        last = i == len(types) - 1
+        if t is ctypes.c_void_p:
+            at = 0x7f0000000000 + 4096 * (i + 1)
+            args.append(Stream() if last else (Tensor(at), at, None)[i % 3])
+            want.append(Stream.cuda_stream if last else (at, at, None)[i % 3])
+        else:
+            v = 2 ** 31 + 5 if t is ctypes.c_longlong else 1000 + i
+            args.append(v)
+            want.append(v)
+    assert call(*args) == -7
+    assert list(calls[0]) == want
+    with pytest.raises(TypeError):
+        call(*args[:-1])
+
+
+def test_conversions_and_refusals():
+    import numpy as np
+    call, calls, _ = recorder("sw_prefill_attn")
+    tail = (8, 1, 128, 64, None)
+    assert call(1, 2, np.int64(3), True, None, Tensor(6), 7.9, ctypes.c_int(4), *tail) == -7
+    assert calls[-1] == (1, 2, 3, 1, None, 6, 7, 4, 8, 1, 128, 64, None)
+    call(2 ** 64 - 1, 0, 0, 0, 0, 0, -1, 2 ** 32 + 3, -8, *tail[1:])         # modulo the C types' ranges
+    assert calls[-1][0] == 2 ** 64 - 1 and calls[-1][6:9] == (-1, 3, -8)
+    n = len(calls)
+    for bad in (("x", 1), (object(), 1), (1, 2.5), (1, "4"), (1, None), (Tensor("at"), 1)):
+        with pytest.raises((TypeError, ValueError)):
+            call(bad[0], 0, 0, 0, 0, 0, 0, bad[1], *tail)
+
+    class Broken:
+        def data_ptr(self):
+            raise RuntimeError("no storage")
+    with pytest.raises(RuntimeError, match="no storage"):
+        call(Broken(), 0, 0, 0, 0, 0, 0, 1, *tail)
+    assert len(calls) == n
+
+
+def test_references_are_given_back():
+    import sys
+    call, calls, _ = recorder("sw_decode_attn")
+    t, s = Tensor(10 ** 12), Stream()
+    before = sys.getrefcount(t), sys.getrefcount(s)
+    for _ in range(100):
+        call(t, t, t, t, t, 1, 8, 1, 128, 64, s)
+        calls.clear()
+    assert (sys.getrefcount(t), sys.getrefcount(s)) == before
+
+
+def test_a_library_needs_every_address():
+    from paper_2311_18677_amd import sw_native
+    with pytest.raises(KeyError):
+        sw_native.Library({})
+    with pytest.raises(ValueError):
+        sw_native.Library({n: 0 for n in sw_native.NAMES})
