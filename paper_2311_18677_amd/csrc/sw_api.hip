@@ -47,6 +47,22 @@ bool use_halves(long long blocks, long long groups, long long avg_q, int n_req, 
     return blocks >= 432 && (blocks <= 512 || (blocks <= 720 && avg_q >= 4000 && from_start));
 }
 
+// Waves a workgroup of the key-split prompt kernel has.  `items`: its workgroups, one per 32 query
+// positions and query head; avg_q: query tokens per request.
+//   Four waves share a compute unit with another workgroup.  While there is none, or only one far
+//   shorter, eight waves halve the chain of tiles that bounds the call: two waves of a SIMD
+//   walk two tiles in 0.86 us, one of them alone one tile in 0.66.  Time with four over time
+//   with eight, 1 to 32 heads: up to 288 workgroups 1.02 to 1.10 from 760 tokens on, 1.15 to 1.34
+//   from 2000, over blocks of 16 positions 1.20 at 1000 and 1.48 at 4000; below 600 tokens 0.95 to 1.04.
+//   Up to 512 workgroups, which take two rounds of eight waves, the second has to be short
+//   against the first (a prompt's late blocks come first): 1.11 to 1.31 where a request has
+//   more tokens than six times the workgroups, 0.95 to 0.99 where it has four times as many.
+//   Beyond that 0.73 to 1.01.  One prompt of 4000 tokens, 2 heads on one: 27.3 -> 22.0 us.
+int split_waves_for(long long items, long long avg_q)
+{
+    return items <= 512 && avg_q >= (items <= 288 ? 900 : 6 * items) ? 8 : 4;
+}
+
 thread_local std::string t_last_error = "";
 
 int fail(int code, const std::string &msg)
@@ -842,6 +858,11 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     if (which == 2) {
         a.hp = 1;
         a.qw = 1;
+        // (a mixed call's chains are not known here, and its other forms take four waves)
+        if (!mixed) {
+            const long long q_all = std::min<long long>(n_tokens, (long long)n_req * max_q_len);
+            split_waves = split_waves_for(((q_all + 31) / 32 + n_req - 1) * n_qh, q_all / n_req);
+        }
         if (knob_qw == 2 || knob_qw == 4 || knob_qw == 8) split_waves = knob_qw;
     } else if (which == 3) {
         a.hp = halves_hp;

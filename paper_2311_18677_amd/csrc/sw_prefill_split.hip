@@ -15,7 +15,8 @@
 // wave (two waves per SIMD issue in turn, and the chip is far from its matrix and memory rates).
 // Measured against one tile at a time, with 8 query heads over one key/value head: prompts of 548 and
 // 1500 tokens 16.3 -> 15.5 us, one of 1024 tokens 11.1 -> 10.5; 2 heads over one, 4096 tokens, 28.9
-// -> 27.3.  (The 32x32x16 product gains more on short chains, but loses 3 to 6 % from
+// -> 27.3 (22.0 with eight waves, which serve few and long chains: split_waves_for in
+// sw_api.hip).  (The 32x32x16 product gains more on short chains, but loses 3 to 6 % from
 // 4096 tokens on.)  The workgroup's code is in sw_prefill_split_body.h.
 #include "sw_prefill_split_body.h"
 #include "sw_merge.h"
