@@ -90,7 +90,76 @@ __device__ __forceinline__ void request_span(const SwPrefillArgs &a, int r, int 
     }
 }
 
-// Called by all 64 lanes of a wave; every wave of a workgroup gets the same answer.
+// The largest of the lanes' values (none negative).
+__device__ __forceinline__ int wave_max(int x)
+{
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true));   // row_shr:1, 2, 4, 8: see the scan
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15, 31
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
+// The same with the items of all requests numbered by work, longest first (one request per lane,
+// n_req <= 64), for the kernels whose workgroups have a compute unit each: their time ends with
+// the last workgroups, and with the requests one after the other those were the last request's, its
+// longest blocks among them.  A block's work is the position it ends at: its level, in blocks.  Levels
+// are taken in up to 64 bands of 2^sh (finer ones gain nothing), the band that holds the item is
+// found by bisection, a scan over the requests a step, and inside a band the requests follow each other.
+// With the cache store, 8 heads on one: 16 prompts of 100 to 1900 tokens 89.5 -> 70.5 us, 4 of 500 to
+// 8000 234 -> 207, 3 of 4000 to 9000 343 -> 284; 32 heads on 8, 16 of 48 to 880 90.2 -> 83.3; 16
+// heads on one, 12 of 1258 to 3776 388 -> 378.  The key-split kernel's workgroups, two to a compute
+// unit and a quarter as long, gain nothing and pay for the steps (6 prompts of 44 to 792 tokens, 8
+// heads on 8, up to 0.90): there the requests stay one after the other.  So they do beyond 64 requests.
+__device__ __forceinline__ QItem find_item_by_work(const SwPrefillArgs &a, unsigned item, int q_block)
+{
+    QItem it;
+    it.r = it.qb = it.L = it.NQ = 0;
+    it.q_first = 0;
+    it.valid = false;
+    const int lane = threadIdx.x & 63;
+    int L = 0, NQ = 0, qb_lo = 0, cnt = 0, top = 0;
+    long long qf = 0;
+    if (lane < a.n_req) {
+        request_span(a, lane, q_block, L, NQ, qf, qb_lo, cnt);
+        if (cnt > 0) top = (int)((unsigned)(L - NQ) / (unsigned)q_block) + qb_lo + cnt;
+    }
+    const int levels = wave_max(top);
+    const int sh = levels <= 64 ? 0 : 32 - __builtin_clz((unsigned)(levels - 1) >> 6);      // 64 << sh >= levels
+    auto from_band = [&](int x) {                   // items at band x and above
+        return (unsigned)__builtin_amdgcn_readlane(sw_wave_inclusive_scan(min(max(top - (x << sh), 0), cnt)), 63);
+    };
+    if (from_band(0) <= item) return it;            // past the last item
+    int band = 0;
+    unsigned above = 0;                             // items above the band
+    for (int step = levels > 1 ? 1 << (31 - __builtin_clz((unsigned)((levels - 1) >> sh))) : 0; step > 0; step >>= 1) {
+        const unsigned n = from_band(band + step);
+        if (n > item) band += step;
+        else          above = n;
+    }
+    const int higher = min(max(top - ((band + 1) << sh), 0), cnt);          // this lane's items above the band ...
+    const int mine = min(max(top - (band << sh), 0), cnt) - higher;         // ... and in it
+    const int incl = sw_wave_inclusive_scan(mine);
+    const unsigned long long hit = __ballot((unsigned)incl > item - above);
+    if (hit == 0) return it;                        // cannot happen when the counts are right
+    const int owner = __builtin_ctzll(hit);
+    const int rank = (int)(item - above) - __builtin_amdgcn_readlane(incl - mine - higher, owner);
+    it.r = owner;
+    it.qb = __builtin_amdgcn_readlane(qb_lo + cnt, owner) - 1 - rank;
+    it.L = __builtin_amdgcn_readlane(L, owner);
+    it.NQ = __builtin_amdgcn_readlane(NQ, owner);
+    const unsigned lo32 = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(unsigned long long)qf, owner);
+    const unsigned hi32 = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)qf >> 32), owner);
+    it.q_first = (long long)(((unsigned long long)hi32 << 32) | lo32);
+    it.valid = true;
+    return it;
+}
+
+// Called by all 64 lanes of a wave; every wave of a workgroup gets the same answer.  BY_WORK: see
+// find_item_by_work.
+template <bool BY_WORK = false>
 __device__ __forceinline__ QItem find_item(const SwPrefillArgs &a, unsigned item, int q_block)
 {
     QItem it;
@@ -110,6 +179,7 @@ __device__ __forceinline__ QItem find_item(const SwPrefillArgs &a, unsigned item
         it.valid = it.qb >= 0;
         return it;
     }
+    if (BY_WORK && a.n_req > 1 && a.n_req <= 64) return find_item_by_work(a, item, q_block);
     const int lane = threadIdx.x & 63;
     const int per = (a.n_req + 63) >> 6;            // consecutive requests per lane
     int L = 0, NQ = 0, qb_lo = 0, cnt = 0, mine = 0;

@@ -49,7 +49,7 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
     const unsigned hb = blockIdx.x % n_hb;
     const unsigned rest = blockIdx.x / n_hb;
     const int g = (int)(rest % (unsigned)a.n_kvh);
-    const QItem it = find_item(a, rest / (unsigned)a.n_kvh, q_block);
+    const QItem it = find_item<true>(a, rest / (unsigned)a.n_kvh, q_block);
     if (!it.valid) return;
     const int r = it.r, qb = it.qb, L = it.L, NQ = it.NQ;   // NQ: the request's last NQ tokens are its queries
     const long long q_first = it.q_first;
