@@ -172,14 +172,29 @@ hipError_t sw_launch_combine(const SwArgs &a, hipStream_t stream, const SwLaunch
 // Bound on the (request, block of q_block query tokens) items of a prompt-phase call, which
 // sizes its grid: no request has more than n_qblocks of them, and requests whose rows of q
 // and out do not overlap have at most n_tokens / q_block + 2 per request between them.
-static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bool *compact)
+// *compact: whether workgroups find their items by a scan of the lengths, which costs each a little
+// (every wave reads all the lengths, ceil(n_req / 64) per lane): it pays once it removes a good part
+// of the grid, and never for huge batches.  `any`: in a batch already where it removes anything,
+// for the kernels that number by work then (two prompts of 2133 and 1066 tokens, 32 heads on
+// 8: 86 -> 65 us), and where the empty workgroups lie unevenly.
+static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bool *compact, bool any)
 {
     const long long by_shape = (long long)a.n_req * a.n_qblocks;
     const long long by_rows = a.n_tokens / q_block + 2LL * a.n_req;
-    // the scan costs every workgroup a little (every wave reads all the lengths, ceil(n_req / 64)
-    // per lane): it pays once it removes a good part of the grid, and never for huge batches
-    *compact = by_rows * 4 < by_shape * 3 && a.n_req <= 4096;
+    *compact = any && a.n_req > 1 && a.n_req <= 64 ? by_rows < by_shape : by_rows * 4 < by_shape * 3 && a.n_req <= 4096;
     return *compact ? by_rows : by_shape;
+}
+// Key-split prompt kernel without the scan: whether a request's (query block, key/value head) pairs, numbered
+// request after request, miss some of the eight XCDs.  The blocks that a shorter request does not have
+// then leave those to the others alone (two prompts of 3200 and 1600 tokens, 8 heads on one: 57.6 ->
+// 44.9 us with the scan; 6 heads on 2: 48.6 -> 37.0).  Where they reach all eight the scan only costs (three
+// prompts of about 500 tokens, 8 heads on one: 9.6 against 10.5).
+static inline bool sw_pairs_miss_xcds(const SwPrefillArgs &a)
+{
+    const long long stride = (long long)a.n_req * a.n_kvh;
+    int common = 8;
+    while (stride % common) common /= 2;
+    return common > a.n_kvh;
 }
 bool       sw_prefill_mfma_supported(const SwPrefillArgs &a);
 void       sw_prefill_shape(int group, int cols, int *hp, int *qw);

@@ -344,7 +344,7 @@ hipError_t sw_launch_prefill_halves(const SwPrefillArgs &a_in, hipStream_t strea
     SwPrefillArgs a = a_in;
     if (a.head_dim != kD || a.hp < 1 || a.group % a.hp != 0 || a.qw < 1) return hipErrorInvalidValue;
     bool compact;
-    const long long blocks = sw_prefill_items(a, kQPerWave * a.qw, &compact) * a.n_kvh * (a.group / a.hp);
+    const long long blocks = sw_prefill_items(a, kQPerWave * a.qw, &compact, true) * a.n_kvh * (a.group / a.hp);
     a.compact = compact;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
