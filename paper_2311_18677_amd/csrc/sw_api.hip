@@ -32,17 +32,22 @@ constexpr long long kPrefillSharedMinGroups = 300;
 //   the whole form's and tiles are shared, which the key-split kernel does not do.  Time of the
 //   other kernels over this one's, 1 to 64 heads: 1.02 to 1.25 for prompts from 865 tokens on, up
 //   to 1.26 behind earlier context; groups of five and seven, where the whole form's workgroups
-//   have as few waves, 1.06 to 1.7.  Below 432: 1.15 down to 0.99.
+//   have as few waves, 1.06 to 1.7.  A whole prompt from 336 on: 1.05 at 350 to 1.28 at 420 (8 heads on
+//   one, 6656 tokens: 130 -> 105 us); 0.98 to 1.06 at 320, less below.
 //   Above two rounds the third is partly empty: behind earlier context (all chains alike) 0.92 to
 //   1.14, with short prompts 0.82 to 1.01.  Prompts of 4000 tokens and more have chains uneven
 //   enough to fill it: 1.03 to 1.25 up to 720 blocks, down to 0.96 at 790.
 //   Several requests: their lengths decide, which the host does not know (8 heads on one, 300 to
 //   340 groups: two of equal length 1.08 to 1.17, one twice the other 0.93 to 0.98).  Only where
-//   the whole form has fewer than eight waves does this one win throughout (1.01 to 2.1).
+//   the whole form has fewer than eight waves does this one win throughout (1.01 to 2.1).  Whole
+//   prompts with their blocks numbered by work, 448 to 512 blocks: 0.97 to 1.28 from 1000 tokens a request
+//   on, mostly above 1.1, 0.74 to 1.12 with shorter ones.
 // Groups of three heads make workgroups of six waves, which gain nothing (0.82 to 1.03).
-bool use_halves(long long blocks, long long groups, long long avg_q, int n_req, int columns, int whole_waves, bool from_start)
+bool use_halves(long long blocks, long long groups, long long avg_q, int n_req, int columns, int whole_waves, bool from_start,
+                bool whole_prompts)
 {
     if (columns != 4) return false;
+    if (whole_prompts && blocks <= 512 && (n_req == 1 ? blocks >= 336 : blocks >= 448 && avg_q >= 1000 && whole_waves == 8)) return true;
     if (n_req > 1) return whole_waves < 8 && avg_q >= 3000 && groups >= 300 && groups < (avg_q < 5000 ? 345 : 400);
     return blocks >= 432 && (blocks <= 512 || (blocks <= 720 && avg_q >= 4000 && from_start));
 }
@@ -852,7 +857,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         const bool from_start = !mixed || max_len <= q_all + q_all / 8;
         // (the caller's heads and waves are the other two kernels' shapes)
         if (knob_hp == 0 && knob_qw == 0 &&
-            use_halves(blocks, groups, avg_q, n_req, halves_hp * halves_qw, shared_hp * shared_qw, from_start)) which = 3;
+            use_halves(blocks, groups, avg_q, n_req, halves_hp * halves_qw, shared_hp * shared_qw, from_start, !mixed)) which = 3;
     }
     int split_waves = 4;
     if (which == 2) {

@@ -1,10 +1,15 @@
-"""Items of a batch numbered by work (shared-tile kernel, 2 to 64 requests): every query block of every
-request is served once, whatever the lengths.  Rows are those of the request in a call of its own, bit
-for bit (one request is numbered as it comes); 65 requests take the other numbering."""
+"""Items of a batch found by a scan of the lengths, numbered by work (shared-tile kernel) or request by
+request: every query block of every request is served once, whatever the lengths.  Rows are those of the request in a call
+of its own, bit for bit (one request is numbered as it comes); 65 requests take the other numbering.
+And the kernel that serves prompts of one or two rounds of the halves kernel's workgroups."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2311_18677_amd import binding as sw
+from helpers import assert_parity
+from test_prefill_halves_gpu import random_call, serving_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -13,7 +18,10 @@ def i32(a):
     return torch.tensor(a, dtype=torch.int32, device="cuda:0")
 
 
+@pytest.mark.parametrize("kernel", [1, 2])
 @pytest.mark.parametrize("n_qh,n_kvh,reqs", [
+    (8, 1, [(600, 600), (500, 500), (400, 400)]),                       # similar lengths: the scan or not
+    (6, 2, [(640, 640), (320, 320)]), (2, 2, [(1000, 1000), (3, 3), (990, 990), (1000, 1000)]),
     (8, 1, [(700, 700), (90, 90)]),
     (8, 1, [(33, 33), (0, 0), (1, 1), (1500, 1500), (64, 64), (32, 32)]),
     (8, 2, [(2047, 2047), (60, 60), (5, 5)]),                            # 64 levels of 64 tokens or fewer: bands of one
@@ -23,7 +31,7 @@ def i32(a):
     (8, 1, [(20 + 37 * (i % 11) * (i % 3), 20 + 37 * (i % 11) * (i % 3)) for i in range(64)]),
     (8, 1, [(20 + 37 * (i % 11) * (i % 3), 20 + 37 * (i % 11) * (i % 3)) for i in range(65)]),
 ])
-def test_rows_are_those_of_the_request_alone(n_qh, n_kvh, reqs):
+def test_rows_are_those_of_the_request_alone(n_qh, n_kvh, reqs, kernel):
     n, max_len, max_q = len(reqs), max(L for L, _ in reqs), max(q for _, q in reqs)
     tot = sum(q for _, q in reqs)
     gen = torch.Generator(device="cuda:0")
@@ -33,7 +41,7 @@ def test_rows_are_those_of_the_request_alone(n_qh, n_kvh, reqs):
     q = torch.randn(tot, n_qh, 128, generator=gen, dtype=torch.float16, device="cuda:0")
     starts = [sum(c for _, c in reqs[:r]) for r in range(n)]
     got, alone = (torch.full_like(q, float("nan")) for _ in range(2))
-    sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, 1)
+    sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, kernel)
     try:
         # (q_starts counts rows; single query tokens go through the token phase in either call)
         sw.sw_mixed_attn(q, k, v, i32([L for L, _ in reqs]), i32(starts), i32([c for _, c in reqs]), got, tot, n, n_qh, n_kvh,
@@ -49,3 +57,30 @@ def test_rows_are_those_of_the_request_alone(n_qh, n_kvh, reqs):
         sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, 0)
     assert not torch.isnan(got).any()
     assert torch.equal(got.view(torch.int16), alone.view(torch.int16))
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,lens,kernel", [
+    (8, 1, [5344], 2), (8, 1, [5376], 3),                  # 334 and 336 of its workgroups
+    (8, 1, [3500, 3600], 2), (8, 1, [3600, 3560], 3),      # 444 and 448
+    (32, 8, [999, 1000], 2), (32, 8, [1000, 1010], 3),     # tokens of a request
+    (16, 1, [2050, 1030, 1000], 3), (16, 1, [2080, 1030, 1000], 2),      # 512 and 516
+])
+def test_the_kernel_that_serves_whole_prompts(n_qh, n_kvh, lens, kernel):
+    call, out = random_call(n_qh, n_kvh, lens, lens, max(lens), False)
+    assert serving_kernel(call, out) == kernel
+    call()
+    torch.cuda.synchronize()
+    # first and last rows of every request from the oracle, over the caches random_call made
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(sum(lens) + n_qh)
+    n, max_len = len(lens), max(lens)
+    lay = sw.sw_kv_layout(n, n_kvh, 128, max_len)
+    k, v = (torch.randn(lay.total_elems, generator=gen, dtype=torch.float16, device="cuda:0") for _ in range(2))
+    q = torch.randn(sum(lens), n_qh, 128, generator=gen, dtype=torch.float16, device="cuda:0")
+    k_host, v_host, q_host = (x.cpu().numpy().view(np.uint16) for x in (k, v, q))
+    got = out.cpu().numpy()
+    for t in (0, 31, 32, 700, -33, -1):
+        rows = [sum(lens[:r]) + t % L for r, L in enumerate(lens)]
+        ref = oracle.decode_attn(np.ascontiguousarray(q_host[rows]), k_host, v_host, np.array([t % L + 1 for L in lens], np.int32),
+                                 n, n_qh, n_kvh, 128, max_len, lay.stride_req, lay.stride_kvh, lay.stride_tok)
+        assert_parity(got[rows], ref, "token %d" % t)
