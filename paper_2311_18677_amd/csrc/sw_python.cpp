@@ -30,10 +30,21 @@ bool address_of(PyObject *x, PyObject *name, bool method, void **out)
     if (!PyLong_CheckExact(x)) {
         got = method ? PyObject_CallMethodNoArgs(x, name) : PyObject_GetAttr(x, name);
         if (!got) {
-            // (an object without it: anything that int() takes)
-            if (!PyErr_ExceptionMatches(PyExc_AttributeError) || PyObject_HasAttr(x, name)) return false;
-            PyErr_Clear();
-            got = PyNumber_Long(x);
+            if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+            if (method) {                               // missing, or raised by the call itself, which stands
+                PyObject *type, *what, *trace;
+                PyErr_Fetch(&type, &what, &trace);
+                if (PyObject_HasAttr(x, name)) {
+                    PyErr_Restore(type, what, trace);
+                    return false;
+                }
+                Py_XDECREF(type);
+                Py_XDECREF(what);
+                Py_XDECREF(trace);
+            } else {
+                PyErr_Clear();
+            }
+            got = PyNumber_Long(x);                     // an object without it: anything that int() takes
             if (!got) return false;
         } else if (!PyLong_Check(got)) {
             PyErr_SetString(PyExc_TypeError, "an address must be an integer");

@@ -81,6 +81,29 @@ def test_conversions_and_refusals():
     assert len(calls) == n
 
 
+def test_the_error_of_an_address_is_its_own():
+    call, calls, _ = recorder("sw_advance_lens")
+
+    class Raises:
+        def data_ptr(self):
+            raise AttributeError("freed")
+
+    class Delegates:
+        def __getattr__(self, name):
+            if name == "data_ptr":
+                return Raises().data_ptr
+            raise AttributeError(name)
+    for x in (Raises(), Delegates()):
+        with pytest.raises(AttributeError, match="freed"):
+            call(x, 1, 4, None)
+
+    class Number:                       # no address of its own: what int() makes of it
+        def __int__(self):
+            return 4096
+    call(Number(), 1, 4, Number())
+    assert calls == [(4096, 1, 4, 4096)]
+
+
 def test_references_are_given_back():
     import sys
     call, calls, _ = recorder("sw_decode_attn")
