@@ -18,14 +18,24 @@
 namespace {
 
 PyObject *s_data_ptr, *s_cuda_stream, *s_value;       // interned attribute names
+PyObject *g_cast, *g_void_p;                          // ctypes.cast, ctypes.c_void_p
 
-// None -> NULL, an integer -> itself, anything else -> its `method`() (or attribute), as an integer.
-bool address_of(PyObject *x, PyObject *name, bool method, void **out)
-{
-    if (x == Py_None) {
-        *out = nullptr;
-        return true;
+// Objects that hold an address until the call is over.
+struct Kept {
+    PyObject *object[16];
+    int n = 0;
+    ~Kept()
+    {
+        while (n > 0) Py_DECREF(object[--n]);
     }
+};
+
+// None -> NULL, an integer -> itself, anything else -> its `method`() (or attribute): None, an integer or
+// what ctypes takes for a void pointer, text and bytes aside, which are no device addresses.
+bool address_of(PyObject *x, PyObject *name, bool method, void **out, Kept &kept)
+{
+    *out = nullptr;
+    if (x == Py_None) return true;
     PyObject *got = nullptr;
     if (!PyLong_CheckExact(x)) {
         got = method ? PyObject_CallMethodNoArgs(x, name) : PyObject_GetAttr(x, name);
@@ -47,9 +57,20 @@ bool address_of(PyObject *x, PyObject *name, bool method, void **out)
             got = PyNumber_Long(x);                     // an object without it: anything that int() takes
             if (!got) return false;
         } else if (!PyLong_Check(got)) {
-            PyErr_SetString(PyExc_TypeError, "an address must be an integer");
+            PyObject *pointer = nullptr, *value = nullptr;
+            if (PyUnicode_Check(got) || PyBytes_Check(got))
+                PyErr_SetString(PyExc_TypeError, "an address must be an integer");
+            else if (got != Py_None && (pointer = PyObject_CallFunctionObjArgs(g_cast, got, g_void_p, nullptr)))
+                value = PyObject_GetAttr(pointer, s_value);
+            const bool null = got == Py_None || value == Py_None;
             Py_DECREF(got);
-            return false;
+            if (pointer) kept.object[kept.n++] = pointer;         // (which refers to what it was made from)
+            if (null) {
+                Py_XDECREF(value);
+                return true;
+            }
+            if (!value) return false;
+            got = value;
         }
         x = got;
     }
@@ -107,15 +128,17 @@ struct Caller<ROWS, std::index_sequence<P...>, std::index_sequence<I...>> {
             PyErr_Format(PyExc_TypeError, "%s takes %zd arguments, not %zd", name, kArgs, n);
             return nullptr;
         }
+        static_assert(sizeof...(P) + 1 <= sizeof(Kept::object) / sizeof(PyObject *), "an object per address");
         void *p[sizeof...(P)], *stream;
+        Kept kept;
         unsigned long long rows = 0, v[sizeof...(I)];
         size_t at = 0;
         for (size_t k = 0; k < sizeof...(P); ++k)
-            if (!address_of(args[at++], s_data_ptr, true, &p[k])) return nullptr;
+            if (!address_of(args[at++], s_data_ptr, true, &p[k], kept)) return nullptr;
         if (ROWS && !integer_of<true>(args[at++], &rows)) return nullptr;
         for (size_t k = 0; k < sizeof...(I); ++k)
             if (!integer_of<false>(args[at++], &v[k])) return nullptr;
-        if (!address_of(args[at], s_cuda_stream, false, &stream)) return nullptr;
+        if (!address_of(args[at], s_cuda_stream, false, &stream, kept)) return nullptr;
         int rc;
         Py_BEGIN_ALLOW_THREADS
         if constexpr (ROWS)
@@ -232,7 +255,12 @@ PyMODINIT_FUNC PyInit_sw_native(void)
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
     s_value = PyUnicode_InternFromString("value");
-    if (!s_data_ptr || !s_cuda_stream || !s_value || PyType_Ready(&kLibraryType) < 0) return nullptr;
+    PyObject *ctypes = PyImport_ImportModule("ctypes");
+    if (!ctypes) return nullptr;
+    g_cast = PyObject_GetAttrString(ctypes, "cast");
+    g_void_p = PyObject_GetAttrString(ctypes, "c_void_p");
+    Py_DECREF(ctypes);
+    if (!s_data_ptr || !s_cuda_stream || !s_value || !g_cast || !g_void_p || PyType_Ready(&kLibraryType) < 0) return nullptr;
     PyObject *m = PyModule_Create(&kModule);
     if (!m) return nullptr;
     PyObject *names = PyTuple_New(kEntries);

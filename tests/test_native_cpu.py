@@ -104,6 +104,25 @@ def test_the_error_of_an_address_is_its_own():
     assert calls == [(4096, 1, 4, 4096)]
 
 
+def test_addresses_that_ctypes_takes():
+    call, calls, _ = recorder("sw_advance_lens")
+    lens = (ctypes.c_int32 * 4)()
+    at = ctypes.addressof(lens)
+
+    class Wrapped:
+        _as_parameter_ = at
+    for given, want in ((None, None), (ctypes.c_void_p(at), at), (ctypes.c_void_p(), None), (lens, at), (ctypes.byref(lens), at),
+                        (ctypes.pointer(lens), at), (Wrapped(), at)):
+        stream = Stream()
+        stream.cuda_stream = given
+        call(Tensor(given), 1, 4, stream)
+        assert calls.pop() == (want, 1, 4, want)
+    for bad in (2.5, object(), [1], b"4096", "4096"):
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            call(Tensor(bad), 1, 4, None)
+    assert calls == []
+
+
 def test_references_are_given_back():
     import sys
     call, calls, _ = recorder("sw_decode_attn")
