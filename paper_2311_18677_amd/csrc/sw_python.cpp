@@ -17,8 +17,9 @@
 
 namespace {
 
-PyObject *s_data_ptr, *s_cuda_stream, *s_value;       // interned attribute names
-PyObject *g_cast, *g_void_p;                          // ctypes.cast, ctypes.c_void_p
+PyObject *s_data_ptr, *s_cuda_stream, *s_value, *s_as_parameter;       // interned attribute names
+PyObject *g_cast, *g_void_p, *g_int;                  // ctypes.cast, ctypes.c_void_p, ctypes.c_int
+PyObject *g_ctypes_error, *g_argument_error;          // ctypes.ArgumentError; and it as a TypeError too
 
 // Objects that hold an address until the call is over.
 struct Kept {
@@ -30,9 +31,16 @@ struct Kept {
     }
 };
 
+// What a ctypes prototype refuses: ctypes.ArgumentError, which callers of it catch, and a TypeError.
+bool refuse(size_t at, const char *want, PyObject *x)
+{
+    PyErr_Format(g_argument_error, "argument %zu: %s, not %s", at + 1, want, Py_TYPE(x)->tp_name);
+    return false;
+}
+
 // None -> NULL, an integer -> itself, anything else -> its `method`() (or attribute): None, an integer or
 // what ctypes takes for a void pointer, text and bytes aside, which are no device addresses.
-bool address_of(PyObject *x, PyObject *name, bool method, void **out, Kept &kept)
+bool address_of(PyObject *x, size_t at, PyObject *name, bool method, void **out, Kept &kept)
 {
     *out = nullptr;
     if (x == Py_None) return true;
@@ -58,10 +66,17 @@ bool address_of(PyObject *x, PyObject *name, bool method, void **out, Kept &kept
             if (!got) return false;
         } else if (!PyLong_Check(got)) {
             PyObject *pointer = nullptr, *value = nullptr;
-            if (PyUnicode_Check(got) || PyBytes_Check(got))
-                PyErr_SetString(PyExc_TypeError, "an address must be an integer");
-            else if (got != Py_None && (pointer = PyObject_CallFunctionObjArgs(g_cast, got, g_void_p, nullptr)))
-                value = PyObject_GetAttr(pointer, s_value);
+            if (PyUnicode_Check(got) || PyBytes_Check(got)) {
+                refuse(at, "an address is required", got);
+            } else if (got != Py_None) {
+                pointer = PyObject_CallFunctionObjArgs(g_cast, got, g_void_p, nullptr);
+                if (pointer) {
+                    value = PyObject_GetAttr(pointer, s_value);
+                } else if (PyErr_ExceptionMatches(g_ctypes_error)) {
+                    PyErr_Clear();
+                    refuse(at, "an address is required", got);
+                }
+            }
             const bool null = got == Py_None || value == Py_None;
             Py_DECREF(got);
             if (pointer) kept.object[kept.n++] = pointer;         // (which refers to what it was made from)
@@ -81,32 +96,43 @@ bool address_of(PyObject *x, PyObject *name, bool method, void **out, Kept &kept
     return true;
 }
 
-// An int argument, taken modulo 2^32 (2^64 for a long long) as C takes it; ctypes integers too.  ANY:
-// whatever int() takes.
-template <bool ANY>
-bool integer_of(PyObject *x, unsigned long long *out)
+// The int argument number `at`, taken modulo 2^32 as C takes it, from what a c_int prototype takes: an
+// integer, a c_int, or an object whose _as_parameter_ is one.
+bool integer_of(PyObject *x, size_t at, unsigned long long *out)
 {
     PyObject *got = nullptr;
     if (!PyLong_Check(x)) {
-        got = ANY ? PyNumber_Long(x) : PyNumber_Index(x);
-        if (!got && !ANY && PyErr_ExceptionMatches(PyExc_TypeError)) {
-            PyObject *type, *what, *trace;
-            PyErr_Fetch(&type, &what, &trace);
-            got = PyObject_GetAttr(x, s_value);
-            if (got && !PyLong_Check(got)) Py_CLEAR(got);
-            if (got) {
-                Py_XDECREF(type);
-                Py_XDECREF(what);
-                Py_XDECREF(trace);
-            } else {
+        const int is_int = PyObject_IsInstance(x, g_int);
+        if (is_int < 0) return false;
+        got = is_int ? PyObject_GetAttr(x, s_value) : PyNumber_Index(x);
+        if (!got) {
+            PyErr_Clear();
+            PyObject *inner = PyObject_GetAttr(x, s_as_parameter);
+            if (!inner) {
                 PyErr_Clear();
-                PyErr_Restore(type, what, trace);
+                return refuse(at, "an integer is required", x);
             }
+            bool ok = false;
+            if (Py_EnterRecursiveCall(" while processing _as_parameter_") == 0) {
+                ok = integer_of(inner, at, out);
+                Py_LeaveRecursiveCall();
+            }
+            Py_DECREF(inner);
+            return ok;
         }
-        if (!got) return false;
         x = got;
     }
     *out = PyLong_AsUnsignedLongLongMask(x);
+    Py_XDECREF(got);
+    return !(*out == (unsigned long long)-1 && PyErr_Occurred());
+}
+
+// A row count, modulo 2^64: whatever int() takes.
+bool rows_of(PyObject *x, unsigned long long *out)
+{
+    PyObject *got = PyLong_Check(x) ? nullptr : PyNumber_Long(x);
+    if (!got && !PyLong_Check(x)) return false;
+    *out = PyLong_AsUnsignedLongLongMask(got ? got : x);
     Py_XDECREF(got);
     return !(*out == (unsigned long long)-1 && PyErr_Occurred());
 }
@@ -133,12 +159,12 @@ struct Caller<ROWS, std::index_sequence<P...>, std::index_sequence<I...>> {
         Kept kept;
         unsigned long long rows = 0, v[sizeof...(I)];
         size_t at = 0;
-        for (size_t k = 0; k < sizeof...(P); ++k)
-            if (!address_of(args[at++], s_data_ptr, true, &p[k], kept)) return nullptr;
-        if (ROWS && !integer_of<true>(args[at++], &rows)) return nullptr;
-        for (size_t k = 0; k < sizeof...(I); ++k)
-            if (!integer_of<false>(args[at++], &v[k])) return nullptr;
-        if (!address_of(args[at], s_cuda_stream, false, &stream, kept)) return nullptr;
+        for (size_t k = 0; k < sizeof...(P); ++k, ++at)
+            if (!address_of(args[at], at, s_data_ptr, true, &p[k], kept)) return nullptr;
+        if (ROWS && !rows_of(args[at++], &rows)) return nullptr;
+        for (size_t k = 0; k < sizeof...(I); ++k, ++at)
+            if (!integer_of(args[at], at, &v[k])) return nullptr;
+        if (!address_of(args[at], at, s_cuda_stream, false, &stream, kept)) return nullptr;
         int rc;
         Py_BEGIN_ALLOW_THREADS
         if constexpr (ROWS)
@@ -226,7 +252,7 @@ PyObject *library_new(PyTypeObject *type, PyObject *args, PyObject *)
         PyObject *x = PyDict_GetItemString(addresses, kNames[k]);        // borrowed
         unsigned long long v = 0;
         if (!x) PyErr_SetString(PyExc_KeyError, kNames[k]);
-        if (!x || !integer_of<false>(x, &v) || v == 0) {
+        if (!x || !rows_of(x, &v) || v == 0) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, kNames[k]);
             Py_DECREF(self);
             return nullptr;
@@ -255,12 +281,19 @@ PyMODINIT_FUNC PyInit_sw_native(void)
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
     s_value = PyUnicode_InternFromString("value");
+    s_as_parameter = PyUnicode_InternFromString("_as_parameter_");
     PyObject *ctypes = PyImport_ImportModule("ctypes");
     if (!ctypes) return nullptr;
     g_cast = PyObject_GetAttrString(ctypes, "cast");
     g_void_p = PyObject_GetAttrString(ctypes, "c_void_p");
+    g_int = PyObject_GetAttrString(ctypes, "c_int");
+    g_ctypes_error = PyObject_GetAttrString(ctypes, "ArgumentError");
     Py_DECREF(ctypes);
-    if (!s_data_ptr || !s_cuda_stream || !s_value || !g_cast || !g_void_p || PyType_Ready(&kLibraryType) < 0) return nullptr;
+    if (!s_data_ptr || !s_cuda_stream || !s_value || !s_as_parameter || !g_cast || !g_void_p || !g_int || !g_ctypes_error) return nullptr;
+    PyObject *bases = PyTuple_Pack(2, g_ctypes_error, PyExc_TypeError);
+    if (bases) g_argument_error = PyErr_NewException("sw_native.ArgumentError", bases, nullptr);
+    Py_XDECREF(bases);
+    if (!g_argument_error || PyType_Ready(&kLibraryType) < 0) return nullptr;
     PyObject *m = PyModule_Create(&kModule);
     if (!m) return nullptr;
     PyObject *names = PyTuple_New(kEntries);

@@ -123,6 +123,53 @@ def test_addresses_that_ctypes_takes():
     assert calls == []
 
 
+def test_integers_are_those_that_ctypes_takes():
+    """Each value through the native caller and through a ctypes prototype of the same shape."""
+    import enum
+    call, calls, types = recorder("sw_advance_lens")
+    by_ctypes = ctypes.CFUNCTYPE(ctypes.c_int, *types)(lambda *args: calls.append(args) or -7)
+
+    class Parameter:
+        def __init__(self, x):
+            self._as_parameter_ = x
+
+    class Index:
+        def __init__(self, x):
+            self.x = x
+
+        def __index__(self):
+            if self.x is None:
+                raise OverflowError("no index")
+            return self.x
+
+    class Valued:
+        value = 3
+    Member = enum.Enum("Member", {"ONE": 1})
+    taken = [3, True, -1, 2 ** 32 + 3, -2 ** 70 - 1, ctypes.c_int(4), ctypes.c_int(-4), Index(5), Parameter(6),
+             Parameter(ctypes.c_int(7)), Parameter(Parameter(Index(8))), enum.IntEnum("Number", {"NINE": 9}).NINE]
+    refused = [2.5, "4", b"4", None, object(), Member.ONE, Valued(), ctypes.c_longlong(2 ** 32 + 3), ctypes.c_short(2),
+               ctypes.c_uint(2), Parameter(2.5), Parameter(Member.ONE), Index(None), [1], 3 + 0j]
+    for x in taken:
+        assert call(4096, x, 4, None) == by_ctypes(4096, x, 4, None) == -7
+        native, other = calls
+        assert native == other
+        calls.clear()
+    for x in refused:
+        with pytest.raises(ctypes.ArgumentError):
+            by_ctypes(4096, x, 4, None)
+        with pytest.raises(ctypes.ArgumentError, match="argument 2: ") as refusal:
+            call(4096, x, 4, None)
+        assert isinstance(refusal.value, TypeError)
+    for x in ("4096", 2.5, object()):
+        with pytest.raises(ctypes.ArgumentError, match="argument 1: "):
+            call(Tensor(x), 1, 4, None)
+    endless = Parameter(None)
+    endless._as_parameter_ = endless
+    with pytest.raises((RecursionError, ctypes.ArgumentError)):
+        call(4096, endless, 4, None)
+    assert calls == []
+
+
 def test_references_are_given_back():
     import sys
     call, calls, _ = recorder("sw_decode_attn")
