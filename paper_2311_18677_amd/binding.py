@@ -80,7 +80,7 @@ def load():
     try:
         from . import sw_native
     except ImportError as e:
-        raise RuntimeError("sw_native.so is not built (%s); run `python -m paper_2311_18677_amd.build`" % e)
+        raise RuntimeError("sw_native is not built for this interpreter (%s); run `python -m paper_2311_18677_amd.build`" % e)
     lib = ctypes.CDLL(LIB_PATH)
     vp, ci = ctypes.c_void_p, ctypes.c_int
     lib.sw_kv_layout.restype = ci

@@ -1,4 +1,4 @@
-"""Build libsw_decode.so (hand-written HIP for gfx950) and sw_native.so (its Python caller) in-tree.
+"""Build libsw_decode.so (hand-written HIP for gfx950) and sw_native (its Python caller) in-tree.
 
     python -m paper_2311_18677_amd.build
 
@@ -16,7 +16,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsw_decode.so")
-NATIVE = os.path.join(HERE, "sw_native.so")          # the Python side of a call (csrc/sw_python.cpp)
+# the Python side of a call (csrc/sw_python.cpp); named for the interpreter whose object layouts it is
+# compiled against, so that no other one imports it
+NATIVE = os.path.join(HERE, "sw_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["sw_api.hip", "sw_partial_valu.hip", "sw_decode_split.hip", "sw_combine.hip", "sw_lens.hip", "sw_prefill_mfma.hip", "sw_kv_handoff.hip", "sw_prefill_split.hip", "sw_prefill_halves.hip", "sw_calibrate.hip", "sw_kv_store.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -53,6 +55,9 @@ def _build_native():
     if res.returncode != 0:
         raise RuntimeError("%s failed on sw_python.cpp:\n%s" % (cmd[0], res.stderr))
     os.replace(tmp, NATIVE)
+    unnamed = os.path.join(HERE, "sw_native.so")
+    if os.path.exists(unnamed) and unnamed != NATIVE:          # of a build before, which any interpreter would take
+        os.unlink(unnamed)
 
 
 def build(verbose=False):

@@ -35,12 +35,19 @@ class Stream:
     cuda_stream = 0x7700000012345678
 
 
-def names():
-    from paper_2311_18677_amd import sw_native
-    return sw_native.NAMES
+NAMES = ("sw_decode_attn", "sw_decode_attn_static", "sw_decode_attn_paged", "sw_decode_attn_append", "sw_decode_attn_paged_append",
+         "sw_advance_lens", "sw_prefill_attn", "sw_prefill_attn_paged", "sw_mixed_attn", "sw_mixed_attn_paged", "sw_kv_store",
+         "sw_kv_store_paged", "sw_kv_pack", "sw_kv_unpack", "sw_kv_span_plan")
 
 
-@pytest.mark.parametrize("name", names())
+def test_the_module_is_this_interpreters_and_has_every_entry_point():
+    import sysconfig
+    from paper_2311_18677_amd import build, sw_native
+    assert sw_native.__file__.endswith("sw_native" + sysconfig.get_config_var("EXT_SUFFIX")) and sw_native.__file__ == build.NATIVE
+    assert sw_native.NAMES == NAMES
+
+
+@pytest.mark.parametrize("name", NAMES)
 def test_every_argument_in_its_place(name):
     call, calls, types = recorder(name)
     args, want = [], []
