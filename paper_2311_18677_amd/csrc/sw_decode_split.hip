@@ -789,7 +789,7 @@ hipError_t sw_launch_decode_split(const SwArgs &a, hipStream_t stream, const SwL
 // (request, query block) items are numbered compactly.
 static long long mixed_prompt_blocks(const SwPrefillArgs &p, bool *compact)
 {
-    const long long pairs = sw_prefill_items(p, sw_prefill::kQPerWave, compact, sw_pairs_miss_xcds(p)) * p.n_kvh;
+    const long long pairs = sw_prefill_items(p, sw_prefill::kQPerWave, compact, sw_split_scans_early(p)) * p.n_kvh;
     return (pairs + 7) / 8 * 8 * p.group;
 }
 

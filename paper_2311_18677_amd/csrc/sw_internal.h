@@ -176,7 +176,7 @@ hipError_t sw_launch_combine(const SwArgs &a, hipStream_t stream, const SwLaunch
 // (every wave reads all the lengths, ceil(n_req / 64) per lane): it pays once it removes a good part
 // of the grid, and never for huge batches.  `any`: in a batch already where it removes anything,
 // for the kernels that number by work then (two prompts of 2133 and 1066 tokens, 32 heads on
-// 8: 86 -> 65 us), and where the empty workgroups lie unevenly.
+// 8: 86 -> 65 us), and for the key-split kernel where sw_split_scans_early says so.
 static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bool *compact, bool any)
 {
     const long long by_shape = (long long)a.n_req * a.n_qblocks;
@@ -184,17 +184,28 @@ static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bo
     *compact = any && a.n_req > 1 && a.n_req <= 64 ? by_rows < by_shape : by_rows * 4 < by_shape * 3 && a.n_req <= 4096;
     return *compact ? by_rows : by_shape;
 }
-// Key-split prompt kernel without the scan: whether a request's (query block, key/value head) pairs, numbered
-// request after request, miss some of the eight XCDs.  The blocks that a shorter request does not have
-// then leave those to the others alone (two prompts of 3200 and 1600 tokens, 8 heads on one: 57.6 ->
-// 44.9 us with the scan; 6 heads on 2: 48.6 -> 37.0).  Where they reach all eight the scan only costs (three
-// prompts of about 500 tokens, 8 heads on one: 9.6 against 10.5).
-static inline bool sw_pairs_miss_xcds(const SwPrefillArgs &a)
+// Whether the key-split prompt kernel takes the scan of the lengths already where it removes 15 % of the grid.
+// Without the scan the (query block, key/value head) pairs are numbered block by block, late blocks first, over
+// all requests, and the blocks that a shorter request does not have are empty workgroups.  Where a
+// request's pairs reach all eight XCDs these cost little (three prompts of about 500 tokens, 8 heads on one:
+// 9.6 us against 10.5 with the scan); where they miss some XCDs, the others alone get the missing work.  The scan
+// mends that but takes the requests one after the other, which costs a batch of many requests more than
+// the empty ones do.  Time without it over time with it, 1300 batches of 1 to 24 heads: two to four requests
+// whose heads come in groups, on a grid beyond the chip's 512 places that shrinks by 15 % or more, 0.96 to 1.47,
+// in the mean 1.16 (3200 and 1600 tokens, 8 heads on one: 57.6 -> 44.9 us); 10 to 15 % of the grid 0.89 to 1.2, less
+// 0.9 to 1.25; one head on one 0.87 to 1.26 at up to four requests; five and more requests 0.72 to 1.52, in
+// the mean 0.96 (18 of about 960 tokens, one head: 14.3 -> 20.0); grids that the chip holds at once 0.78 to 1.2,
+// in the mean 0.96.
+static inline bool sw_split_scans_early(const SwPrefillArgs &a)
 {
+    const long long by_shape = (long long)a.n_req * a.n_qblocks;
+    const long long by_rows = a.n_tokens / 32 + 2LL * a.n_req;          // (blocks of 32 query tokens)
+    if (a.n_req < 2 || a.n_req > 4 || a.group < 2) return false;
+    if (by_rows * 20 >= by_shape * 17 || by_shape * a.n_qh <= 512) return false;
     const long long stride = (long long)a.n_req * a.n_kvh;
     int common = 8;
     while (stride % common) common /= 2;
-    return common > a.n_kvh;
+    return common > a.n_kvh;                                            // a request's pairs miss some XCDs
 }
 bool       sw_prefill_mfma_supported(const SwPrefillArgs &a);
 void       sw_prefill_shape(int group, int cols, int *hp, int *qw);
