@@ -23,7 +23,7 @@ def i32(a):
     (8, 1, [(600, 600), (500, 500), (400, 400)]),                       # similar lengths: the scan or not
     (6, 2, [(640, 640), (320, 320)]), (2, 2, [(1000, 1000), (3, 3), (990, 990), (1000, 1000)]),
     (8, 1, [(700, 700), (90, 90)]),
-    (8, 1, [(1600, 1600), (1000, 1000)]), (4, 1, [(1100, 1100), (1000, 1000), (800, 800), (700, 700)]),      # a tenth of a full grid
+    (8, 1, [(1600, 1600), (900, 900)]), (4, 1, [(1100, 1100), (900, 900), (700, 700), (600, 600)]),      # a sixth of a full grid
     (8, 1, [(33, 33), (0, 0), (1, 1), (1500, 1500), (64, 64), (32, 32)]),
     (8, 2, [(2047, 2047), (60, 60), (5, 5)]),                            # 64 levels of 64 tokens or fewer: bands of one
     (8, 1, [(2049, 2049), (31, 31), (40, 40)]),                         # 65 levels: bands of two
