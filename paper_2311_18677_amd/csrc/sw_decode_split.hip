@@ -787,15 +787,15 @@ hipError_t sw_launch_decode_split(const SwArgs &a, hipStream_t stream, const SwL
 
 // Workgroups of the mixed kernel's prompt part (the prompt kernel's own grid), and whether its
 // (request, query block) items are numbered compactly.
-static long long mixed_prompt_blocks(const SwPrefillArgs &p, bool *compact)
+static long long mixed_prompt_blocks(const SwPrefillArgs &p, int *compact)
 {
-    const long long pairs = sw_prefill_items(p, sw_prefill::kQPerWave, compact, sw_split_scans_early(p)) * p.n_kvh;
+    const long long pairs = sw_prefill_items(p, sw_prefill::kQPerWave, sw_split_scans_early(p), compact) * p.n_kvh;
     return (pairs + 7) / 8 * 8 * p.group;
 }
 
 bool sw_mixed_supported(const SwArgs &d, const SwPrefillArgs &p)
 {
-    bool compact;
+    int compact;
     const long long n_prompt = mixed_prompt_blocks(p, &compact);
     return d.head_dim == 128 && p.head_dim == 128 && sw_decode_split_supported(d) && d.waves == 4 && !d.units && !d.k_new
         && sw_worklist_per(d.n_req) > 0 && n_prompt > 0 && n_prompt + decode_blocks(d) <= 0x7fffffffLL;
@@ -805,7 +805,7 @@ hipError_t sw_launch_mixed(const SwArgs &d, const SwPrefillArgs &p_in, hipStream
 {
     if (!sw_mixed_supported(d, p_in)) return hipErrorNotSupported;
     SwPrefillArgs p = p_in;
-    bool compact;
+    int compact;
     const unsigned np = (unsigned)mixed_prompt_blocks(p, &compact);
     p.compact = compact;
     const dim3 grid((unsigned)(np + decode_blocks(d)));

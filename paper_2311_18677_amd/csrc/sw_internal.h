@@ -78,7 +78,7 @@ struct SwPrefillArgs {
     int   head_dim, max_len;
     int   max_q;                        // bound on the query tokens of a request (sizes the grid)
     int   skip_single;                  // non-zero: requests with exactly one query token are left out
-    int   compact;                      // non-zero: workgroups find their (request, query block) by a scan of the lengths
+    int   compact;                      // how workgroups find their (request, query block): see sw_prefill_items
     int   hp;                           // query heads (of one group) per workgroup
     int   qw;                           // waves per query head in a workgroup
     int   n_qblocks;                    // query blocks (of 32 * qw positions) that cover max_len
@@ -172,17 +172,35 @@ hipError_t sw_launch_combine(const SwArgs &a, hipStream_t stream, const SwLaunch
 // Bound on the (request, block of q_block query tokens) items of a prompt-phase call, which
 // sizes its grid: no request has more than n_qblocks of them, and requests whose rows of q
 // and out do not overlap have at most n_tokens / q_block + 2 per request between them.
-// *compact: whether workgroups find their items by a scan of the lengths, which costs each a little
+// *compact: how workgroups find their items: kDirect, or by a scan of the lengths, which costs each a little
 // (every wave reads all the lengths, ceil(n_req / 64) per lane): it pays once it removes a good part
-// of the grid, and never for huge batches.  `any`: in a batch already where it removes anything,
-// for the kernels that number by work then (two prompts of 2133 and 1066 tokens, 32 heads on
-// 8: 86 -> 65 us), and for the key-split kernel where sw_split_scans_early says so.
-static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bool *compact, bool any)
+// of the grid, and never for huge batches.  `early`: also where it removes less.
+enum { kDirect = 0, kScan = 1, kScanByWork = 2 };
+static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bool early, int *compact)
 {
     const long long by_shape = (long long)a.n_req * a.n_qblocks;
     const long long by_rows = a.n_tokens / q_block + 2LL * a.n_req;
-    *compact = any && a.n_req > 1 && a.n_req <= 64 ? by_rows < by_shape : by_rows * 4 < by_shape * 3 && a.n_req <= 4096;
+    *compact = early || (by_rows * 4 < by_shape * 3 && a.n_req <= 4096) ? kScan : kDirect;
     return *compact ? by_rows : by_shape;
+}
+// The same for the kernels that can number a batch's items by work, with a compute unit to each of their
+// workgroups (`per_item` of them an item).  The numbering takes its workgroup a scan of the requests per step of
+// the search, and shortens the call by a part of one chain: it wins where chains are long against the number
+// of rounds of 256 workgroups.  Time without it over time with it, batches of 1 to 64 heads that are scanned either
+// way: 0.95 to 1.60, in the mean 1.14, where a request has three blocks of 32 tokens a round; 0.90 to 1.16, in
+// the mean 1.00, below (20 prompts of 490 tokens, 32 heads on 8: 92 -> 102 us; 24 of 250, 64 on 16: 94 -> 103).  There
+// the scan also pays from a tenth of the grid on (two prompts of 2133 and 1066 tokens, 32 heads on
+// 8: 86 -> 65 us): 0.94 to 1.47, in the mean 1.07 (19 of these 565 batches below 0.97); elsewhere 0.92 to 1.31, in
+// the mean 1.02, a seventh of them below 0.97.
+static inline long long sw_prefill_items_by_work(const SwPrefillArgs &a, int q_block, long long per_item, int *compact)
+{
+    const long long by_shape = (long long)a.n_req * a.n_qblocks;
+    const long long by_rows = a.n_tokens / q_block + 2LL * a.n_req;
+    const long long rows = a.n_tokens / (a.n_req > 0 ? a.n_req : 1);        // of a request, the host's estimate
+    const bool by_work = a.n_req > 1 && a.n_req <= 64 && rows * (256 / 32) >= 3 * by_rows * per_item;
+    const long long items = sw_prefill_items(a, q_block, by_work && by_rows * 10 < by_shape * 9, compact);
+    if (by_work && *compact) *compact = kScanByWork;
+    return items;
 }
 // Whether the key-split prompt kernel takes the scan of the lengths already where it removes 15 % of the grid.
 // Without the scan the (query block, key/value head) pairs are numbered block by block, late blocks first, over

@@ -64,8 +64,8 @@ hipError_t sw_launch_kv_store(const SwPrefillArgs &a_in, const uint16_t *k_rows,
     SwPrefillArgs a = a_in;
     if (a.head_dim != 64 && a.head_dim != 128) return hipErrorNotSupported;
     if (a.n_kvh < 1 || a.n_kvh > 65535) return hipErrorInvalidValue;
-    bool compact;
-    const long long items = sw_prefill_items(a, kStoreTokens, &compact, false);
+    int compact;
+    const long long items = sw_prefill_items(a, kStoreTokens, false, &compact);
     if (items <= 0 || items > 0x7fffffffLL) return hipErrorInvalidValue;
     a.compact = compact;
     const dim3 grid((unsigned)items, (unsigned)a.n_kvh);

@@ -105,7 +105,7 @@ __device__ __forceinline__ int wave_max(int x)
 // The same with the items of all requests numbered by work, longest first (one request per lane,
 // n_req <= 64), for the kernels whose workgroups have a compute unit each: their time ends with
 // the last workgroups, and with the requests one after the other those were the last request's, its
-// longest blocks among them.  A block's work is the position it ends at: its level, in blocks.  Levels
+// longest blocks among them (which batches take it: sw_prefill_items_by_work).  A block's work is the position it ends at: its level, in blocks.  Levels
 // are taken in up to 64 bands of 2^sh (finer ones gain nothing), the band that holds the item is
 // found by bisection, a scan over the requests a step, and inside a band the requests follow each other.
 // With the cache store, 8 heads on one: 16 prompts of 100 to 1900 tokens 89.5 -> 70.5 us, 4 of 500 to
@@ -179,7 +179,7 @@ __device__ __forceinline__ QItem find_item(const SwPrefillArgs &a, unsigned item
         it.valid = it.qb >= 0;
         return it;
     }
-    if (BY_WORK && a.n_req > 1 && a.n_req <= 64) return find_item_by_work(a, item, q_block);
+    if (BY_WORK && a.compact == kScanByWork) return find_item_by_work(a, item, q_block);
     const int lane = threadIdx.x & 63;
     const int per = (a.n_req + 63) >> 6;            // consecutive requests per lane
     int L = 0, NQ = 0, qb_lo = 0, cnt = 0, mine = 0;

@@ -343,8 +343,9 @@ hipError_t sw_launch_prefill_halves(const SwPrefillArgs &a_in, hipStream_t strea
 {
     SwPrefillArgs a = a_in;
     if (a.head_dim != kD || a.hp < 1 || a.group % a.hp != 0 || a.qw < 1) return hipErrorInvalidValue;
-    bool compact;
-    const long long blocks = sw_prefill_items(a, kQPerWave * a.qw, &compact, true) * a.n_kvh * (a.group / a.hp);
+    int compact;
+    const long long per_item = (long long)a.n_kvh * (a.group / a.hp);
+    const long long blocks = sw_prefill_items_by_work(a, kQPerWave * a.qw, per_item, &compact) * per_item;
     a.compact = compact;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);

@@ -50,8 +50,8 @@ hipError_t sw_launch_prefill_split(const SwPrefillArgs &a_in, int waves, hipStre
 {
     if (a_in.head_dim != kD) return hipErrorNotSupported;
     SwPrefillArgs a = a_in;
-    bool compact;
-    const long long pairs = sw_prefill_items(a, kQPerWave, &compact, sw_split_scans_early(a)) * a.n_kvh;
+    int compact;
+    const long long pairs = sw_prefill_items(a, kQPerWave, sw_split_scans_early(a), &compact) * a.n_kvh;
     const long long n_prompt = (pairs + 7) / 8 * 8 * a.group;      // see the kernel's numbering of the heads
     if (n_prompt <= 0 || n_prompt > 0x7fffffffLL) return hipErrorInvalidValue;
     a.compact = compact;
