@@ -26,28 +26,33 @@ constexpr long long kPrefillSharedMinGroups = 300;
 
 // Whether the shared-tile form with the key range in two halves serves a prompt call.  `blocks` is
 // the number of its workgroups, one to a compute unit at a time; `groups` counts the work in
-// workgroups of the whole form, `whole_waves` waves each; avg_q: query tokens per request;
-// from_start: the queries are known to begin (nearly) at position 0.
+// workgroups of the whole form, `whole_waves` waves each; of this form's `columns` columns of waves `heads`
+// are query heads, the rest query positions; avg_q: query tokens per request; from_start: the queries
+// are known to begin (nearly) at position 0.
 //   One request, up to two rounds of workgroups (432 to 512 blocks): the chains are half as long as
 //   the whole form's and tiles are shared, which the key-split kernel does not do.  Time of the
 //   other kernels over this one's, 1 to 64 heads: 1.02 to 1.25 for prompts from 865 tokens on, up
 //   to 1.26 behind earlier context; groups of five and seven, where the whole form's workgroups
-//   have as few waves, 1.06 to 1.7.  A whole prompt from 336 on: 1.05 at 350 to 1.28 at 420 (8 heads on
-//   one, 6656 tokens: 130 -> 105 us); 0.98 to 1.06 at 320, less below.
+//   have as few waves, 1.06 to 1.7.  A whole prompt from 336 on: 0.95 to 1.13 at 336 to 384, 1.04 to
+//   1.69 above (8 heads on one, 6656 tokens: 130 -> 105 us); 0.98 to 1.06 at 320, less below.  With one head a
+//   workgroup and so blocks of 128 positions only from 1500 tokens on: a short prompt has few of them, the last
+//   partly empty (700 tokens 0.79 to 0.99, 1100 0.92 to 1.16; 56 heads on 8, 800: 24.7 -> 28.8 us).
 //   Above two rounds the third is partly empty: behind earlier context (all chains alike) 0.92 to
 //   1.14, with short prompts 0.82 to 1.01.  Prompts of 4000 tokens and more have chains uneven
 //   enough to fill it: 1.03 to 1.25 up to 720 blocks, down to 0.96 at 790.
 //   Several requests: their lengths decide, which the host does not know (8 heads on one, 300 to
 //   340 groups: two of equal length 1.08 to 1.17, one twice the other 0.93 to 0.98).  Only where
 //   the whole form has fewer than eight waves does this one win throughout (1.01 to 2.1).  Whole
-//   prompts with their blocks numbered by work, 448 to 512 blocks: 0.97 to 1.28 from 1000 tokens a request
-//   on, mostly above 1.1, 0.74 to 1.12 with shorter ones.
+//   prompts with their blocks numbered by work, 448 to 512 blocks: 0.93 to 1.39 from 1000 tokens a request
+//   on, in the mean 1.15, 0.74 to 1.12 with shorter ones; with blocks of 128 positions 1.00 to 2.3 from 1500 on, 0.88
+//   to 1.6 below (7 prompts of 1114 tokens, 8 heads on 8: 42 -> 48 us).
 // Groups of three heads make workgroups of six waves, which gain nothing (0.82 to 1.03).
-bool use_halves(long long blocks, long long groups, long long avg_q, int n_req, int columns, int whole_waves, bool from_start,
-                bool whole_prompts)
+bool use_halves(long long blocks, long long groups, long long avg_q, int n_req, int heads, int columns, int whole_waves,
+                bool from_start, bool whole_prompts)
 {
     if (columns != 4) return false;
-    if (whole_prompts && blocks <= 512 && (n_req == 1 ? blocks >= 336 : blocks >= 448 && avg_q >= 1000 && whole_waves == 8)) return true;
+    if (whole_prompts && blocks <= 512 && (heads > 1 || avg_q >= 1500) &&
+        (n_req == 1 ? blocks >= 336 : blocks >= 448 && avg_q >= 1000 && whole_waves == 8)) return true;
     if (n_req > 1) return whole_waves < 8 && avg_q >= 3000 && groups >= 300 && groups < (avg_q < 5000 ? 345 : 400);
     return blocks >= 432 && (blocks <= 512 || (blocks <= 720 && avg_q >= 4000 && from_start));
 }
@@ -857,7 +862,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         const bool from_start = !mixed || max_len <= q_all + q_all / 8;
         // (the caller's heads and waves are the other two kernels' shapes)
         if (knob_hp == 0 && knob_qw == 0 &&
-            use_halves(blocks, groups, avg_q, n_req, halves_hp * halves_qw, shared_hp * shared_qw, from_start, !mixed)) which = 3;
+            use_halves(blocks, groups, avg_q, n_req, halves_hp, halves_hp * halves_qw, shared_hp * shared_qw, from_start, !mixed)) which = 3;
     }
     int split_waves = 4;
     if (which == 2) {

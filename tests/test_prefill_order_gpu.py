@@ -65,6 +65,8 @@ def test_rows_are_those_of_the_request_alone(n_qh, n_kvh, reqs, kernel):
     (8, 1, [3500, 3600], 2), (8, 1, [3600, 3560], 3),      # 444 and 448
     (32, 8, [999, 1000], 2), (32, 8, [1000, 1010], 3),     # tokens of a request
     (16, 1, [2050, 1030, 1000], 3), (16, 1, [2080, 1030, 1000], 2),      # 512 and 516
+    (28, 4, [1499], 2), (28, 4, [1500], 3),                # blocks of 128 positions: tokens
+    (8, 8, [1499, 1498, 1499, 1500, 1499], 2), (8, 8, [1500] * 5, 3),
 ])
 def test_the_kernel_that_serves_whole_prompts(n_qh, n_kvh, lens, kernel):
     call, out = random_call(n_qh, n_kvh, lens, lens, max(lens), False)
