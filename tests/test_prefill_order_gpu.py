@@ -8,7 +8,7 @@ import torch
 
 import oracle
 from paper_2311_18677_amd import binding as sw
-from helpers import assert_parity
+from helpers import assert_parity, launches
 from test_prefill_halves_gpu import random_call, serving_kernel
 
 pytestmark = pytest.mark.gpu
@@ -87,3 +87,44 @@ def test_the_kernel_that_serves_whole_prompts(n_qh, n_kvh, lens, kernel):
         ref = oracle.decode_attn(np.ascontiguousarray(q_host[rows]), k_host, v_host, np.array([t % L + 1 for L in lens], np.int32),
                                  n, n_qh, n_kvh, 128, max_len, lay.stride_req, lay.stride_kvh, lay.stride_tok)
         assert_parity(got[rows], ref, "token %d" % t)
+
+
+def grid_of(n_qh, n_kvh, lens, kernel):
+    """Workgroups that the prompt kernel (SW_PARAM_PREFILL_KERNEL) is launched with."""
+    n, tot, max_len = len(lens), sum(lens), max(lens)
+    k, v = (torch.zeros(sw.sw_kv_layout(n, n_kvh, 128, max_len).total_elems, dtype=torch.float16, device="cuda:0") for _ in range(2))
+    q = torch.zeros(tot, n_qh, 128, dtype=torch.float16, device="cuda:0")
+    out, seq, first = torch.empty_like(q), i32(lens), i32([sum(lens[:r]) for r in range(n)])
+    torch.cuda.synchronize()
+    sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, kernel)
+    try:
+        (grid, _), = launches(lambda s: sw.sw_prefill_attn(q, k, v, seq, first, out, tot, n, n_qh, n_kvh, 128, max_len, stream=s))
+    finally:
+        sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, 0)
+    return grid
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,lens,items", [
+    # blocks of 32 query tokens by shape (requests x blocks of the longest), or by rows where the lengths are scanned
+    (1, 1, [960 + r for r in range(17)] + [900], 18 * 31),        # 545 by rows: late blocks of all requests first
+    (2, 2, [915, 1044, 986, 956, 963, 1042], 6 * 33),             # 196
+    (8, 1, [1600, 1000], 2 * 50),                                 # 85: less than 15 % of the grid
+    (8, 1, [1600, 900], 78 + 4),                                  # 82 of 100
+    (2, 1, [1600, 900], 2 * 50),                                  # ... of a grid that the chip holds at once
+    (8, 8, [1600, 900], 2 * 50),                                  # ... where a request's pairs reach all XCDs
+    (8, 1, [700, 90], 24 + 4),                                    # of 44: a good part
+])
+def test_which_batches_the_key_split_kernel_scans(n_qh, n_kvh, lens, items):
+    # (pairs of a block and a key/value head come in eights)
+    assert grid_of(n_qh, n_kvh, lens, 2) == (items * n_kvh + 7) // 8 * 8 * (n_qh // n_kvh)
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,lens,items", [
+    (32, 8, [2133, 1066], 49 + 4),                         # blocks of 64: of 68, long chains
+    (32, 8, [2133, 1900], 2 * 34),                         # 66: less than a tenth
+    (40, 8, [227] * 38 + [297], 39 * 10),                  # blocks of 32: 356, many rounds of short chains
+    (64, 16, [501] + [250] * 23, 24 * 8),                  # 145 of 192, the same
+    (64, 16, [501] + [200] * 23, 79 + 48),                 # of 192: a good part anyway
+])
+def test_which_batches_the_shared_tile_kernel_scans(n_qh, n_kvh, lens, items):
+    assert grid_of(n_qh, n_kvh, lens, 1) == items * n_kvh             # (all heads of a group in one workgroup)
