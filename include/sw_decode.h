@@ -251,10 +251,13 @@ int sw_advance_lens(int32_t *seq_lens, int n_req, int max_len, void *stream);
  *   n_tokens   rows of q and out (0 returns SW_OK without touching the device).
  *   head_dim must be 128 (SW_ERR_UNSUPPORTED otherwise); n_qh / n_kvh at most 64.
  * One kernel, no workspace; asynchrony, ownership and the other errors as in
- * sw_decode_attn.  Which of the library's prompt kernels runs depends on the call's
- * size (n_tokens, n_req, the head counts); they sum in different orders, so a prompt's
- * result may differ in the last bits between a small and a large batch.  Under any of
- * them it does not depend on the other requests of the batch.  The launch is sized by
+ * sw_decode_attn.  Which of the library's prompt kernels runs, and whether the key-split
+ * one has four or eight waves, depends on the call's size (n_tokens, n_req, the head
+ * counts); they sum in different orders, so a prompt's result may differ in the last
+ * bits between a small and a large batch.  Under any one of them, of one number of
+ * waves, it does not depend on the other requests of the batch; SW_PARAM_PREFILL_KERNEL
+ * and, for the key-split kernel, SW_PARAM_PREFILL_WAVES with it fix one for calls of
+ * every size.  The launch is sized by
  * the smaller of n_req * max_len and about n_tokens + 64 * n_req query tokens, so a
  * batch of a few long and many short prompts costs what its tokens cost.  Weights enter
  * the second matrix product rounded to binary16 (the normaliser is the sum, in binary32,
@@ -272,7 +275,8 @@ int sw_prefill_attn(const void *q, const void *k_cache, const void *v_cache,
  * its LAST nq_r cached tokens as queries, nq_r = clamp(q_lens[r], 0, min(L_r,
  * max_q_len)); query i (row q_starts[r] + i of q and out) is the token at position
  * L_r - nq_r + i and attends to positions 0 .. L_r - nq_r + i.  nq_r = L_r is a whole
- * prompt (sw_prefill_attn is this call with q_lens = all of them), nq_r = 1 a request in
+ * prompt (sw_prefill_attn is this call with q_lens = all of them; the kernel that the
+ * size chooses, and with it the last bits, may be another), nq_r = 1 a request in
  * its token phase, values between a prompt processed in pieces.  The K/V rows of the
  * query tokens are already in the cache, as in sw_prefill_attn.
  *   q_lens      DEVICE int32 [n_req], 4-byte aligned.
@@ -454,7 +458,10 @@ int sw_device_status(int *gave_up);
  *   SW_PARAM_PREFILL_WAVES  prompt-phase kernel: waves (32 query positions each) per
  *                      head in a workgroup (0 = library default; ignored if heads *
  *                      waves would exceed 8).  For the key-split kernel: waves per
- *                      workgroup, 2, 4 or 8.  (With either set, the default choice is
+ *                      workgroup, 2, 4 or 8 (default: 4, in sw_prefill_attn 8 where few
+ *                      workgroups walk long prompts; which of them is part of what a
+ *                      result's last bits depend on, also with the kernel forced).
+ *                      (With either of the two parameters set, the default choice is
  *                      between the two kernels below.)
  *   SW_PARAM_PREFILL_KERNEL  0 = library default (one of these two, or, for one or a few
  *                      long prompts, the first one's form with the keys in two halves,

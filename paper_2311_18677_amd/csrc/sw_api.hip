@@ -833,8 +833,9 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     // of its own and splits its keys among the waves: four times the workgroups, each a quarter
     // as long, but no tile is shared.  Measured crossover: about 300 eight-wave workgroups, i.e.
     // query tokens x heads of about 77000 (one 12288-token prompt or ten 1024-token prompts at 8
-    // heads); less for batches of short prompts.  The choice looks at the call's number of query tokens, which the host knows; inside either kernel
-    // a request's result does not depend on the rest of its batch.
+    // heads); less for batches of short prompts.  The choice looks at the call's number of query tokens, which the host knows; inside either kernel,
+    // the key-split one at one number of waves (split_waves_for looks at the same sizes), a
+    // request's result does not depend on the rest of its batch.
     int shared_hp, shared_qw;
     sw_prefill_shape(a.group, 8, &shared_hp, &shared_qw);
     int which, knob_hp, knob_qw, knob_merge, halves_hp = 1, halves_qw = 1;

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2311_18677_amd import binding as sw
-from helpers import assert_parity
+from helpers import MAX_ABS, MAX_REL_L2, assert_parity, parity_errors
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,51 @@ def test_waves_by_size(n_qh, n_kvh, lens, waves):
             ref = oracle.decode_attn(qs, k_host, v_host, at, n, n_qh, n_kvh, 128, max_len, lay.stride_req, lay.stride_kvh,
                                      lay.stride_tok)
             assert_parity(got[row:row + 1], ref[r:r + 1], "request %d token %d" % (r, t))
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,L,others", [
+    (2, 1, 1000, [1000] * 11),                              # 64 workgroups alone, 750 in the batch
+    (2, 1, 4000, [4000, 3990, 17]),
+    (8, 2, 1150, [64, 1]),                                  # the batch's mean is below the rule's line
+    (1, 1, 9000, [8990, 9000]),
+])
+def test_a_prompt_alone_and_in_a_batch_on_the_other_side_of_the_rule(n_qh, n_kvh, L, others):
+    """With kernel and waves named, the prompt's rows have the same bits; by default, where the two calls take eight
+    and four waves, they are the named ones' of those numbers, within the parity bounds."""
+    lens = [L] + others
+    n, tot, max_len = len(lens), sum(lens), max(lens)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(tot)
+    lay = sw.sw_kv_layout(n, n_kvh, 128, max_len)
+    k, v = (torch.randn(lay.total_elems, generator=gen, dtype=torch.float16, device="cuda:0") for _ in range(2))
+    q = torch.randn(tot, n_qh, 128, generator=gen, dtype=torch.float16, device="cuda:0")
+    starts = [sum(lens[:r]) for r in range(n)]
+
+    def rows(kernel, waves):
+        batch, alone = torch.full_like(q, float("nan")), torch.full_like(q[:L], float("nan"))
+        sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, kernel)
+        sw.sw_set_param(sw.SW_PARAM_PREFILL_WAVES, waves)
+        try:
+            sw.sw_prefill_attn(q, k, v, i32(lens), i32(starts), batch, tot, n, n_qh, n_kvh, 128, max_len)
+            sw.sw_prefill_attn(q[:L], k, v, i32([L]), i32([0]), alone, L, 1, n_qh, n_kvh, 128, max_len)
+            torch.cuda.synchronize()
+        finally:
+            sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, 0)
+            sw.sw_set_param(sw.SW_PARAM_PREFILL_WAVES, 0)
+        assert not torch.isnan(batch).any()
+        return batch[:L].view(torch.int16), alone.view(torch.int16)
+    named = {}
+    for waves in (4, 8):
+        batch, alone = rows(2, waves)
+        assert torch.equal(batch, alone)
+        named[waves] = alone
+    assert not torch.equal(named[4], named[8])
+    batch, alone = rows(1, 0)
+    assert torch.equal(batch, alone)
+    for kernel in (0, 2):
+        batch, alone = rows(kernel, 0)
+        assert torch.equal(alone, named[8]) and torch.equal(batch, named[4])
+    # either is within the bound of the exact rows, so the two are within twice the bound of each other
+    four, eight = (named[w].view(torch.float16).cpu().numpy() for w in (4, 8))
+    max_abs, rel, _ = parity_errors(four, eight.astype(np.float64))
+    assert max_abs <= 2 * MAX_ABS and rel <= 2 * MAX_REL_L2
