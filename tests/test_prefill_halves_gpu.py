@@ -1,5 +1,6 @@
-"""The prompt kernel that takes a long prompt's keys in two halves (the default for one prompt of
-432 to 512 of its workgroups, and somewhat beyond for long ones): where it serves and where not, one query head per workgroup column, two, four, ragged last
+"""The prompt kernel that takes a long prompt's keys in two halves (the default for one request of
+432 to 512 of its workgroups, somewhat beyond for long ones, a whole prompt from 336 on, and batches of whole prompts
+of 448 to 512, for which see also test_prefill_order_gpu.py): where it serves and where not, one query head per workgroup column, two, four, ragged last
 tiles and query blocks, prompts with earlier context, block tables of every addressing kind, and
 keys scaled by 8 (maxima raised late, rows of a single key).
 Tolerance: the library's parity bound against the oracle; over block tables the same bits as dense."""

@@ -128,3 +128,61 @@ def test_which_batches_the_key_split_kernel_scans(n_qh, n_kvh, lens, items):
 ])
 def test_which_batches_the_shared_tile_kernel_scans(n_qh, n_kvh, lens, items):
     assert grid_of(n_qh, n_kvh, lens, 1) == items * n_kvh             # (all heads of a group in one workgroup)
+
+
+def exact_rows(q, k, v, lay, r, L, first, n_qh, n_kvh):
+    """Request r's rows from position `first` on, in 64 bits: q its query rows [L - first, n_qh, 128]."""
+    rows = [x.as_strided((n_kvh, L, 128), (lay.stride_kvh, lay.stride_tok, 1), r * lay.stride_req).double() for x in (k, v)]
+    ref = torch.empty(L - first, n_qh, 128, dtype=torch.float64, device=q.device)
+    for h in range(n_qh):
+        kt, vg = rows[0][h // (n_qh // n_kvh)].t().contiguous(), rows[1][h // (n_qh // n_kvh)].contiguous()
+        for a in range(0, L - first, 1024):
+            b = min(a + 1024, L - first)
+            later = torch.arange(L, device=q.device)[None, :] > (first + torch.arange(a, b, device=q.device))[:, None]
+            ref[a:b, h] = torch.softmax((q[a:b, h].double().contiguous() @ kt / 128 ** 0.5).masked_fill_(later, -float("inf")), dim=-1) @ vg
+    return ref
+
+
+# cut: query rows that the first and the last request lack
+@pytest.mark.parametrize("n_qh,n_kvh,lens,cut", [
+    (16, 1, [3400, 133, 500], (0, 0)), (16, 1, [3400, 133, 500], (100, 70)),        # one column of waves a head: blocks of 32
+    (32, 8, [1910, 136], (0, 0)), (32, 8, [1910, 136], (34, 10)),
+    (8, 1, [5000, 1, 33, 700, 1500, 64, 400], (0, 0)), (8, 1, [5000, 1, 33, 700, 1500, 64, 400], (99, 71)),
+    (4, 2, [9000, 6000, 65, 1, 300], (0, 0)), (4, 2, [9000, 6000, 65, 1, 300], (200, 64)),         # two: of 64
+    (8, 8, [4000, 130, 2700, 1000], (0, 0)), (8, 8, [4000, 130, 2700, 1000], (300, 128)),          # four: of 128
+])
+def test_every_row_of_an_uneven_batch_in_the_halves_kernel(n_qh, n_kvh, lens, cut):
+    """Blocks of several requests numbered by work: every row is written and within the parity bound of 64 bits, rows
+    outside [0, n_tokens) are left out, and block tables give the same bits."""
+    n, max_len, bs = len(lens), max(lens), 16
+    tot = sum(lens) - sum(cut)
+    starts = [sum(lens[:r]) - cut[0] for r in range(n)]
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(tot)
+
+    def rand(*shape):
+        return torch.randn(*shape, generator=gen, dtype=torch.float16, device="cuda:0")
+    lay = sw.sw_kv_layout(n, n_kvh, 128, max_len)
+    k, v, q = rand(lay.total_elems), rand(lay.total_elems), rand(tot, n_qh, 128)
+    out, paged = torch.zeros_like(q), torch.full_like(q, float("nan"))
+    seq, first = i32(lens), i32(starts)
+
+    def call():
+        sw.sw_prefill_attn(q, k, v, seq, first, out, tot, n, n_qh, n_kvh, 128, max_len)
+    assert serving_kernel(call, out) == 3
+    out.fill_(float("nan"))
+    call()
+    for r, L in enumerate(lens):
+        lo, hi = max(0, -starts[r]), min(L, tot - starts[r])
+        if hi > lo:
+            # (the rows that are missing at the end attend to nothing that the others see)
+            ref = exact_rows(q[starts[r] + lo:starts[r] + hi], k, v, lay, r, hi, lo, n_qh, n_kvh)
+            assert_parity(out[starts[r] + lo:starts[r] + hi].cpu().numpy(), ref.cpu().numpy(), "request %d" % r)
+    mb = -(-max_len // bs)
+    lay_p = sw.sw_kv_paged_layout(n * mb, n_kvh, 128, bs)
+    table = torch.randperm(n * mb, generator=gen, device="cuda:0").to(torch.int32).view(n, mb).contiguous()
+    kp, vp = rand(lay_p.total_elems), rand(lay_p.total_elems)
+    sw.sw_kv_unpack(k, v, table, seq, kp, vp, n, n_kvh, 128, max_len, bs, mb, n * mb)
+    sw.sw_prefill_attn_paged(q, kp, vp, table, seq, first, paged, tot, n, n_qh, n_kvh, 128, bs, mb, n * mb)
+    torch.cuda.synchronize()
+    assert torch.equal(paged.view(torch.int16), out.view(torch.int16))
