@@ -422,8 +422,8 @@ def main_prefill(args):
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": MFMA_F16_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / MFMA_F16_PEAK_TFLOPS,
                      "traffic": None if args.paged else read_traffic(cfg.name, "pmc_prefill.txt"),
-                     "kernel": "prompt kernel (sw_prefill_split_kernel below about 77000 query tokens x heads, "
-                               "sw_prefill_mfma_kernel from there)", "kernel_us": kernel_us,
+                     "kernel": "prompt kernel (sw_prefill_split_kernel for small calls, sw_prefill_halves_kernel for one "
+                               "or a few long prompts, sw_prefill_mfma_kernel for large calls)", "kernel_us": kernel_us,
                      "flops_per_launch": flops, "launches_timed": n_rec},
         "cpu_baseline": cpu_baseline,
         "parity_set0": parity,

@@ -360,16 +360,15 @@ __device__ __forceinline__ void mask_tile(float4_t (&s)[2][2], int q0, int t0, i
                 if (t0 + 16 * tb + 4 * gq + i > q0 + 16 * nb + n16) s[nb][tb][i] = -INFINITY;
 }
 
-// Sum of two binary16 values onto a binary32 one, each exactly as it is (v_fma_mix_f32 with one
-// for the other factor; opaque, or the compiler takes the product away and converts by itself).
-// Not one more matrix product with ones in V's place, which the shared-tile kernel took before: two of
-// its 34 matrix instructions a tile, on a chip whose clock gives way under them (one prompt of 32768
-// tokens, 8 heads on one, with its cache store: 2043 -> 1945 us; of 16384 532 -> 503; 16 of 100 to 1900
-// 96 -> 90.5).
-// DOT: the two-element dot product, which does it in one instruction and rounds alike, but waits until
-// the SIMD's matrix pipe is empty: 64 of them made no headway beside another wave's matrix
-// instructions, where 64 mixed multiply-adds took 430 cycles for 312 alone.  For the key-split
-// kernel, whose long chains have a SIMD to themselves (2 heads on one, 4096 tokens: 31.0 us against 31.3).
+// Sum of two binary16 values onto a binary32 one, each taken as it is and the sum rounded to binary32
+// (v_fma_mix_f32 with one for the other factor; opaque, or the compiler takes the product away and
+// converts by itself).  Not one more matrix product with ones in V's place, which the shared-tile kernel
+// took before: two of 34 matrix instructions a tile, on a chip whose clock gives way under them (one prompt
+// of 32768 tokens, 8 heads on one, with its cache store: 5 to 6 % in three sessions, 2043 -> 1945 us in one; of
+// 16384 532 -> 503; 16 of 100 to 1900 96 -> 90.5).
+// DOT: the two-element dot product, one instruction for two, in the key-split kernel.  The bits were the same
+// in 500 calls of 1 to 64 heads, 1 to 20000 tokens; time without it over time with it 0.97 to 1.02, in the mean
+// 1.002, and 1.008 where eight waves walk long chains.
 template <bool DOT>
 __device__ __forceinline__ float add_halves(half2_t w, float one, float sum)
 {

@@ -15,8 +15,8 @@
 // waves of a SIMD fill each other's gaps.  (With the first product of the next tile beside the softmax
 // of this one a step took 1.06 us instead of 0.95: that form has all eight waves wait for the same
 // LDS reads behind the barrier, before their first matrix instruction.)  K operands are read two
-// 32-dim steps, V operands three 16-dim blocks ahead of their products, and no further: all sixteen
-// of either held at once cost 30 registers and 4 us of a call.
+// 32-dim steps, V operands three 16-dim blocks ahead of their products, and no further, which would
+// take registers.
 // The tiles are requested by inline assembly: with the builtin the compiler's wait-count pass holds the
 // transposing LDS reads until ALL outstanding requests have landed.  The waits below count
 // exactly instead; no other vector-memory operation is issued inside the loop.
@@ -30,8 +30,9 @@
 //
 // Measured (8 heads on one key/value head, with the cache store before it): one prompt of 8192
 // tokens 147 us where the next tile's product ran beside the softmax 156, key-split 186.  What bounds
-// it: a SIMD's matrix and vector instructions, which share its issue slots (1290 cycles a step
-// for two waves, of about 2100), and staging two tiles per step (16 us of a call).
+// it: the two waves of a SIMD and their waits.  By the counters of that call the matrix pipes are busy 35 %
+// and the vector ALU 39 % of the SIMD cycles (32 and about 124 instructions a tile), and of its resident
+// time a wave issues 34 %, waits for data or at the barrier 30 % and is ready but not picked 35 %.
 #include "sw_prefill_common.h"
 
 #include <type_traits>
