@@ -33,7 +33,7 @@ constexpr long long kPrefillSharedMinGroups = 300;
 //   the whole form's and tiles are shared, which the key-split kernel does not do.  Time of the
 //   other kernels over this one's, 1 to 64 heads: 1.02 to 1.25 for prompts from 865 tokens on, up
 //   to 1.26 behind earlier context; groups of five and seven, where the whole form's workgroups
-//   have as few waves, 1.06 to 1.7.  A whole prompt from 336 on: 0.95 to 1.13 at 336 to 384, 1.04 to
+//   have as few waves, 1.06 to 1.7.  A whole prompt from 336 on: 0.93 to 1.13 at 336 to 384, 1.04 to
 //   1.69 above (8 heads on one, 6656 tokens: 130 -> 105 us); 0.98 to 1.06 at 320, less below.  With one head a
 //   workgroup and so blocks of 128 positions only from 1500 tokens on: a short prompt has few of them, the last
 //   partly empty (700 tokens 0.79 to 0.99, 1100 0.92 to 1.16; 56 heads on 8, 800: 24.7 -> 28.8 us).

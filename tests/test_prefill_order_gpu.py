@@ -1,7 +1,8 @@
-"""Items of a batch found by a scan of the lengths, numbered by work (shared-tile kernel) or request by
+"""Items of a batch found by a scan of the lengths, numbered by work (shared-tile and halves kernels) or request by
 request: every query block of every request is served once, whatever the lengths.  Rows are those of the request in a call
 of its own, bit for bit (one request is numbered as it comes); 65 requests take the other numbering.
-And the kernel that serves prompts of one or two rounds of the halves kernel's workgroups."""
+And the kernel that serves prompts of one or two rounds of the halves kernel's workgroups, and which batches are
+scanned."""
 import numpy as np
 import pytest
 import torch
