@@ -105,9 +105,10 @@ __device__ __forceinline__ int wave_max(int x)
 // The same with the items of all requests numbered by work, longest first (one request per lane,
 // n_req <= 64), for the kernels whose workgroups have a compute unit each: their time ends with
 // the last workgroups, and with the requests one after the other those were the last request's, its
-// longest blocks among them (which batches take it: sw_prefill_items_by_work).  A block's work is the position it ends at: its level, in blocks.  Levels
-// are taken in up to 64 bands of 2^sh (finer ones gain nothing), the band that holds the item is
-// found by bisection, a scan over the requests a step, and inside a band the requests follow each other.
+// longest blocks among them (which batches take it: sw_prefill_items_by_work).  A block's work is
+// the position it ends at: its level, in blocks.  Levels are taken in up to 64 bands of 2^sh (finer
+// ones gain nothing), the band that holds the item is found by bisection, a scan over the requests
+// a step, and inside a band the requests follow each other.
 // With the cache store, 8 heads on one: 16 prompts of 100 to 1900 tokens 89.5 -> 70.5 us, 4 of 500 to
 // 8000 234 -> 207, 3 of 4000 to 9000 343 -> 284; 32 heads on 8, 16 of 48 to 880 90.2 -> 83.3; 16
 // heads on one, 12 of 1258 to 3776 388 -> 378.  The key-split kernel's workgroups, two to a compute
