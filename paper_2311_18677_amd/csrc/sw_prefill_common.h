@@ -444,51 +444,6 @@ __device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_
     weights_block<DOT>(s, scale_log2e, -m * scale_log2e, p, psum);
 }
 
-// Online softmax of one tile, base 2, for one query block.  m[] is kept in raw score
-// units; the scale enters through one fused multiply-add.  `diagonal`: some position of
-// the tile is later than some query of the wave (q0 = the wave's first query, t0 = the
-// tile's first position).
-__device__ __forceinline__ void softmax_block(int nb, const float4_t (&sacc)[2][2], bool diagonal, int q0, int t0,
-                                              int n16, int gq, float scale_log2e, float lazy_raw,
-                                              float (&m)[2], float (&l)[2], float4_t (&o)[2][8], Frag (&p)[2])
-{
-    {
-        float s[8];
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[4 * tb + i] = sacc[nb][tb][i];
-        if (diagonal) {
-            const int qpos = q0 + 16 * nb + n16;
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (t0 + 16 * tb + 4 * gq + i > qpos) s[4 * tb + i] = -INFINITY;
-        }
-        // Optimistic pass: weights against the running maximum as it stands.  While every
-        // lane's eight weights sum to at most 8 * 2^kLazyBits nothing has to change -- no
-        // weight exceeds that bound (fine for binary16, whose precision is relative) and the
-        // tile's own maximum is never needed.  A larger (or infinite, or NaN) sum in any
-        // lane sends the whole wave through the exact pass below; sums above the bound
-        // imply a score more than 2^kLazyBits above the maximum, so that pass raises it.
-        float4_t sv[2] = {float4_t{s[0], s[1], s[2], s[3]}, float4_t{s[4], s[5], s[6], s[7]}};
-        float psum;
-        weights_block(sv, scale_log2e, -m[nb] * scale_log2e, p[nb], psum);
-        if (__builtin_amdgcn_ballot_w64(!(psum <= kSumBound)) != 0)       // rare after the first tiles
-            raise_block(sv, scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum);
-        l[nb] += psum;
-    }
-}
-
-// O^T += V^T P^T for one query block.
-__device__ __forceinline__ void pv_block(int nb, const Frag (&va)[8], const Frag (&p)[2], float4_t (&o)[2][8])
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[nb].h, o[nb][e], 0, 0, 0);
-}
-
 // 64 lanes x 16 bytes, global -> LDS, asynchronously: lane l's bytes (at base + off, base
 // wave-uniform) land at LDS offset lds_at + 16 l.  Inline assembly, because the compiler's
 // wait-count pass holds an LDS read that may alias a pending request of the builtin form (every
@@ -532,5 +487,117 @@ __device__ __forceinline__ unsigned lds_offset(const void *p)
 {
     return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
 }
+
+// The block table is read-only for the whole launch; reading it through the constant
+// address space lets wave-uniform entries come in over the scalar path.
+typedef const __attribute__((address_space(4))) int32_t *const_table_t;
+
+// A moving wave of the kernels that share staged tiles: it requests tiles and does nothing else.
+// Requests are dealt to MOVERS such waves and not to the waves that compute, because these walk in step
+// behind a barrier: dealt to them, every wave stands at the 16-cycle issue of all the others' requests before
+// its first product (a tile's 16 requests took 7 % of the shared-tile kernel's time, in the form with
+// two tiles a step twice that), and does the address arithmetic and the table reads between its products.
+// A step is TILES consecutive tiles of K and of V.  Row group j of a step is rows 4(j%8) .. +3 of tile j/8:
+// one request for K (16-byte pieces XOR-swizzled by row), one for V (by pairs of rows).
+template <bool PAGED, int MOVERS, int TILES>
+struct TileMover {
+    static constexpr int C = 8 * TILES / MOVERS;       // row groups of a step that are this wave's
+    static constexpr int kRequests = 2 * C;            // requests of a step
+    static_assert(C * MOVERS == 8 * TILES, "row groups go round");
+    const SwPrefillArgs &a;
+    const char *kslab, *vslab;                         // settled
+    const_table_t table;
+    int L, mover, gq, n16, in_block;
+    // this lane's byte offsets where a tile lies in the context whole: dense, inside the step's
+    // tiles; block table, inside a pool block.  And where a request lands behind the step's first byte.
+    unsigned k_off[C], v_off[C], at[C];
+
+    __device__ __forceinline__ TileMover(const SwPrefillArgs &args, const char *k, const char *v, const_table_t t, int len,
+                                         int which, int lane)
+        : a(args), kslab(k), vslab(v), table(t), L(len), mover(which), gq(lane >> 4), n16(lane & 15),
+          in_block(PAGED ? (1 << args.block_shift) - 1 : ~0)
+    {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int j = mover + MOVERS * c;
+            const int rho = 4 * (j & 7) + gq;
+            const unsigned row = PAGED ? (unsigned)(rho & in_block) * kRowBytes
+                                       : (unsigned)((j >> 3) * kTileBytes + rho * kRowBytes);
+            k_off[c] = row | (unsigned)((n16 ^ (rho & 15)) << 4);
+            v_off[c] = row | (unsigned)((n16 ^ v_swizzle(rho)) << 4);
+            at[c] = (unsigned)__builtin_amdgcn_readfirstlane(j * 1024);
+            asm volatile("" : "+s"(at[c]));
+        }
+    }
+
+    // This wave's share of step st -> LDS, K tiles from k_to on, V tiles from v_to on.
+    __device__ __forceinline__ void request(int st, unsigned k_to, unsigned v_to) const
+    {
+        const bool whole = (st + 1) * (TILES * kTile) <= L;
+        if (!PAGED && whole) {
+            const unsigned tile = (unsigned)st * (TILES * kTileBytes);
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                request_1k<true>(kslab, tile + k_off[c], at[c] + k_to);
+                request_1k<true>(vslab, tile + v_off[c], at[c] + v_to);
+            }
+            return;
+        }
+        // block table: the four rows of a request share a pool block (blocks hold a multiple of four
+        // positions, tiles start at multiples of 32): one wave-uniform table read for K and V, the id
+        // clamped into the pool
+        long long block_off[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int j = mover + MOVERS * c;
+            block_off[c] = PAGED ? table[min((st * TILES + (j >> 3)) * kTile + 4 * (j & 7), L - 1) >> a.block_shift] : 0;
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (!PAGED) continue;
+            int id = (int)block_off[c];
+            id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
+            block_off[c] = 2 * (long long)id * a.stride_block;
+        }
+        if (PAGED && whole) {
+            // row (t0 + rho) % block_size of a block is t0 % block_size + rho % block_size: t0 is a multiple of 32
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int t0 = (st * TILES + ((mover + MOVERS * c) >> 3)) * kTile;
+                const long long off = block_off[c] + (long long)(((unsigned)t0 & (unsigned)in_block) * kRowBytes);
+                request_1k<false>(kslab + off, k_off[c], at[c] + k_to);
+                request_1k<false>(vslab + off, v_off[c], at[c] + v_to);
+            }
+            return;
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int j = mover + MOVERS * c;
+            const int rho = 4 * (j & 7) + gq;
+            const int t = min((st * TILES + (j >> 3)) * kTile + rho, L - 1);       // rows past the prompt repeat its last row
+            const unsigned row = ((unsigned)t & (unsigned)in_block) << 8;
+            request_1k<!PAGED>(kslab + block_off[c], row | (unsigned)((n16 ^ (rho & 15)) << 4), at[c] + k_to);
+            request_1k<!PAGED>(vslab + block_off[c], row | (unsigned)((n16 ^ v_swizzle(rho)) << 4), at[c] + v_to);
+        }
+    }
+
+    // All n_steps of them, three ring slots: of step i, K lands at k_ring + (i % 3) * stride, V likewise.
+    // One barrier a step, behind which every wave may read step i and this one fills the slot of step i - 1.
+    __device__ __forceinline__ void walk(int n_steps, unsigned k_ring, unsigned v_ring, unsigned stride) const
+    {
+        request(0, k_ring, v_ring);
+        if (n_steps > 1) request(1, k_ring + stride, v_ring + stride);
+        unsigned ahead = 2 * stride;                   // slot of step i + 2
+        for (int i = 0; i < n_steps; ++i) {
+            // this wave's requests of step i have landed (those of step i + 1 may be in flight)
+            if (i + 1 < n_steps) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kRequests));
+            else                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (i + 2 < n_steps) request(i + 2, k_ring + ahead, v_ring + ahead);
+            ahead = ahead == 2 * stride ? 0 : ahead + stride;
+        }
+    }
+};
 
 }  // namespace sw_prefill

@@ -16,6 +16,19 @@
 // Each lane therefore owns one query position: its running maximum, its sum and
 // its causal bound are per-lane scalars, and its output row is stored straight
 // from the accumulators.
+//
+// Two further waves request the tiles (TileMover in sw_prefill_common.h); the others only read LDS, multiply
+// and weigh.  What bounds a computing wave is its own chain: 32 matrix instructions of 16 cycles, about
+// 95 vector instructions of about 8 (a wave alone cannot issue them faster) and the LDS reads between
+// them, with two such waves to a SIMD that a barrier keeps in step.  Behind it, on long calls, power: with all
+// inputs zero one prompt of 32768 tokens takes 1.54 ms.
+// Measured (8 heads on one, attention alone) against requests dealt to the computing waves: one prompt of 32768 tokens
+// 1920 -> 1800 to 1860 us, of 16384 500 -> 473, 12 of 618 to 8039 560 -> 527; 8 heads on 8, 8 of 1024
+// 36.1 -> 32.7; over blocks of 16 positions one of 16384 559 -> 459, 16 of 1024 57.4 -> 48.7.  One moving wave
+// or four: dense within 1 % of two; over blocks of 4 positions one takes 8 % longer (its table reads).
+// Tried: both products' operands read before the first product (188 registers instead of 162), the
+// same; each product of one query block beside the other's weights 13 % slower; the first product at a raised
+// wave priority 4 % slower; the key range in thirds for twelve waves, three to a SIMD, 6 % slower.
 #include "sw_prefill_common.h"
 
 #include <type_traits>
@@ -26,21 +39,16 @@ using namespace sw_prefill;
 
 constexpr int kBufBytes = 2 * kTileBytes;          // K tile, then V tile
 constexpr int kBufs     = 3;
+constexpr int kMovers   = 2;                       // waves that only request tiles
 
-// The block table is read-only for the whole launch; reading it through the constant
-// address space lets wave-uniform entries come in over the scalar path.
-typedef const __attribute__((address_space(4))) int32_t *const_table_t;
-
-// NW = waves per workgroup = (query heads per workgroup) * (waves per head).
+// NW = computing waves per workgroup = (query heads per workgroup) * (waves per head); kMovers more
+// request the tiles.
 // PAGED: K and V are block pools addressed through the request's row of the block table
 // (position t = row t % block_size of pool block table[t / block_size]).
 template <int NW, bool PAGED>
-__global__ __launch_bounds__(64 * NW, 1)
+__global__ __launch_bounds__(64 * (NW + kMovers), 1)
 void sw_prefill_mfma_kernel(SwPrefillArgs a)
 {
-    // a tile's 16 one-kilobyte load instructions are dealt round-robin to the waves;
-    // every wave issues C of them per tile (the last may repeat instruction 15)
-    constexpr int C = (16 + NW - 1) / NW;
     __shared__ __attribute__((aligned(16))) unsigned char lds[kBufs * kBufBytes];
 
     // blockIdx -> (item = (request, query block), key/value head, block of hp query heads)
@@ -61,65 +69,33 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n16  = lane & 15;
     const int gq   = lane >> 4;
+
+    // dense: the (request, head) slab; block table: the head's rows inside pool block 0
+    const long long slab = PAGED ? (long long)g * a.stride_kvh : (long long)r * a.stride_req + (long long)g * a.stride_kvh;
+    const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * slab;
+    const char *vslab = reinterpret_cast<const char *>(a.v) + 2 * slab;
+    settled(kslab);
+    settled(vslab);
+    const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
+
+    // tiles the workgroup walks: up to the position of its last query
+    const int last_pos = P0 + min(Q0 + q_block, NQ) - 1;
+    const int n_tiles = last_pos / kTile + 1;
+
+    if (wave >= NW) {
+        const unsigned at = lds_offset(lds);
+        TileMover<PAGED, kMovers, 1>(a, kslab, vslab, table, L, wave - NW, lane).walk(n_tiles, at, at + kTileBytes, kBufBytes);
+        return;
+    }
+
     const int hh   = (int)hb * a.hp + wave % a.hp;   // query head within the group
     const int sb   = wave / a.hp;                // which 32 query positions of the block
     const int qw0  = Q0 + kQPerWave * sb;        // first query index of the wave ...
     const int aw0  = P0 + qw0;                   // ... and its position
     const int h    = g * a.group + hh;
 
-    // The staging area is filled by global->LDS loads only; one ordinary store keeps
-    // the compiler from treating it as never written.
-    *reinterpret_cast<uint4_t *>(lds + threadIdx.x * 16) = uint4_t{0u, 0u, 0u, 0u};
-    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0): the store is done before any load lands
-    __builtin_amdgcn_s_barrier();
-
-    // dense: the (request, head) slab; block table: the head's rows inside pool block 0
-    const long long slab = PAGED ? (long long)g * a.stride_kvh : (long long)r * a.stride_req + (long long)g * a.stride_kvh;
-    const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * slab;
-    const char *vslab = reinterpret_cast<const char *>(a.v) + 2 * slab;
-    const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
-    const int in_block = PAGED ? (1 << a.block_shift) - 1 : ~0;
-
-    // tiles the workgroup walks: up to the position of its last query
-    const int last_pos = P0 + min(Q0 + q_block, NQ) - 1;
-    const int n_tiles = last_pos / kTile + 1;
     // tiles this wave computes on: up to the position of its own last query
     const int my_tiles = qw0 < NQ ? min(aw0 + kQPerWave - 1, L - 1) / kTile + 1 : 0;
-
-    // this wave's share of tile ti's loads -> buffer ti % 3.  Instruction j < 8 is K rows
-    // 4j .. 4j+3 (16-byte pieces XOR-swizzled by row), j >= 8 is V rows 4(j-8) .. +3.
-    // (the buffer index is a compile-time constant everywhere: LDS addresses are then a
-    // per-lane value computed once plus an immediate offset, instead of two vector
-    // instructions per LDS read to add the rotating buffer's offset)
-    auto issue_tile = [&](int ti, auto buf_c) {
-        constexpr int B = decltype(buf_c)::value;
-        static_assert(B >= 0 && B < kBufs, "buffer index");
-        unsigned char *buf = lds + B * kBufBytes;
-        const int t0 = ti * kTile;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            int j = wave + NW * c;
-            j = j < 16 ? j : 15;
-            const int n = j & 7;
-            const bool is_v = j >= 8;
-            const int rho = 4 * n + gq;
-            const int t = min(t0 + rho, L - 1);                      // rows past the prompt repeat its last row
-            const int piece = is_v ? (n16 ^ v_swizzle(rho)) : (n16 ^ (rho & 15));
-            // block table: the four rows of an instruction share a pool block (blocks hold a
-            // multiple of four positions, tiles start at multiples of 32): one wave-uniform
-            // table read, the id clamped into the pool
-            long long block_off = 0;
-            if (PAGED) {
-                const int tu = min(t0 + 4 * n, L - 1);
-                int id = table[tu >> a.block_shift];
-                id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
-                block_off = 2 * (long long)id * a.stride_block;
-            }
-            const char *src = (is_v ? vslab : kslab) + block_off +
-                              ((((unsigned)t & (unsigned)in_block) << 8) | (unsigned)(piece << 4));
-            __builtin_amdgcn_global_load_lds(src, buf + (is_v ? kTileBytes : 0) + n * 1024, 16, 0, 0);
-        }
-    };
 
     unsigned vt_off[8];
     vt_offsets(n16, gq, vt_off);
@@ -132,44 +108,67 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[nb][e] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-    issue_tile(0, std::integral_constant<int, 0>{});
-    if (n_tiles > 1) issue_tile(1, std::integral_constant<int, 1>{});
-
-    // ---- Q^T operands.  Requested after the first tiles so that both latencies overlap;
-    // awaited here, once, so that no wait inside the loop has to cover them.
+    // ---- Q^T operands
     Frag qreg[2][4];
     load_q(a, q_first, qw0, NQ, h, n16, gq, qreg);
-
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qreg[nb][kk].u));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
 
     // One tile, staged in buffer B (= ti % kBufs, as a compile-time constant).
     auto step = [&](int ti, auto buf_c) {
         constexpr int B = decltype(buf_c)::value;
-        // this wave's loads of tile ti have landed (those of tile ti + 1 may be in flight) ...
-        if (ti + 1 < n_tiles) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C) & 0xc07f);
-        else                  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
-        // ... and so have everyone's; every wave has also finished reading tile ti - 1,
-        // whose buffer tile ti + 2 may now overwrite
+        // the tile has landed, and this wave is done with the one before
+        __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();
-        if (ti + 2 < n_tiles) issue_tile(ti + 2, std::integral_constant<int, (B + 2) % kBufs>{});
+        asm volatile("" ::: "memory");
         if (ti >= my_tiles) return;
 
         const unsigned char *kb = lds + B * kBufBytes;
         const unsigned char *vb = kb + kTileBytes;
         const int t0 = ti * kTile;
 
-        // The two query blocks are independent: the second block's vector work is placed
-        // behind the first block's matrix work so that the two units overlap within the wave.
+        // K operands are read two 32-dim steps, V operands three 16-dim blocks ahead of their
+        // products, and no further, which would take registers.
         float4_t sacc[2][2];
         qk_tile(kb, qreg, n16, gq, sacc);
-        const bool diagonal = t0 + kTile > aw0;
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);          // LDS reads of two 32-dim steps ...
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);      // ... products of one ...
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);      // ... reads of the one after next
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+        if (t0 + kTile > aw0) mask_tile(sacc, aw0, t0, n16, gq);
+        // Optimistic pass: weights against the running maximum as it stands; the exact pass where
+        // some lane's weights sum to more than kSumBound (rare after the first tiles).
         Frag p[2];
-        softmax_block(0, sacc, diagonal, aw0, t0, n16, gq, a.scale_log2e, lazy_raw, m, l, o, p);
+        float psum[2];
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) weights_block(sacc[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
+        if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+                raise_block(sacc[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum[nb]);
+        }
+        l[0] += psum[0];
+        l[1] += psum[1];
         Frag va[8];
         load_vt(vb, vt_off, va);
-        pv_block(0, va, p, o);
-        softmax_block(1, sacc, diagonal, aw0, t0, n16, gq, a.scale_log2e, lazy_raw, m, l, o, p);
-        pv_block(1, va, p, o);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+                o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[e].h, p[nb].h, o[nb][e], 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);          // LDS reads of three 16-dim blocks ahead
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
     };
     static_assert(kBufs == 3, "the loop below is unrolled by the number of buffers");
     for (int ti = 0; ti < n_tiles; ti += kBufs) {
@@ -233,8 +232,8 @@ hipError_t sw_launch_prefill_mfma(const SwPrefillArgs &a_in, hipStream_t stream,
     const dim3 grid((unsigned)blocks);
     const int nw = a.hp * a.qw;
 #define SW_PREFILL_CASE(W) \
-    if (nw == W) return a.block_table ? sw_launch(sw_prefill_mfma_kernel<W, true>, grid, dim3(64 * W), 0, stream, ev, a) \
-                                      : sw_launch(sw_prefill_mfma_kernel<W, false>, grid, dim3(64 * W), 0, stream, ev, a);
+    if (nw == W) return a.block_table ? sw_launch(sw_prefill_mfma_kernel<W, true>, grid, dim3(64 * (W + kMovers)), 0, stream, ev, a) \
+                                      : sw_launch(sw_prefill_mfma_kernel<W, false>, grid, dim3(64 * (W + kMovers)), 0, stream, ev, a);
     SW_PREFILL_CASE(8) SW_PREFILL_CASE(7) SW_PREFILL_CASE(6) SW_PREFILL_CASE(5)
     SW_PREFILL_CASE(4) SW_PREFILL_CASE(3) SW_PREFILL_CASE(2) SW_PREFILL_CASE(1)
 #undef SW_PREFILL_CASE

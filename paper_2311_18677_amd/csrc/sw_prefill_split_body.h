@@ -24,10 +24,6 @@ struct SplitLds {
 // Block-table variant: byte offset of the pool block behind each of a tile's 8 load instructions.
 struct TileBlocks { long long off[8]; };
 
-// The block table is read-only for the whole launch; reading it through the constant
-// address space lets wave-uniform entries come in over the scalar path.
-typedef const __attribute__((address_space(4))) int32_t *const_table_t;
-
 // PAGED: K and V are block pools addressed through the request's row of the block table
 // (position t = row t % block_size of pool block table[t / block_size]).  `block` is the
 // workgroup's number among the prompt workgroups.
