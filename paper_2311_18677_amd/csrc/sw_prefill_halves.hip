@@ -17,9 +17,9 @@
 // LDS reads behind the barrier, before their first matrix instruction.)  K operands are read two
 // 32-dim steps, V operands three 16-dim blocks ahead of their products, and no further, which would
 // take registers.
-// The tiles are requested by inline assembly: with the builtin the compiler's wait-count pass holds the
-// transposing LDS reads until ALL outstanding requests have landed.  The waits below count
-// exactly instead; no other vector-memory operation is issued inside the loop.
+// Four further waves request the tiles (TileMover in sw_prefill_common.h), 32 requests a step; dealt to the waves
+// that compute they held up all of these behind every barrier.  With two moving waves prompts over block
+// tables take up to 7 % longer, dense ones the same.
 //
 // Rounding.  Weights are binary16, relative to a maximum that a wave takes from its first tile, so
 // the largest weight of that tile is exact.  The key-split kernel has four such maxima for a row, here
@@ -28,11 +28,10 @@
 // multiply their first tile by the rest of its weights as well: 2.47e-4, rows behind 2600
 // and more positions are as far off as the key-split kernel's.  It takes 1 to 2 us of a call.
 //
-// Measured (8 heads on one key/value head, with the cache store before it): one prompt of 8192
-// tokens 147 us where the next tile's product ran beside the softmax 156, key-split 186.  What bounds
-// it: the two waves of a SIMD and their waits.  By the counters of that call the matrix pipes are busy 35 %
-// and the vector ALU 39 % of the SIMD cycles (32 and about 124 instructions a tile), and of its resident
-// time a wave issues 34 %, waits for data or at the barrier 30 % and is ready but not picked 35 %.
+// Measured (8 heads on one key/value head, attention alone): one prompt of 8192 tokens 144 us with the requests dealt to the
+// computing waves, 140 to 141 now, over blocks of 16 positions 163 -> 140, of 4 positions 180 -> 145; key-split 181.
+// What bounds it: the chain of a wave's own instructions, with two such waves to a SIMD (see sw_prefill_mfma.hip),
+// and power: 127 us with all inputs zero.  (A third of the keys for each of twelve computing waves: 145.)
 #include "sw_prefill_common.h"
 
 #include <type_traits>
@@ -41,18 +40,15 @@ namespace {
 
 using namespace sw_prefill;
 
+constexpr int kMovers = 4;        // waves that only request tiles
 constexpr int kBufs = 3;          // steps' worth of K and of V tiles in the staging rings
-
-// The block table is read-only for the whole launch; reading it through the constant
-// address space lets wave-uniform entries come in over the scalar path.
-typedef const __attribute__((address_space(4))) int32_t *const_table_t;
 
 // Eight waves = 2 * (query heads per workgroup) * (waves per head): wave w works on tile
 // 2 * i + w / 4 of step i.
 // PAGED: K and V are block pools addressed through the request's row of the block table
 // (position t = row t % block_size of pool block table[t / block_size]).
 template <bool PAGED>
-__global__ __launch_bounds__(512, 1)
+__global__ __launch_bounds__(512 + 64 * kMovers, 1)
 void sw_prefill_halves_kernel(SwPrefillArgs a)
 {
     constexpr int NW = 8;                             // waves
@@ -60,9 +56,6 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     constexpr int NC = NW / KS;                       // (query head, 32 positions) columns
     constexpr int kStepBytes = KS * kTileBytes;       // the K (or V) tiles of one step
     constexpr int kVBase = kBufs * kStepBytes;        // K ring, then V ring
-    // a step's 8 * KS one-kilobyte requests for K, and as many for V, are dealt round-robin to
-    // the waves; every wave issues C of each
-    constexpr int C = 8 * KS / NW;
     __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kBufs * kStepBytes];
 
     // blockIdx -> (item = (request, query block), key/value head, block of hp query heads)
@@ -83,14 +76,6 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n16  = lane & 15;
     const int gq   = lane >> 4;
-    const int kg   = wave / NC;                  // which of a step's KS tiles
-    const int col  = wave % NC;
-    const int hh   = (int)hb * a.hp + col % a.hp;    // query head within the group
-    const int sb   = col / a.hp;                 // which 32 query positions of the block
-    const int qw0  = Q0 + kQPerWave * sb;        // first query index of the wave ...
-    const int aw0  = P0 + qw0;                   // ... and its position
-    const int h    = g * a.group + hh;
-
     // dense: the (request, head) slab; block table: the head's rows inside pool block 0
     const long long slab = PAGED ? (long long)g * a.stride_kvh : (long long)r * a.stride_req + (long long)g * a.stride_kvh;
     const char *kslab = reinterpret_cast<const char *>(a.k) + 2 * slab;
@@ -98,50 +83,33 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     settled(kslab);
     settled(vslab);
     const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
-    const int in_block = PAGED ? (1 << a.block_shift) - 1 : ~0;
 
     // tiles the workgroup walks: up to the position of its last query
     const int last_pos = P0 + min(Q0 + q_block, NQ) - 1;
     const int n_steps = last_pos / (kTile * KS) + 1;
-    // steps this wave computes in: up to the position of its own last query
-    const int my_tiles = qw0 < NQ ? min(aw0 + kQPerWave - 1, L - 1) / kTile + 1 : 0;
-    const int my_steps = my_tiles > kg ? (my_tiles - kg + KS - 1) / KS : 0;
 
-    const unsigned lds0 = lds_offset(lds);
-
-    // This wave's share of step `st`'s K (or V) requests -> ring slot B.  Request j brings rows
-    // 4(j%8) .. +3 of tile j/8 (K pieces XOR-swizzled by row, V pieces by pairs of rows).
-    auto request = [&](int st, auto buf_c, auto is_v_c) __attribute__((always_inline)) {
-        constexpr int B = decltype(buf_c)::value;
-        constexpr bool IS_V = decltype(is_v_c)::value;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int j = wave + NW * c;
-            const int n = j & 7;
-            const int t0 = (st * KS + (j >> 3)) * kTile;
-            const int rho = 4 * n + gq;
-            const int t = min(t0 + rho, L - 1);                      // rows past the prompt repeat its last row
-            const int piece = IS_V ? (n16 ^ v_swizzle(rho)) : (n16 ^ (rho & 15));
-            // block table: the four rows of a request share a pool block (blocks hold a
-            // multiple of four positions, tiles start at multiples of 32): one wave-uniform
-            // table read, the id clamped into the pool
-            long long block_off = 0;
-            if (PAGED) {
-                const int tu = min(t0 + 4 * n, L - 1);
-                int id = table[tu >> a.block_shift];
-                id = id < 0 ? 0 : (id >= a.n_blocks ? a.n_blocks - 1 : id);
-                block_off = 2 * (long long)id * a.stride_block;
-            }
-            request_1k<!PAGED>((IS_V ? vslab : kslab) + block_off,
-                       (((unsigned)t & (unsigned)in_block) << 8) | (unsigned)(piece << 4),
-                       lds0 + (IS_V ? kVBase : 0) + B * kStepBytes + (j >> 3) * kTileBytes + n * 1024);
-        }
-    };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
-    using KTile = std::false_type;
-    using VTile = std::true_type;
+
+    if (wave >= NW) {
+        const unsigned at = lds_offset(lds);
+        TileMover<PAGED, kMovers, KS>(a, kslab, vslab, table, L, wave - NW, lane).walk(n_steps, at, at + kVBase, kStepBytes);
+        __syncthreads();                         // the two of the merge
+        __syncthreads();
+        return;
+    }
+
+    const int kg   = wave / NC;                  // which of a step's KS tiles
+    const int col  = wave % NC;
+    const int hh   = (int)hb * a.hp + col % a.hp;    // query head within the group
+    const int sb   = col / a.hp;                 // which 32 query positions of the block
+    const int qw0  = Q0 + kQPerWave * sb;        // first query index of the wave ...
+    const int aw0  = P0 + qw0;                   // ... and its position
+    const int h    = g * a.group + hh;
+    // steps this wave computes in: up to the position of its own last query
+    const int my_tiles = qw0 < NQ ? min(aw0 + kQPerWave - 1, L - 1) / kTile + 1 : 0;
+    const int my_steps = my_tiles > kg ? (my_tiles - kg + KS - 1) / KS : 0;
 
     unsigned vt_off[8];
     vt_offsets(n16, gq, vt_off);
@@ -154,13 +122,7 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[nb][e] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-    // ---- first tiles and Q^T operands, awaited together
-    request(0, I0{}, KTile{});
-    request(0, I0{}, VTile{});
-    if (n_steps > 1) {
-        request(1, I1{}, KTile{});
-        request(1, I1{}, VTile{});
-    }
+    // ---- Q^T operands
     Frag qreg[2][4];
     load_q(a, q_first, qw0, NQ, h, n16, gq, qreg);
 #pragma unroll
@@ -189,17 +151,10 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     // Step i, staged in ring slot B (= i % kBufs, as a compile-time constant).
     auto step = [&](int i, auto buf_c) __attribute__((always_inline)) {
         constexpr int B = decltype(buf_c)::value;
-        // this wave's share of step i has landed (that of step i + 1 may be in flight) ...
-        if (i + 1 < n_steps) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * C) & 0xc07f);
-        else                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
-        // ... and so has everyone's; every wave has also finished reading step i - 1,
-        // whose slot step i + 2 may now overwrite
+        // the step's tiles have landed, and this wave is done with the step before
+        __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (i + 2 < n_steps) {
-            request(i + 2, std::integral_constant<int, (B + 2) % kBufs>{}, KTile{});
-            request(i + 2, std::integral_constant<int, (B + 2) % kBufs>{}, VTile{});
-        }
         if (i >= my_steps) return;
         const unsigned char *kb = kmine + B * kStepBytes;
         const unsigned char *vb = vmine + B * kStepBytes;
@@ -269,6 +224,7 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     spoiled = __builtin_elementwise_fma((half2_t){v.h[2 * j], v.h[2 * j + 1]}, none, spoiled);
+                __builtin_amdgcn_sched_barrier(0);
             }
             if (__builtin_amdgcn_ballot_w64(!(spoiled[0] + spoiled[1] == (_Float16)0.f)) == 0) {
 #pragma unroll
@@ -278,8 +234,10 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
                     rest_block(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], rest, rsum);
                     l[nb] += rsum;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
+                    for (int e = 0; e < 8; ++e) {
                         o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v_operand(vb, e).h, rest.h, o[nb][e], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
         }
@@ -351,6 +309,6 @@ hipError_t sw_launch_prefill_halves(const SwPrefillArgs &a_in, hipStream_t strea
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     if (a.hp * a.qw != 4) return hipErrorInvalidValue;
-    return a.block_table ? sw_launch(sw_prefill_halves_kernel<true>, grid, dim3(512), 0, stream, ev, a)
-                         : sw_launch(sw_prefill_halves_kernel<false>, grid, dim3(512), 0, stream, ev, a);
+    return a.block_table ? sw_launch(sw_prefill_halves_kernel<true>, grid, dim3(512 + 64 * kMovers), 0, stream, ev, a)
+                         : sw_launch(sw_prefill_halves_kernel<false>, grid, dim3(512 + 64 * kMovers), 0, stream, ev, a);
 }
