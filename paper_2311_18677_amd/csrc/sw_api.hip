@@ -20,41 +20,72 @@ namespace {
 
 constexpr int kVersion = 200;   // 0.2.0
 
-// Workgroups of eight waves from which the shared-tile prompt kernel is the faster of the
-// two on long prompts (batches of short prompts switch earlier, see causal_attn).
-constexpr long long kPrefillSharedMinGroups = 300;
+// A prompt call as the host sees it, for the choice of a kernel.
+struct PromptCall {
+    long long avg_q;         // query tokens per request
+    int n_req;
+    int group;               // query heads to a key/value head
+    bool whole;              // every request's queries begin at position 0 ...
+    bool from_start;         // ... or nearly, as far as the host knows
+    long long blocks;        // workgroups of the halves kernel
+    long long groups;        // workgroups of the shared-tile kernel with whole heads in each ...
+    int group_waves;         // ... and their computing waves
+    long long full_groups;   // the same with eight waves in all of them
+};
 
-// Whether the shared-tile form with the key range in two halves serves a prompt call.  `blocks` is
-// the number of its workgroups, one to a compute unit at a time; `groups` counts the work in
-// workgroups of the whole form, `whole_waves` waves each; of this form's `columns` columns of waves `heads`
-// are query heads, the rest query positions; avg_q: query tokens per request; from_start: the queries
-// are known to begin (nearly) at position 0.
-//   One request, up to two rounds of workgroups (432 to 512 blocks): the chains are half as long as
+// Whether the shared-tile form with the key range in two halves serves a prompt call, one of its
+// workgroups to a compute unit at a time.
+//   One request, up to two rounds of workgroups (432 to 512): the chains are half as long as
 //   the whole form's and tiles are shared, which the key-split kernel does not do.  Time of the
-//   other kernels over this one's, 1 to 64 heads: 1.02 to 1.25 for prompts from 865 tokens on, up
-//   to 1.26 behind earlier context; groups of five and seven, where the whole form's workgroups
-//   have as few waves, 1.06 to 1.7.  A whole prompt from 336 on: 0.93 to 1.13 at 336 to 384, 1.04 to
-//   1.69 above (8 heads on one, 6656 tokens: 130 -> 105 us); 0.98 to 1.06 at 320, less below.  With one head a
-//   workgroup and so blocks of 128 positions only from 1500 tokens on: a short prompt has few of them, the last
-//   partly empty (700 tokens 0.79 to 0.99, 1100 0.92 to 1.16; 56 heads on 8, 800: 24.7 -> 28.8 us).
-//   Above two rounds the third is partly empty: behind earlier context (all chains alike) 0.92 to
-//   1.14, with short prompts 0.82 to 1.01.  Prompts of 4000 tokens and more have chains uneven
-//   enough to fill it: 1.03 to 1.25 up to 720 blocks, down to 0.96 at 790.
-//   Several requests: their lengths decide, which the host does not know (8 heads on one, 300 to
-//   340 groups: two of equal length 1.08 to 1.17, one twice the other 0.93 to 0.98).  Only where
-//   the whole form has fewer than eight waves does this one win throughout (1.01 to 2.1).  Whole
-//   prompts with their blocks numbered by work, 448 to 512 blocks: 0.93 to 1.39 from 1000 tokens a request
-//   on, in the mean 1.15, 0.74 to 1.12 with shorter ones; with blocks of 128 positions 1.00 to 2.3 from 1500 on, 0.88
-//   to 1.6 below (7 prompts of 1114 tokens, 8 heads on 8: 42 -> 48 us).
-// Groups of three heads make workgroups of six waves, which gain nothing (0.82 to 1.03).
-bool use_halves(long long blocks, long long groups, long long avg_q, int n_req, int heads, int columns, int whole_waves,
-                bool from_start, bool whole_prompts)
+//   other kernels over this one's, 1 to 64 heads: 1.12 to 1.26, a whole prompt from 336 on 1.00 to 1.26
+//   (8 heads on one, 6656 tokens: 127 -> 102 us); 1.00 to 1.04 at 316 to 334.  With odd groups only from
+//   1500 tokens on: an item has 128 positions, a short prompt few of them, the last partly empty.
+//   Above two rounds the third is partly empty, which prompts of 4000 tokens and more have chains uneven
+//   enough to fill: 1.20 to 1.22 up to 530 workgroups, 0.99 at 760.
+//   Several whole prompts, 130 batches of 1 to 64 heads, lengths alike to one ten times the other: 345 to 400
+//   workgroups 0.99 to 1.21, in the mean 1.07, from 1400 tokens a request on; 400 to 448 1.04 to 1.44 from 1100 on; 448 to
+//   512 0.87 to 1.25, in the mean 1.14, from 1000 on, 0.65 to 0.98 below; 512 to 580 1.02 to 1.28 from 2500 on, 0.64 to 0.98
+//   below; 580 to 680 1.00 to 1.28 from 4500 on, 0.70 to 1.21 below.  Beyond 0.64 to 1.20.  (Two prompts alike gain least
+//   below 448: 1.00 to 1.13, key-split up to there.)
+//   Several requests that may have earlier context: their lengths decide, which the host does not know.  Only where
+//   whole heads make workgroups of five or seven waves does this one win throughout (1.01 to 2.1).
+// Groups of three and six heads that may have earlier context stay with the other kernels (0.82 to 1.03 for six waves).
+bool use_halves(const PromptCall &c)
 {
-    if (columns != 4) return false;
-    if (whole_prompts && blocks <= 512 && (heads > 1 || avg_q >= 1500) &&
-        (n_req == 1 ? blocks >= 336 : blocks >= 448 && avg_q >= 1000 && whole_waves == 8)) return true;
-    if (n_req > 1) return whole_waves < 8 && avg_q >= 3000 && groups >= 300 && groups < (avg_q < 5000 ? 345 : 400);
-    return blocks >= 432 && (blocks <= 512 || (blocks <= 720 && avg_q >= 4000 && from_start));
+    const bool long_enough = c.group % 2 == 0 || c.group % 3 == 0 || c.avg_q >= 1500;
+    if (!c.whole && c.group % 3 == 0 && c.group % 4 != 0) return false;
+    if (c.n_req == 1) {
+        if (c.blocks <= 512) return c.blocks >= 432 || (c.whole && c.blocks >= 336 && long_enough);
+        return c.blocks <= 720 && c.avg_q >= 4000 && c.from_start;
+    }
+    if (!c.whole)
+        return c.group_waves < 8 && c.avg_q >= 3000 && c.groups >= 300 && c.groups < (c.avg_q < 5000 ? 345 : 400);
+    if (c.blocks > 512) return c.blocks <= 680 && c.avg_q >= (c.blocks <= 580 ? 2500 : 4500);
+    if (c.blocks >= 448) return c.avg_q >= 1000 && long_enough;
+    return c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough;
+}
+
+// Whether the shared-tile kernel is faster than the key-split one.
+//   Batches of three and more whole prompts, 1 to 64 heads, time of the key-split kernel over its: up to 512 tokens a request
+//   1.00 to 1.34 from 160 full workgroups on (0.92 at 152); up to 1024 0.95 to 1.33 from 192 on (0.76 to 1.04 below); up to
+//   2500 1.09 to 2.5 from 264 on (10 prompts of 1488, 5 heads on 5: 111 -> 44 us), above from 290.
+//   One or two prompts, and calls that may have earlier context or token-phase requests, about which the host
+//   knows less: 300 workgroups, 256 and 192 for short prompts.
+bool use_shared(const PromptCall &c)
+{
+    if (c.whole && c.n_req > 2)
+        return c.full_groups >= (c.avg_q <= 512 ? 160 : c.avg_q <= 1024 ? 192 : c.avg_q <= 2500 ? 264 : 290);
+    return c.groups >= (c.avg_q <= 256 ? 192 : c.avg_q <= 1024 ? 256 : 300);
+}
+
+// Whether the shared-tile kernel deals its columns flat (sw_prefill_flat_blocks), which matters for groups that are
+// no power of two.  avg_q: query tokens per request.  Time with whole heads over time flat: one prompt of
+// 17731 tokens, 6 heads on 2, 508 -> 463 us; 8 of 795 to 7954, 12 on 4, 614 -> 562; 8 of 2000 to 4000, 5 on one,
+// 135 -> 108; 13 of 1748 to 6993, 7 on one, 508 -> 490.  Short prompts have few items, which flat are of up to 256
+// positions: 24 of 300 to 600, 7 heads on one, 25.5 -> 29.0; 16 of 500 to 1000, 12 on 4, 57.5 -> 56.1.
+bool flat_columns(int group, long long avg_q)
+{
+    return (group & (group - 1)) == 0 || avg_q >= 1000;
 }
 
 // Waves a workgroup of the key-split prompt kernel has.  `items`: its workgroups, one per 32 query
@@ -827,18 +858,16 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     a.max_len = max_len;
     // Two kernels, the first in two forms (the other: see use_halves).  The shared-tile kernel
     // stages every K/V tile once for the eight waves of a workgroup (the heads of a group, or
-    // more query positions of one head) and runs at a steady 41-45 % of the matrix peak once
+    // more query positions of one head) and runs at a steady 45-49 % of the matrix peak once
     // its workgroups fill the chip more than once; with fewer its time is that of the longest
     // prompt's last block.  The key-split kernel gives every (32 queries, head) pair a workgroup
-    // of its own and splits its keys among the waves: four times the workgroups, each a quarter
-    // as long, but no tile is shared.  Measured crossover: about 300 eight-wave workgroups, i.e.
-    // query tokens x heads of about 77000 (one 12288-token prompt or ten 1024-token prompts at 8
-    // heads); less for batches of short prompts.  The choice looks at the call's number of query tokens, which the host knows; inside either kernel,
-    // the key-split one at one number of waves (split_waves_for looks at the same sizes), a
-    // request's result does not depend on the rest of its batch.
-    int shared_hp, shared_qw;
-    sw_prefill_shape(a.group, 8, &shared_hp, &shared_qw);
-    int which, knob_hp, knob_qw, knob_merge, halves_hp = 1, halves_qw = 1;
+    // of its own and splits its keys among the waves: more workgroups, each a quarter
+    // as long, but no tile is shared.  The lines: use_shared.  The choice looks at the call's number of query tokens,
+    // which the host knows; inside either kernel, the key-split one at one number of waves (split_waves_for looks
+    // at the same sizes), a request's result does not depend on the rest of its batch.
+    const int shared_qw = sw_prefill_flat_blocks(a.group, 8), halves_qw = sw_prefill_flat_blocks(a.group, 4);
+    const bool flat = flat_columns(a.group, std::min<long long>(n_tokens, (long long)n_req * max_q_len) / n_req);
+    int which, knob_hp, knob_qw, knob_merge;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         which = g_prefill_kernel;
@@ -851,19 +880,21 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         // which the prompt kernel never sees: leave one row per request out of the estimate)
         const long long q_all = std::min<long long>(n_tokens, (long long)n_req * max_q_len);
         const long long q_bound = mixed ? std::max<long long>(0, q_all - n_req) : q_all;
-        const long long groups = (q_bound / (32 * shared_qw)) * n_kvh * (a.group / shared_hp);
-        // short prompts make short chains of tiles, so fewer workgroups already suffice
-        // (measured: 24 x 256 and 16 x 512 tokens gain 17-25 % from the shared-tile kernel)
-        const long long avg_q = q_bound / (n_req > 0 ? n_req : 1);
-        const long long need = avg_q <= 256 ? 192 : (avg_q <= 1024 ? 256 : kPrefillSharedMinGroups);
-        which = groups >= need ? 1 : 2;
-        sw_prefill_shape(a.group, 4, &halves_hp, &halves_qw);
-        const long long q_block = 32 * halves_qw;
-        const long long blocks = (q_all + q_block - 1) / q_block * n_kvh * (a.group / halves_hp);
-        const bool from_start = !mixed || max_len <= q_all + q_all / 8;
+        int hp, qw;
+        sw_prefill_shape(a.group, 8, &hp, &qw);
+        PromptCall c;
+        c.avg_q = q_bound / n_req;
+        c.n_req = n_req;
+        c.group = a.group;
+        c.whole = !mixed;
+        c.from_start = !mixed || max_len <= q_all + q_all / 8;
+        c.blocks = (q_all + 32 * halves_qw - 1) / (32 * halves_qw) * n_kvh * (a.group * halves_qw / 4);
+        c.groups = (q_bound / (32 * qw)) * n_kvh * (a.group / hp);
+        c.group_waves = hp * qw;
+        c.full_groups = (q_bound / 32) * n_qh / 8;
+        which = use_shared(c) ? 1 : 2;
         // (the caller's heads and waves are the other two kernels' shapes)
-        if (knob_hp == 0 && knob_qw == 0 &&
-            use_halves(blocks, groups, avg_q, n_req, halves_hp, halves_hp * halves_qw, shared_hp * shared_qw, from_start, !mixed)) which = 3;
+        if (knob_hp == 0 && knob_qw == 0 && use_halves(c)) which = 3;
     }
     int split_waves = 4;
     if (which == 2) {
@@ -876,16 +907,18 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         }
         if (knob_qw == 2 || knob_qw == 4 || knob_qw == 8) split_waves = knob_qw;
     } else if (which == 3) {
-        a.hp = halves_hp;
+        a.hp = 0;
         a.qw = halves_qw;
-    } else {
-        a.hp = shared_hp;
-        a.qw = shared_qw;
+    } else if (knob_hp > 0 || knob_qw > 0 || !flat) {
+        sw_prefill_shape(a.group, 8, &a.hp, &a.qw);
         if (knob_hp > 0 && a.group % knob_hp == 0) {
             a.hp = knob_hp;
             a.qw = 8 / a.hp > 0 ? 8 / a.hp : 1;
         }
         if (knob_qw > 0 && a.hp * knob_qw <= 8) a.qw = knob_qw;
+    } else {
+        a.hp = 0;
+        a.qw = shared_qw;
     }
     a.n_qblocks = (max_q_len + 32 * a.qw - 1) / (32 * a.qw);      // the grid covers max_q_len query tokens
     if (pg) {

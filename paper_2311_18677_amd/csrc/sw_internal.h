@@ -79,8 +79,8 @@ struct SwPrefillArgs {
     int   max_q;                        // bound on the query tokens of a request (sizes the grid)
     int   skip_single;                  // non-zero: requests with exactly one query token are left out
     int   compact;                      // how workgroups find their (request, query block): see sw_prefill_items
-    int   hp;                           // query heads (of one group) per workgroup
-    int   qw;                           // waves per query head in a workgroup
+    int   hp;                           // query heads (of one group) per workgroup; 0: the columns are dealt flat (sw_prefill_flat)
+    int   qw;                           // waves per query head in a workgroup; flat: blocks of 32 query positions an item has
     int   n_qblocks;                    // query blocks (of 32 * qw positions) that cover max_len
     long long stride_req, stride_kvh;   // in elements
     // block-table variant: k, v are pools, row t of request r is row
@@ -227,6 +227,21 @@ static inline bool sw_split_scans_early(const SwPrefillArgs &a)
 }
 bool       sw_prefill_mfma_supported(const SwPrefillArgs &a);
 void       sw_prefill_shape(int group, int cols, int *hp, int *qw);
+// Flat dealing of the shared-tile kernels' columns (query head, 32 query positions): the columns of an item, which
+// is as many blocks of 32 positions as make the columns of all the group's heads a multiple of the `cols` that a
+// workgroup computes, are numbered block by block, and a workgroup takes the next `cols` of them.  For groups
+// of a power of two it is the dealing by whole heads; groups of three, five, six and seven have no idle waves.
+static inline int sw_prefill_flat_blocks(int group, int cols)
+{
+    int common = cols;                                  // (cols is a power of two)
+    while (group % common) common /= 2;
+    return cols / common;
+}
+// Workgroups of `cols` columns that serve one item of one key/value head.
+static inline int sw_prefill_parts(const SwPrefillArgs &a, int cols)
+{
+    return a.hp ? a.group / a.hp : a.group * a.qw / cols;
+}
 // merge != null (mixed batches, four waves): extra workgroups merge the token-phase chunks that the
 // partial kernel launched before on the same stream left in the workspace (instead of the combine kernel)
 hipError_t sw_launch_prefill_split(const SwPrefillArgs &a, int waves, hipStream_t stream, const SwLaunchEvents *ev,

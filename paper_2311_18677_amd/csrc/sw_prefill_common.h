@@ -230,6 +230,16 @@ __device__ __forceinline__ QItem find_item(const SwPrefillArgs &a, unsigned item
     return it;
 }
 
+// What a workgroup of the shared-tile kernels computes of its item: `cols` columns (query head, 32 query
+// positions), wave by wave.
+struct Columns {
+    int width, first, head0;       // column c: head head0 + c % width, positions 32 * (c / width) .. +31 of the item
+    __device__ __forceinline__ Columns(const SwPrefillArgs &a, int part, int cols)
+        : width(a.hp ? a.hp : a.group), first(a.hp ? 0 : part * cols), head0(a.hp ? part * a.hp : 0) {}
+    __device__ __forceinline__ int head(int i) const { return head0 + (first + i) % width; }
+    __device__ __forceinline__ int block(int i) const { return (first + i) / width; }
+};
+
 // Q^T operands of a wave: lane (n16, gq) holds dims 32kk + 8gq .. +7 of the query with
 // index q0 + 16nb + n16 (of nq).  Indices past the last query repeat it (never stored);
 // row indices are clamped into [0, n_tokens).

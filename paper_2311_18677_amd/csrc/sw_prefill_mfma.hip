@@ -51,19 +51,20 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kBufs * kBufBytes];
 
-    // blockIdx -> (item = (request, query block), key/value head, block of hp query heads)
-    const int q_block = kQPerWave * a.qw;        // query tokens per workgroup
-    const unsigned n_hb = (unsigned)(a.group / a.hp);
-    const unsigned hb = blockIdx.x % n_hb;
-    const unsigned rest = blockIdx.x / n_hb;
+    // blockIdx -> (item = (request, query block), key/value head, part of the item's columns, later
+    // positions first)
+    const int q_block = kQPerWave * a.qw;        // query tokens of an item
+    const unsigned n_parts = a.hp ? (unsigned)(a.group / a.hp) : (unsigned)(a.group * a.qw) / NW;
+    const Columns mine(a, (int)(n_parts - 1 - blockIdx.x % n_parts), NW);
+    const unsigned rest = blockIdx.x / n_parts;
     const int g = (int)(rest % (unsigned)a.n_kvh);
     const QItem it = find_item<true>(a, rest / (unsigned)a.n_kvh, q_block);
     if (!it.valid) return;
     const int r = it.r, qb = it.qb, L = it.L, NQ = it.NQ;   // NQ: the request's last NQ tokens are its queries
     const long long q_first = it.q_first;
     const int P0 = L - NQ;                       // position of query index 0
-    const int Q0 = qb * q_block;                 // first query index of the workgroup
-    if (Q0 >= NQ) return;
+    const int Q0 = qb * q_block;                 // first query index of the item
+    if (Q0 + kQPerWave * mine.block(0) >= NQ) return;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -79,7 +80,7 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
     const_table_t table = PAGED ? (const_table_t)(a.block_table + (long long)r * a.max_blocks) : nullptr;
 
     // tiles the workgroup walks: up to the position of its last query
-    const int last_pos = P0 + min(Q0 + q_block, NQ) - 1;
+    const int last_pos = P0 + min(Q0 + kQPerWave * (mine.block(NW - 1) + 1), NQ) - 1;
     const int n_tiles = last_pos / kTile + 1;
 
     if (wave >= NW) {
@@ -88,8 +89,8 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
         return;
     }
 
-    const int hh   = (int)hb * a.hp + wave % a.hp;   // query head within the group
-    const int sb   = wave / a.hp;                // which 32 query positions of the block
+    const int hh   = mine.head(wave);               // query head within the group
+    const int sb   = mine.block(wave);              // which 32 query positions of the item
     const int qw0  = Q0 + kQPerWave * sb;        // first query index of the wave ...
     const int aw0  = P0 + qw0;                   // ... and its position
     const int h    = g * a.group + hh;
@@ -203,7 +204,7 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
 
 bool sw_prefill_mfma_supported(const SwPrefillArgs &a)
 {
-    return a.head_dim == kD && a.group >= 1 && a.hp >= 1 && a.hp <= 8 && a.group % a.hp == 0;
+    return a.head_dim == kD && a.group >= 1 && a.qw >= 1 && (a.hp == 0 ? a.group * a.qw % 8 == 0 : a.hp >= 1 && a.hp <= 8 && a.group % a.hp == 0);
 }
 
 // How a workgroup is shaped: hp query heads of one group, qw waves (32 query positions
@@ -223,14 +224,13 @@ hipError_t sw_launch_prefill_mfma(const SwPrefillArgs &a_in, hipStream_t stream,
 {
     SwPrefillArgs a = a_in;
     if (!sw_prefill_mfma_supported(a)) return hipErrorNotSupported;
-    if (a.hp < 1 || a.group % a.hp != 0 || a.qw < 1) return hipErrorInvalidValue;
     int compact;
-    const long long per_item = (long long)a.n_kvh * (a.group / a.hp);
+    const long long per_item = (long long)a.n_kvh * sw_prefill_parts(a, 8);
     const long long blocks = sw_prefill_items_by_work(a, kQPerWave * a.qw, per_item, &compact) * per_item;
     a.compact = compact;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
-    const int nw = a.hp * a.qw;
+    const int nw = a.hp ? a.hp * a.qw : 8;
 #define SW_PREFILL_CASE(W) \
     if (nw == W) return a.block_table ? sw_launch(sw_prefill_mfma_kernel<W, true>, grid, dim3(64 * (W + kMovers)), 0, stream, ev, a) \
                                       : sw_launch(sw_prefill_mfma_kernel<W, false>, grid, dim3(64 * (W + kMovers)), 0, stream, ev, a);
