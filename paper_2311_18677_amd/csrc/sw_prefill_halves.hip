@@ -3,7 +3,7 @@
 //
 // The shared-tile kernel (sw_prefill_mfma.hip) stages every K/V tile once for the eight waves of
 // a workgroup, which is what keeps the L2 traffic low, but with few workgroups its time is the
-// chain of tiles of the longest prompt's last block: 0.9 us for every 32 positions, on a partly
+// chain of tiles of the longest prompt's last block: 0.75 us for every 32 positions, on a partly
 // idle chip.  The key-split kernel (sw_prefill_split.hip) has short chains but streams the key
 // range through L2 once per 32 queries and head.  Here four of the waves take the even tiles and four
 // the odd ones, for half as many (query head, 32 positions) columns: half the chain, twice the
