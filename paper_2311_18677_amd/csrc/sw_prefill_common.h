@@ -454,6 +454,53 @@ __device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_
     weights_block<DOT>(s, scale_log2e, -m * scale_log2e, p, psum);
 }
 
+// One operand of load_vt: dims 16e .. 16e+15 of the tile's V rows.
+__device__ __forceinline__ Frag v_operand(const unsigned char *vb, const unsigned (&off)[8], int e)
+{
+    Frag v;
+#pragma unroll
+    for (int hk = 0; hk < 2; ++hk) {
+        union { short4_t s; unsigned int u[2]; } x;
+        x.s = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(vb + off[e] + hk * 16 * kRowBytes));
+        v.u[2 * hk] = x.u[0];
+        v.u[2 * hk + 1] = x.u[1];
+    }
+    return v;
+}
+
+// O^T += V^T (what the rounding left of the tile's weights)^T, and its sum: for the tile that a wave's
+// maximum comes from, whose weights are the largest and, for rows of few positions, all there are.  (An infinity in
+// V stays out of that product, where its sign would be the rest's.  The fences keep the operands from
+// being read all at once, which would take registers.)
+__device__ __forceinline__ void add_rest(const unsigned char *vb, const unsigned (&vt_off)[8], const float4_t (&s)[2][2],
+                                         float scale_log2e, const float (&m)[2], const Frag (&p)[2], float (&l)[2],
+                                         float4_t (&o)[2][8])
+{
+    const half2_t none = {(_Float16)0.f, (_Float16)0.f};
+    half2_t spoiled = none;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const Frag v = v_operand(vb, vt_off, e);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            spoiled = __builtin_elementwise_fma((half2_t){v.h[2 * j], v.h[2 * j + 1]}, none, spoiled);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (__builtin_amdgcn_ballot_w64(!(spoiled[0] + spoiled[1] == (_Float16)0.f)) != 0) return;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        Frag rest;
+        float rsum;
+        rest_block(s[nb], scale_log2e, -m[nb] * scale_log2e, p[nb], rest, rsum);
+        l[nb] += rsum;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v_operand(vb, vt_off, e).h, rest.h, o[nb][e], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
 // 64 lanes x 16 bytes, global -> LDS, asynchronously: lane l's bytes (at base + off, base
 // wave-uniform) land at LDS offset lds_at + 16 l.  Inline assembly, because the compiler's
 // wait-count pass holds an LDS read that may alias a pending request of the builtin form (every

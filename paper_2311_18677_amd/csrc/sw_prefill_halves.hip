@@ -136,19 +136,6 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     const unsigned char *vmine = lds + kVBase + kg * kTileBytes;
     const int t_mine = kg * kTile;
 
-    // Operand of the second product: dims 16e .. 16e+15 of the tile's V rows (see load_vt).
-    auto v_operand = [&](const unsigned char *vb, int e) __attribute__((always_inline)) {
-        Frag v;
-#pragma unroll
-        for (int hk = 0; hk < 2; ++hk) {
-            union { short4_t s; unsigned int u[2]; } x;
-            x.s = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(vb + vt_off[e] + hk * 16 * kRowBytes));
-            v.u[2 * hk] = x.u[0];
-            v.u[2 * hk + 1] = x.u[1];
-        }
-        return v;
-    };
-
     // Step i, staged in ring slot B (= i % kBufs, as a compile-time constant).
     auto step = [&](int i, auto buf_c) __attribute__((always_inline)) {
         constexpr int B = decltype(buf_c)::value;
@@ -203,7 +190,7 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
         // ---- O^T += V^T P^T
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const Frag v = v_operand(vb, e);
+            const Frag v = v_operand(vb, vt_off, e);
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v.h, p[nb].h, o[nb][e], 0, 0, 0);
         }
@@ -214,34 +201,8 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
             __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-        // The wave's first tile: what the rounding left of its weights as well (an infinity in V
-        // stays out of that product, where its sign would be the rest's).
-        if (B == 0 && i == 0) {
-            const half2_t none = {(_Float16)0.f, (_Float16)0.f};
-            half2_t spoiled = none;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const Frag v = v_operand(vb, e);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    spoiled = __builtin_elementwise_fma((half2_t){v.h[2 * j], v.h[2 * j + 1]}, none, spoiled);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (__builtin_amdgcn_ballot_w64(!(spoiled[0] + spoiled[1] == (_Float16)0.f)) == 0) {
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    Frag rest;
-                    float rsum;
-                    rest_block(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], rest, rsum);
-                    l[nb] += rsum;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v_operand(vb, e).h, rest.h, o[nb][e], 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-            }
-        }
+        // The wave's first tile: what the rounding left of its weights as well.
+        if (B == 0 && i == 0) add_rest(vb, vt_off, s, a.scale_log2e, m, p, l, o);
     };
     static_assert(kBufs == 3, "the loop below is unrolled by the number of buffers");
     for (int i = 0; i < n_steps; i += kBufs) {
