@@ -48,7 +48,8 @@ struct PromptCall {
 //   below; 580 to 680 1.00 to 1.28 from 4500 on, 0.70 to 1.21 below.  Beyond 0.64 to 1.20.  (Two prompts alike gain least
 //   below 448: 1.00 to 1.13, key-split up to there.)
 //   Several requests that may have earlier context: their lengths decide, which the host does not know.  Only where
-//   whole heads make workgroups of five or seven waves does this one win throughout (1.01 to 2.1).
+//   whole heads make workgroups of five or seven waves does this one win throughout (1.01 to 2.1), two whole
+//   prompts of such groups included.
 // Groups of three and six heads that may have earlier context stay with the other kernels (0.82 to 1.03 for six waves).
 bool use_halves(const PromptCall &c)
 {
@@ -58,11 +59,11 @@ bool use_halves(const PromptCall &c)
         if (c.blocks <= 512) return c.blocks >= 432 || (c.whole && c.blocks >= 336 && long_enough);
         return c.blocks <= 720 && c.avg_q >= 4000 && c.from_start;
     }
-    if (!c.whole)
-        return c.group_waves < 8 && c.avg_q >= 3000 && c.groups >= 300 && c.groups < (c.avg_q < 5000 ? 345 : 400);
+    const bool odd = c.group_waves < 8 && c.avg_q >= 3000 && c.groups >= 300 && c.groups < (c.avg_q < 5000 ? 345 : 400);
+    if (!c.whole) return odd;
     if (c.blocks > 512) return c.blocks <= 680 && c.avg_q >= (c.blocks <= 580 ? 2500 : 4500);
     if (c.blocks >= 448) return c.avg_q >= 1000 && long_enough;
-    return c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough;
+    return odd || (c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough);
 }
 
 // Whether the shared-tile kernel is faster than the key-split one.
