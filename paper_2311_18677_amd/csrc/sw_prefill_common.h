@@ -417,41 +417,74 @@ __device__ __forceinline__ void weights_block(const float4_t (&s)[2], float scal
     }
 }
 
-// What that rounding left of the weights, in binary16 again, and the lane's sum of it: with p it
-// makes the weights good to about 22 bits.
-__device__ __forceinline__ void rest_block(const float4_t (&s)[2], float scale_log2e, float neg_m, const Frag &p, Frag &rest,
-                                           float &rsum)
+// The same, and what the rounding left of the weights, in binary16 again, with the lane's sum of it: with it the
+// weights are good to about 22 bits.
+struct Rest {
+    Frag w;
+    float sum;
+};
+
+__device__ __forceinline__ void weights_rest_block(const float4_t (&s)[2], float scale_log2e, float neg_m, Frag &p, float &psum,
+                                                   Rest &rest)
 {
     const float one = opaque_one();
-    rsum = 0.f;
+    psum = rest.sum = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const float x = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1)], scale_log2e, neg_m)) - (float)p.h[2 * j];
-        const float y = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1) + 1], scale_log2e, neg_m)) - (float)p.h[2 * j + 1];
+        const float x = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1)], scale_log2e, neg_m));
+        const float y = __builtin_amdgcn_exp2f(fmaf(s[j >> 1][2 * (j & 1) + 1], scale_log2e, neg_m));
         const half2_t w = __builtin_convertvector((float2_t){x, y}, half2_t);
-        rest.h[2 * j] = w[0];
-        rest.h[2 * j + 1] = w[1];
-        rsum = add_halves<false>(w, one, rsum);
+        p.h[2 * j] = w[0];
+        p.h[2 * j + 1] = w[1];
+        psum = add_halves<false>(w, one, psum);
+        const half2_t left = __builtin_convertvector((float2_t){x - (float)w[0], y - (float)w[1]}, half2_t);
+        rest.w.h[2 * j] = left[0];
+        rest.w.h[2 * j + 1] = left[1];
+        rest.sum = add_halves<false>(left, one, rest.sum);
     }
 }
 
-// The exact pass of one query block: raises the running maximum where a score of the tile lies
-// more than kLazyBits above it, rescales what has been accumulated and computes the tile's
-// weights again.  (weights_block takes the maximum as it stands.)
-template <bool DOT = false>
-__device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_log2e, float lazy_raw,
-                                            float &m, float &l, float4_t (&o)[8], Frag &p, float &psum)
+// A tile's largest score of each query.
+__device__ __forceinline__ float tile_max(const float4_t (&s)[2])
 {
-    float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
-                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
-    mt = quad_rows_max(mt);
+    return quad_rows_max(fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                               fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))));
+}
+
+// Raises the running maximum of one query block where a score of the tile lies more than kLazyBits above it, and
+// rescales what has been accumulated.
+__device__ __forceinline__ void raise_max(const float4_t (&s)[2], float scale_log2e, float lazy_raw, float &m, float &l,
+                                          float4_t (&o)[8])
+{
+    const float mt = tile_max(s);
     const float m_new = mt > m + lazy_raw ? mt : m;
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * scale_log2e);
     m = m_new;
     l *= alpha;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] *= alpha;
+}
+
+// The exact pass of one query block: that, and the tile's weights again.  (weights_block takes the
+// maximum as it stands.)
+template <bool DOT = false>
+__device__ __forceinline__ void raise_block(const float4_t (&s)[2], float scale_log2e, float lazy_raw,
+                                            float &m, float &l, float4_t (&o)[8], Frag &p, float &psum)
+{
+    raise_max(s, scale_log2e, lazy_raw, m, l, o);
     weights_block<DOT>(s, scale_log2e, -m * scale_log2e, p, psum);
+}
+
+// Both of a wave's first tile, where there is no maximum yet (m is kNegBig, l and o are zero).
+__device__ __forceinline__ void first_weights(const float4_t (&s)[2][2], float scale_log2e, float lazy_raw, float (&m)[2],
+                                              Frag (&p)[2], float (&psum)[2], Rest (&rest)[2])
+{
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        const float mt = tile_max(s[nb]);
+        m[nb] = mt > kNegBig + lazy_raw ? mt : kNegBig;        // (no position of the tile may be visible)
+        weights_rest_block(s[nb], scale_log2e, -m[nb] * scale_log2e, p[nb], psum[nb], rest[nb]);
+    }
 }
 
 // One operand of load_vt: dims 16e .. 16e+15 of the tile's V rows.
@@ -468,36 +501,39 @@ __device__ __forceinline__ Frag v_operand(const unsigned char *vb, const unsigne
     return v;
 }
 
-// O^T += V^T (what the rounding left of the tile's weights)^T, and its sum: for the tile that a wave's
-// maximum comes from, whose weights are the largest and, for rows of few positions, all there are.  (An infinity in
-// V stays out of that product, where its sign would be the rest's.  The fences keep the operands from
-// being read all at once, which would take registers.)
-__device__ __forceinline__ void add_rest(const unsigned char *vb, const unsigned (&vt_off)[8], const float4_t (&s)[2][2],
-                                         float scale_log2e, const float (&m)[2], const Frag (&p)[2], float (&l)[2],
-                                         float4_t (&o)[2][8])
+// O^T += V^T rest^T behind the second product of one of a wave's first tiles.  An infinity in V stays out, where its
+// sign would be the rest's.  It (or a NaN in V) has left a dim of the accumulators without a finite value in every
+// query, which one block of queries tells; a query that is itself not finite has lost all its dims and no other's.
+// Some 0.35 us a tile for two waves to a SIMD, where a second look at V's operands, the weights computed anew and a
+// pass over the operands for each block of queries took 1.4.
+__device__ __forceinline__ void add_rest(const unsigned char *vb, const unsigned (&vt_off)[8], const Rest (&rest)[2],
+                                         float (&l)[2], float4_t (&o)[2][8])
 {
-    const half2_t none = {(_Float16)0.f, (_Float16)0.f};
-    half2_t spoiled = none;
+    constexpr int kAhead = 2;                    // operands read ahead of their products
+    Frag v[kAhead];
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) v[e] = v_operand(vb, vt_off, e);
+    float top[2] = {0.f, 0.f};                   // (v_maximum3_f32, which hands a NaN on)
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            top[i] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(o[0][e][2 * i]),
+                                                                                 __builtin_fabsf(o[0][e][2 * i + 1])), top[i]);
+    unsigned long long lost = __builtin_amdgcn_ballot_w64(!(__builtin_elementwise_maximum(top[0], top[1]) < INFINITY));
+    if (lost != 0) {                             // all sixteen queries of a lane group?
+        for (int i = 1; i < 16; i *= 2) lost &= lost >> i;
+        if (lost & 0x0001000100010001ull) return;
+    }
+    l[0] += rest[0].sum;
+    l[1] += rest[1].sum;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const Frag v = v_operand(vb, vt_off, e);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            spoiled = __builtin_elementwise_fma((half2_t){v.h[2 * j], v.h[2 * j + 1]}, none, spoiled);
+        for (int nb = 0; nb < 2; ++nb)
+            o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v[e % kAhead].h, rest[nb].w.h, o[nb][e], 0, 0, 0);
+        if (e + kAhead < 8) v[e % kAhead] = v_operand(vb, vt_off, e + kAhead);
         __builtin_amdgcn_sched_barrier(0);
-    }
-    if (__builtin_amdgcn_ballot_w64(!(spoiled[0] + spoiled[1] == (_Float16)0.f)) != 0) return;
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        Frag rest;
-        float rsum;
-        rest_block(s[nb], scale_log2e, -m[nb] * scale_log2e, p[nb], rest, rsum);
-        l[nb] += rsum;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            o[nb][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v_operand(vb, vt_off, e).h, rest.h, o[nb][e], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
     }
 }
 

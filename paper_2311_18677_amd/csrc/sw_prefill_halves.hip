@@ -26,7 +26,8 @@
 // there are two, which costs 1.5 % of the error against 64 bits (2.57e-4 -> 2.61e-4 of the 2-norm
 // for a prompt of 8192 tokens, nearly all of it in rows of few positions).  The waves therefore
 // multiply their first tile by the rest of its weights as well: 2.47e-4, rows behind 2600
-// and more positions are as far off as the key-split kernel's.  It takes 1 to 2 us of a call.
+// and more positions are as far off as the key-split kernel's.  The first tile is a step of its own, in front
+// of the loop (one prompt of 8192 tokens with its cache store 141 -> 136 us against the rest taken inside it).
 //
 // Measured (8 heads on one key/value head, attention alone): one prompt of 8192 tokens 144 us with the requests dealt to the
 // computing waves, 140 to 141 now, over blocks of 16 positions 163 -> 140, of 4 positions 180 -> 145; key-split 181.
@@ -137,8 +138,9 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     const int t_mine = kg * kTile;
 
     // Step i, staged in ring slot B (= i % kBufs, as a compile-time constant).
-    auto step = [&](int i, auto buf_c) __attribute__((always_inline)) {
+    auto step = [&](int i, auto buf_c, auto first_c) __attribute__((always_inline)) {
         constexpr int B = decltype(buf_c)::value;
+        constexpr bool FIRST = decltype(first_c)::value;
         // the step's tiles have landed, and this wave is done with the step before
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();
@@ -173,16 +175,21 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
         const int t0 = i * (KS * kTile) + t_mine;
         if (t0 + kTile > aw0) mask_tile(s, aw0, t0, n16, gq);
 
-        // ---- Optimistic pass: weights against the running maximum as it stands; the exact pass where
-        // some lane's weights sum to more than kSumBound (rare after the first tiles).
         Frag p[2];
+        Rest left[2];
         float psum[2];
+        if constexpr (FIRST) {
+            first_weights(s, a.scale_log2e, lazy_raw, m, p, psum, left);
+        } else {
+            // Optimistic pass: weights against the running maximum as it stands; the exact pass where
+            // some lane's weights sum to more than kSumBound (rare).
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) weights_block(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
-        if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
+            for (int nb = 0; nb < 2; ++nb) weights_block(s[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
+            if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-                raise_block(s[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum[nb]);
+                for (int nb = 0; nb < 2; ++nb)
+                    raise_block(s[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum[nb]);
+            }
         }
         l[0] += psum[0];
         l[1] += psum[1];
@@ -201,14 +208,16 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
             __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-        // The wave's first tile: what the rounding left of its weights as well.
-        if (B == 0 && i == 0) add_rest(vb, vt_off, s, a.scale_log2e, m, p, l, o);
+        if constexpr (FIRST) add_rest(vb, vt_off, left, l, o);
     };
+    using First = std::true_type;
+    using Later = std::false_type;
+    step(0, I0{}, First{});
     static_assert(kBufs == 3, "the loop below is unrolled by the number of buffers");
-    for (int i = 0; i < n_steps; i += kBufs) {
-        step(i, I0{});
-        if (i + 1 < n_steps) step(i + 1, I1{});
-        if (i + 2 < n_steps) step(i + 2, I2{});
+    for (int i = 1; i < n_steps; i += kBufs) {
+        step(i, I1{}, Later{});
+        if (i + 1 < n_steps) step(i + 1, I2{}, Later{});
+        if (i + 2 < n_steps) step(i + 2, I0{}, Later{});
     }
     l[0] = quad_rows_sum(l[0]);
     l[1] = quad_rows_sum(l[1]);

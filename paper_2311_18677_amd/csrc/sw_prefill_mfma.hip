@@ -26,8 +26,7 @@
 // 1920 -> 1800 to 1860 us, of 16384 500 -> 473, 12 of 618 to 8039 560 -> 527; 8 heads on 8, 8 of 1024
 // 36.1 -> 32.7; over blocks of 16 positions one of 16384 559 -> 459, 16 of 1024 57.4 -> 48.7.  One moving wave
 // or four: dense within 1 % of two; over blocks of 4 positions one takes 8 % longer (its table reads).
-// Tried: both products' operands read before the first product (188 registers instead of 162), the
-// same; each product of one query block beside the other's weights 13 % slower; the first product at a raised
+// Tried: both products' operands read before the first product, the same; each product of one query block beside the other's weights 13 % slower; the first product at a raised
 // wave priority 4 % slower; the key range in thirds for twelve waves, three to a SIMD, 6 % slower.
 #include "sw_prefill_common.h"
 
@@ -40,11 +39,12 @@ using namespace sw_prefill;
 constexpr int kBufBytes = 2 * kTileBytes;          // K tile, then V tile
 constexpr int kBufs     = 3;
 constexpr int kMovers   = 2;                       // waves that only request tiles
-// Queries before this position take the rest of their first tile's weights (add_rest).  A row has one maximum here
-// against the key-split kernel's four, which cost 3 to 4 % of the error against 64 bits (14 prompts of 371 tokens, 8
-// heads on one: 2.40e-4 there, 2.49e-4 here, with it 2.30e-4; 10 of 1488, 5 heads on 5, 2.50e-4, 2.58e-4 and 2.44e-4).
-// For every query it would take 1.4 us of each workgroup; those before this one's are the shortest.
-constexpr int kRestBefore = 128;
+// A prompt's first tiles whose weights' rest is taken into the second product as well.  A row has one maximum here,
+// whose own key's weight is exact, against the key-split kernel's four, and with weights of binary16 alone is up to 9 %
+// further off 64 bits.  Error over the key-split kernel's, rows before position 128, from there to 256, to 512 and
+// behind: one tile 0.92, 1.05, 1.03, 1.02; two 0.87, 0.99, 1.00, 1.00 (8 heads on one, 14 prompts of 371 tokens; 12 on
+// 4, 900 to 1100).
+constexpr int kRestTiles = 2;
 
 // NW = computing waves per workgroup = (query heads per workgroup) * (waves per head); kMovers more
 // request the tiles.
@@ -103,6 +103,11 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
     // tiles this wave computes on: up to the position of its own last query
     const int my_tiles = qw0 < NQ ? min(aw0 + kQPerWave - 1, L - 1) / kTile + 1 : 0;
 
+    if (my_tiles == 0) {                         // no query of its own: only the barriers
+        for (int ti = 0; ti < n_tiles; ++ti) __builtin_amdgcn_s_barrier();
+        return;
+    }
+
     unsigned vt_off[8];
     vt_offsets(n16, gq, vt_off);
     float m[2] = {kNegBig, kNegBig};
@@ -123,9 +128,11 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
         for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qreg[nb][kk].u));
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xc07f);
 
-    // One tile, staged in buffer B (= ti % kBufs, as a compile-time constant).
-    auto step = [&](int ti, auto buf_c) {
+    // One tile, staged in buffer B (= ti % kBufs, as a compile-time constant).  REST: the tile is
+    // one of the first kRestTiles.
+    auto step = [&](int ti, auto buf_c, auto rest_c) __attribute__((always_inline)) {
         constexpr int B = decltype(buf_c)::value;
+        constexpr bool REST = decltype(rest_c)::value;
         // the tile has landed, and this wave is done with the one before
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();
@@ -148,16 +155,27 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
         if (t0 + kTile > aw0) mask_tile(sacc, aw0, t0, n16, gq);
-        // Optimistic pass: weights against the running maximum as it stands; the exact pass where
-        // some lane's weights sum to more than kSumBound (rare after the first tiles).
         Frag p[2];
+        Rest left[2];
         float psum[2];
+        if constexpr (REST && B == 0) {
+            first_weights(sacc, a.scale_log2e, lazy_raw, m, p, psum, left);
+        } else {
+            // Optimistic pass: weights against the running maximum as it stands; the exact pass where
+            // some lane's weights sum to more than kSumBound (rare).
+            auto weigh = [&](int nb) __attribute__((always_inline)) {
+                if constexpr (REST) weights_rest_block(sacc[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb], left[nb]);
+                else                weights_block(sacc[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
+            };
+            weigh(0);
+            weigh(1);
+            if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) weights_block(sacc[nb], a.scale_log2e, -m[nb] * a.scale_log2e, p[nb], psum[nb]);
-        if (__builtin_amdgcn_ballot_w64(!(psum[0] <= kSumBound && psum[1] <= kSumBound)) != 0) {
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-                raise_block(sacc[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb], p[nb], psum[nb]);
+                for (int nb = 0; nb < 2; ++nb) {
+                    raise_max(sacc[nb], a.scale_log2e, lazy_raw, m[nb], l[nb], o[nb]);
+                    weigh(nb);
+                }
+            }
         }
         l[0] += psum[0];
         l[1] += psum[1];
@@ -175,15 +193,20 @@ void sw_prefill_mfma_kernel(SwPrefillArgs a)
             __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-        // The first tile, where it is a good part of what the queries see: what the rounding left of
-        // its weights as well.
-        if (B == 0 && ti == 0 && aw0 < kRestBefore) add_rest(vb, vt_off, sacc, a.scale_log2e, m, p, l, o);
+        if constexpr (REST) add_rest(vb, vt_off, left, l, o);
     };
-    static_assert(kBufs == 3, "the loop below is unrolled by the number of buffers");
-    for (int ti = 0; ti < n_tiles; ti += kBufs) {
-        step(ti, std::integral_constant<int, 0>{});
-        if (ti + 1 < n_tiles) step(ti + 1, std::integral_constant<int, 1>{});
-        if (ti + 2 < n_tiles) step(ti + 2, std::integral_constant<int, 2>{});
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using Rested = std::true_type;
+    using Later = std::false_type;
+    static_assert(kBufs == 3 && kRestTiles == 2, "tiles by number and by buffer");
+    step(0, I0{}, Rested{});
+    if (n_tiles > 1) step(1, I1{}, Rested{});
+    for (int ti = 2; ti < n_tiles; ti += kBufs) {
+        step(ti, I2{}, Later{});
+        if (ti + 1 < n_tiles) step(ti + 1, I0{}, Later{});
+        if (ti + 2 < n_tiles) step(ti + 2, I1{}, Later{});
     }
 
     // ---- this lane's query rows: dims 16e + 4gq + i
