@@ -66,17 +66,19 @@ bool use_halves(const PromptCall &c)
     return odd || (c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough);
 }
 
-// Whether the shared-tile kernel is faster than the key-split one.
-//   Batches of three and more whole prompts, 1 to 64 heads, time of the key-split kernel over its: up to 512 tokens a request
-//   1.00 to 1.34 from 160 full workgroups on (0.92 at 152); up to 1024 0.95 to 1.33 from 192 on (0.76 to 1.04 below); up to
-//   2500 1.09 to 2.5 from 264 on (10 prompts of 1488, 5 heads on 5: 111 -> 44 us), above from 290.
-//   One or two prompts, and calls that may have earlier context or token-phase requests, about which the host
-//   knows less: 300 workgroups, 256 and 192 for short prompts.
+// Whether the shared-tile kernel is faster than the key-split one: from 300 of its workgroups with whole heads in each,
+// 256 and 192 for short prompts.
+//   Batches of three and more whole prompts, 1 to 64 heads, time of the key-split kernel over its, also with fewer where
+//   these would be as many with eight waves in each: up to 512 tokens a request 1.00 to 1.34 from 160 on (0.92 at 152); up to 1024
+//   0.95 to 1.33 from 192 on (0.76 to 1.04 below); up to 2500 1.09 to 2.5 from 264 on (10 prompts of 1488, 5 heads on 5:
+//   111 -> 44 us), above from 290.  (Not instead: groups of 5, 10 and 15 heads, with five waves a workgroup, fill
+//   the chip with workgroups that are counted as 5/8.  13 prompts of 63 tokens, 40 heads on 8, 9.9 us, key-split 14.5; 42 of
+//   147, 6 on 2, 15.1 and 19.2; 28 of 110, 10 on one, 12.3 and 16.3.)
 bool use_shared(const PromptCall &c)
 {
-    if (c.whole && c.n_req > 2)
-        return c.full_groups >= (c.avg_q <= 512 ? 160 : c.avg_q <= 1024 ? 192 : c.avg_q <= 2500 ? 264 : 290);
-    return c.groups >= (c.avg_q <= 256 ? 192 : c.avg_q <= 1024 ? 256 : 300);
+    if (c.groups >= (c.avg_q <= 256 ? 192 : c.avg_q <= 1024 ? 256 : 300)) return true;
+    if (!c.whole || c.n_req < 3) return false;
+    return c.full_groups >= (c.avg_q <= 512 ? 160 : c.avg_q <= 1024 ? 192 : c.avg_q <= 2500 ? 264 : 290);
 }
 
 // Whether the shared-tile kernel deals its columns flat (sw_prefill_flat_blocks), which matters for groups that are
