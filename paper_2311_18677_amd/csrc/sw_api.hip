@@ -49,22 +49,24 @@ struct PromptCall {
 //   below; 580 to 680 1.00 to 1.28 from 4500 on, 0.70 to 1.21 below.  Beyond 0.64 to 1.20.  (Two prompts alike gain least
 //   below 448: 1.00 to 1.13, key-split up to there.)
 //   Several requests that may have earlier context: their lengths decide, which the host does not know.  Only where
-//   whole heads make workgroups of five or seven waves does this one win throughout (1.01 to 2.1), two whole
-//   prompts of such groups included.
-// Groups of three and six heads that may have earlier context stay with the other kernels (0.82 to 1.03 for six waves).
+//   whole heads make workgroups of five to seven waves does this one win throughout (1.01 to 2.1), whole
+//   prompts of such groups included (3 of 3999 tokens, 7 heads on one: 156 us shared-tile, 124 here).
+// Groups of three, six and nine heads, thirds of the columns, have no part in that, and stay with the other kernels where
+// they may have earlier context (0.82 to 1.03 for six waves).
 bool use_halves(const PromptCall &c)
 {
     const bool long_enough = c.group % 2 == 0 || c.group % 3 == 0 || c.avg_q >= 1500;
-    if (!c.whole && c.group % 3 == 0 && c.group % 4 != 0) return false;
+    const bool thirds = c.group % 3 == 0 && c.group % 4 != 0;
+    if (!c.whole && thirds) return false;
     if (c.n_req == 1) {
         if (c.blocks <= 512) return c.blocks >= 432 || (c.whole && c.blocks >= 336 && long_enough);
         return c.blocks <= 720 && c.avg_q >= 4000 && c.from_start;
     }
-    const bool odd = c.group_waves < 8 && c.avg_q >= 3000 && c.groups >= 300 && c.groups < (c.avg_q < 5000 ? 345 : 400);
-    if (!c.whole) return odd;
+    if (!thirds && c.group_waves < 8 && c.avg_q >= 3000 && c.groups >= 300 && c.groups < (c.avg_q < 5000 ? 345 : 400)) return true;
+    if (!c.whole) return false;
     if (c.blocks > 512) return c.blocks <= 680 && c.avg_q >= (c.blocks <= 580 ? 2500 : 4500);
     if (c.blocks >= 448) return c.avg_q >= 1000 && long_enough;
-    return odd || (c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough);
+    return c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough;
 }
 
 // Whether the shared-tile kernel is faster than the key-split one: from 300 of its workgroups with whole heads in each,

@@ -55,3 +55,14 @@ def test_short_prompts_whose_heads_do_not_fill_the_waves(n_qh, n_kvh, lens, kern
 def test_lengths_apart(n_qh, n_kvh, lens, spare, kernel):
     """A batch moves to the shared-tile kernel where its longest prompt can be no longer than its mean allows."""
     check(n_qh, n_kvh, lens, kernel, spare)
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,lens,kernel", [
+    (5, 1, [5000, 5000], 3), (5, 1, [4799, 4800], 2),           # 312 workgroups of five waves, 299
+    (7, 1, [3200, 3200, 3200], 3), (7, 1, [3505, 3505, 3505], 3), (7, 1, [7000, 1760, 1790], 3),
+    (7, 1, [3680, 3680, 3679], 3), (7, 1, [3680, 3680, 3680], 1),               # 344 of seven and 345, below 5000 tokens
+    (7, 1, [6400, 6399], 3), (7, 1, [6400, 6400], 1),           # 399 and 400
+    (3, 1, [8000, 6500], 2),                                    # 226 of six; threes have no part in this
+])
+def test_whole_prompts_of_groups_of_five_and_seven(n_qh, n_kvh, lens, kernel):
+    check(n_qh, n_kvh, lens, kernel)
