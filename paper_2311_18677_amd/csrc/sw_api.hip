@@ -69,16 +69,24 @@ bool use_halves(const PromptCall &c)
     return c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough;
 }
 
+// Whether a batch's prompts are enough of a length: a call takes as long as its longest prompt's last item in the
+// kernels that share staged tiles, which one workgroup walks, and as long as all its work in the key-split kernel.  The
+// lengths are the device's to know; their mean and the positions that the caches have bound how far apart they can be.
+// `workgroups` against `line`, what even lengths need.  (600: what a call takes apart from its chains, in positions of the
+// longest one.)
+bool alike(const PromptCall &c, long long workgroups, long long line)
+{
+    return workgroups * (c.avg_q + 600) >= line * (c.longest + 600);
+}
+
 // Whether the shared-tile kernel is faster than the key-split one: from 300 of its workgroups with whole heads in each,
 // 256 and 192 for short prompts.
 //   Batches of three and more whole prompts also with fewer, where these would be as many with eight waves in each and the
-// prompts are much of a length: a call takes as long as its longest prompt's last item here, which one workgroup walks, and
-// as long as all its work in the key-split kernel.  The lengths are the device's to know; their mean and the
-// positions that the caches have bound how far apart they can be.  Full workgroups times mean over that bound, time of the
-// key-split kernel over this one's, 3000 batches of 1 to 64 heads: up to 512 tokens a request 0.93 to 2.0 from 160 on, in
-// the mean 1.3 (0.87 to 1.3 at 140 to 160); up to 1024 0.94 to 2.5 from 192 on (0.84 to 1.1 below 180); up to 2500 1.05
-// to 2.9 from 240 on (0.95 to 1.1 at 200 to 225); longer ones 1.03 to 2.5 from 290 on.  By the mean alone 0.45 to 2.5: 31
-// prompts of 425, one of them of 13625 tokens, 2 heads on 2, 142 us key-split and 313 here.
+// prompts are much of a length.  1100 batches of 1 to 64 heads that do not reach the first lines, 25 to 16000 tokens a
+// request, lengths alike to fifteen times apart and one long among short, time of the key-split kernel over this one's: 168 of
+// them taken, 0.95 to 2.9, in the mean 1.25, one below 0.97; lines of 150 and 180 for short prompts take 223, six down to
+// 0.91.  By the mean alone 0.45 to 2.5: 31 prompts of 425, one of them of 13625 tokens, 2 heads on 2, 142 us key-split and 313
+// here.
 //   (Not the full workgroups instead of those launched: groups of 5, 10 and 15 heads, with five waves a workgroup, fill
 // the chip with workgroups that are counted as 5/8.  13 prompts of 63 tokens, 40 heads on 8, 9.9 us, key-split 14.5; 42 of
 // 147, 6 on 2, 15.1 and 19.2; 28 of 110, 10 on one, 12.3 and 16.3.)
@@ -86,7 +94,7 @@ bool use_shared(const PromptCall &c)
 {
     if (c.groups >= (c.avg_q <= 256 ? 192 : c.avg_q <= 1024 ? 256 : 300)) return true;
     if (!c.whole || c.n_req < 3) return false;
-    return c.full_groups * c.avg_q >= c.longest * (c.avg_q <= 512 ? 160 : c.avg_q <= 1024 ? 192 : c.avg_q <= 2500 ? 240 : 290);
+    return alike(c, c.full_groups, c.avg_q <= 512 ? 160 : c.avg_q <= 1024 ? 192 : c.avg_q <= 2500 ? 240 : 290);
 }
 
 // Whether the shared-tile kernel deals its columns flat (sw_prefill_flat_blocks), which matters for groups that are

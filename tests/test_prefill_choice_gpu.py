@@ -46,11 +46,12 @@ def test_short_prompts_whose_heads_do_not_fill_the_waves(n_qh, n_kvh, lens, kern
     (64, 8, [800, 40, 30], 0, 2), (8, 1, [4962] + [619] * 6, 0, 2), (8, 8, [4000, 2700, 1000, 1000], 0, 2),
     (8, 1, [371] * 14, 0, 1), (8, 1, [371] * 14, 4096, 2),      # ... as far as the caches' positions tell
     (8, 1, [366] * 14, 0, 1), (8, 1, [365] * 14, 0, 2),         # 160 full workgroups and 159, tokens of all alike
-    (8, 1, [430] + [365] * 14, 0, 2), (8, 1, [427] + [400] * 14, 0, 1),
+    (8, 1, [445] + [364] * 14, 0, 1), (8, 1, [500] + [360] * 14, 0, 2),         # 160 and 152 against the longest
+    (64, 8, [94] * 8, 50, 1), (14, 14, [206] * 17, 60, 1),      # short chains
     (16, 1, [1024, 1024, 1024], 0, 1), (16, 1, [1021, 1023, 1024], 0, 2),     # 192 and 190
     (5, 5, [1370] * 9, 0, 1), (5, 5, [1360] * 9, 0, 2),         # 240 and 238
-    (5, 5, [1600] + [1480] * 8, 0, 1), (5, 5, [1680] + [1470] * 8, 0, 2),     # 245 and 233 against the longest
-    (3, 3, [3125] * 8, 0, 1), (3, 3, [3200] + [3115] * 7, 0, 2),              # 292 and 285
+    (5, 5, [1600] + [1480] * 8, 0, 1), (5, 5, [1800] + [1455] * 8, 0, 2),     # 250 and 228 against the longest
+    (3, 3, [3125] * 8, 0, 1), (3, 3, [3250] + [3108] * 7, 0, 2),              # 292 and 282
 ])
 def test_lengths_apart(n_qh, n_kvh, lens, spare, kernel):
     """A batch moves to the shared-tile kernel where its longest prompt can be no longer than its mean allows."""
