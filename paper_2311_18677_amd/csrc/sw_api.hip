@@ -34,41 +34,6 @@ struct PromptCall {
     long long full_groups;   // the same with eight waves in all of them
 };
 
-// Whether the shared-tile form with the key range in two halves serves a prompt call, one of its
-// workgroups to a compute unit at a time.
-//   One request, up to two rounds of workgroups (432 to 512): the chains are half as long as
-//   the whole form's and tiles are shared, which the key-split kernel does not do.  Time of the
-//   other kernels over this one's, 1 to 64 heads: 1.12 to 1.26, a whole prompt from 336 on 1.00 to 1.26
-//   (8 heads on one, 6656 tokens: 127 -> 102 us); 1.00 to 1.04 at 316 to 334.  With odd groups only from
-//   1500 tokens on: an item has 128 positions, a short prompt few of them, the last partly empty.
-//   Above two rounds the third is partly empty, which prompts of 4000 tokens and more have chains uneven
-//   enough to fill: 1.20 to 1.22 up to 530 workgroups, 0.99 at 760.
-//   Several whole prompts, 130 batches of 1 to 64 heads, lengths alike to one ten times the other: 345 to 400
-//   workgroups 0.99 to 1.21, in the mean 1.07, from 1400 tokens a request on; 400 to 448 1.04 to 1.44 from 1100 on; 448 to
-//   512 0.87 to 1.25, in the mean 1.14, from 1000 on, 0.65 to 0.98 below; 512 to 580 1.02 to 1.28 from 2500 on, 0.64 to 0.98
-//   below; 580 to 680 1.00 to 1.28 from 4500 on, 0.70 to 1.21 below.  Beyond 0.64 to 1.20.  (Two prompts alike gain least
-//   below 448: 1.00 to 1.13, key-split up to there.)
-//   Several requests that may have earlier context: their lengths decide, which the host does not know.  Only where
-//   whole heads make workgroups of five to seven waves does this one win throughout (1.01 to 2.1), whole
-//   prompts of such groups included (3 of 3999 tokens, 7 heads on one: 156 us shared-tile, 124 here).
-// Groups of three, six and nine heads, thirds of the columns, have no part in that, and stay with the other kernels where
-// they may have earlier context (0.82 to 1.03 for six waves).
-bool use_halves(const PromptCall &c)
-{
-    const bool long_enough = c.group % 2 == 0 || c.group % 3 == 0 || c.avg_q >= 1500;
-    const bool thirds = c.group % 3 == 0 && c.group % 4 != 0;
-    if (!c.whole && thirds) return false;
-    if (c.n_req == 1) {
-        if (c.blocks <= 512) return c.blocks >= 432 || (c.whole && c.blocks >= 336 && long_enough);
-        return c.blocks <= 720 && c.avg_q >= 4000 && c.from_start;
-    }
-    if (!thirds && c.group_waves < 8 && c.avg_q >= 3000 && c.groups >= 300 && c.groups < (c.avg_q < 5000 ? 345 : 400)) return true;
-    if (!c.whole) return false;
-    if (c.blocks > 512) return c.blocks <= 680 && c.avg_q >= (c.blocks <= 580 ? 2500 : 4500);
-    if (c.blocks >= 448) return c.avg_q >= 1000 && long_enough;
-    return c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough;
-}
-
 // Whether a batch's prompts are enough of a length: a call takes as long as its longest prompt's last item in the
 // kernels that share staged tiles, which one workgroup walks, and as long as all its work in the key-split kernel.  The
 // lengths are the device's to know; their mean and the positions that the caches have bound how far apart they can be.
@@ -95,6 +60,46 @@ bool use_shared(const PromptCall &c)
     if (c.groups >= (c.avg_q <= 256 ? 192 : c.avg_q <= 1024 ? 256 : 300)) return true;
     if (!c.whole || c.n_req < 3) return false;
     return alike(c, c.full_groups, c.avg_q <= 512 ? 160 : c.avg_q <= 1024 ? 192 : c.avg_q <= 2500 ? 240 : 290);
+}
+
+// Whether the shared-tile form with the key range in two halves serves a prompt call, one of its
+// workgroups to a compute unit at a time.
+//   One request, up to two rounds of workgroups (432 to 512): the chains are half as long as
+//   the whole form's and tiles are shared, which the key-split kernel does not do.  Time of the
+//   other kernels over this one's, 1 to 64 heads: 1.12 to 1.26, a whole prompt from 336 on 1.00 to 1.26
+//   (8 heads on one, 6656 tokens: 127 -> 102 us); 1.00 to 1.04 at 316 to 334.  With odd groups only from
+//   1500 tokens on: an item has 128 positions, a short prompt few of them, the last partly empty.
+//   Above two rounds the third is partly empty, which prompts of 4000 tokens and more have chains uneven
+//   enough to fill: 1.20 to 1.22 up to 530 workgroups, 0.99 at 760.
+//   Several whole prompts: from 448 to 512, 1000 tokens a request, whatever their lengths, where whole heads fill the
+//   eight waves (0.87 to 1.25, in the mean 1.14; 0.65 to 0.98 with shorter ones).  Beyond that where the shared-tile kernel
+//   would serve, whose chains are twice as long, or where the prompts are much of a length: 345 to 400 workgroups from 1400
+//   tokens a request on, 400 to 448 from 1100 on, to 512 from 1000 on, to 580 from 2500 on, to 680 from 4500 on.  514 such
+//   batches of 1 to 64 heads: 213 that were the shared-tile kernel's 0.98 to 1.89, in the mean 1.4; 234 of the other 301
+//   taken, 0.98 to 2.5, in the mean 1.2; with all of them 26 slower, down to 0.74 (16 prompts of 2957 tokens, one of
+//   25148, one head: key-split 241 us, 327 here).  (Two prompts below 448 stay with the
+//   key-split kernel whatever their lengths; 38 that are alike would gain 1.06 to 1.48 here.)
+//   Several requests that may have earlier context: their lengths decide, which the host does not know.  Only where
+//   whole heads make workgroups of five to seven waves does this one win throughout (1.01 to 2.1), whole
+//   prompts of such groups included (3 of 3999 tokens, 7 heads on one: 156 us shared-tile, 124 here).
+// Groups of three, six and nine heads, thirds of the columns, have no part in that, and stay with the other kernels where
+// they may have earlier context (0.82 to 1.03 for six waves).
+bool use_halves(const PromptCall &c)
+{
+    const bool long_enough = c.group % 2 == 0 || c.group % 3 == 0 || c.avg_q >= 1500;
+    const bool thirds = c.group % 3 == 0 && c.group % 4 != 0;
+    if (!c.whole && thirds) return false;
+    if (c.n_req == 1) {
+        if (c.blocks <= 512) return c.blocks >= 432 || (c.whole && c.blocks >= 336 && long_enough);
+        return c.blocks <= 720 && c.avg_q >= 4000 && c.from_start;
+    }
+    if (!thirds && c.group_waves < 8 && c.avg_q >= 3000 && c.groups >= 300 && c.groups < (c.avg_q < 5000 ? 345 : 400)) return true;
+    if (!c.whole) return false;
+    if (c.blocks >= 448 && c.blocks <= 512 && c.group_waves == 8 && c.avg_q >= 1000 && long_enough) return true;
+    if (!use_shared(c) && !alike(c, c.blocks, 250)) return false;
+    if (c.blocks > 512) return c.blocks <= 680 && c.avg_q >= (c.blocks <= 580 ? 2500 : 4500);
+    if (c.blocks >= 448) return c.avg_q >= 1000 && long_enough;
+    return c.n_req > 2 && c.blocks >= 345 && c.avg_q >= (c.blocks < 400 ? 1400 : 1100) && long_enough;
 }
 
 // Whether the shared-tile kernel deals its columns flat (sw_prefill_flat_blocks), which matters for groups that are

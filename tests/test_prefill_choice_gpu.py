@@ -67,3 +67,22 @@ def test_lengths_apart(n_qh, n_kvh, lens, spare, kernel):
 ])
 def test_whole_prompts_of_groups_of_five_and_seven(n_qh, n_kvh, lens, kernel):
     check(n_qh, n_kvh, lens, kernel)
+
+
+@pytest.mark.parametrize("n_qh,n_kvh,lens,spare,kernel", [
+    (2, 1, [13035] + [1302] * 8, 0, 2), (1, 1, [25148] + [1478] * 15, 0, 2), (8, 1, [5400, 500, 1], 0, 2),
+    (8, 1, [4600, 2300], 0, 2), (8, 1, [4800, 2400], 0, 3),     # 432 and 450: as before, whatever the lengths
+    (8, 1, [7000, 200, 200], 0, 3), (6, 2, [9300, 200], 0, 2),  # ... but with eight waves filled
+    (8, 1, [1840] * 3, 0, 3), (8, 1, [1830] * 3, 0, 2),         # 345 and 344 of 1400 tokens and more
+    (8, 1, [1399] * 4, 0, 2), (8, 1, [1400] * 4, 0, 3),
+    (8, 1, [2270, 1900, 1350], 500, 3), (8, 1, [2270, 1900, 1350], 520, 2),     # 250 and 249 against the longest
+    (8, 1, [1100] * 6, 0, 3), (8, 1, [1099] * 6, 0, 2),         # 413
+    (6, 2, [1000] * 10, 0, 3), (6, 2, [999] * 10, 0, 1),        # 470: tokens, of groups of three
+    (12, 4, [2490, 2500], 0, 3), (8, 1, [2500, 2480, 2520, 1170], 0, 2),        # two of them; 542 of 2167
+    (4, 2, [2500] * 7, 0, 3), (4, 2, [2499] * 7, 0, 1),         # 547: tokens
+    (8, 1, [3090] * 3, 0, 3), (8, 1, [3110] * 3, 0, 1),         # 580 and 584, below 4500 tokens
+    (8, 1, [4700, 4620], 0, 3), (8, 1, [4480, 4830], 0, 3),     # 583, not below
+    (4, 2, [5440] * 4, 0, 3), (4, 2, [5450] * 4, 0, 1),         # 680 and 682
+])
+def test_lines_of_the_halves_kernel(n_qh, n_kvh, lens, spare, kernel):
+    check(n_qh, n_kvh, lens, kernel, spare)

@@ -19,9 +19,11 @@ def rand(gen, *shape):
 
 @pytest.mark.parametrize("n_qh,n_kvh,lens", [
     (8, 1, [371] * 14), (12, 4, [1001, 900, 1100, 77]), (5, 5, [1488] * 4), (7, 1, [2300, 1400]), (1, 1, [128] * 40),
+    (8, 1, [1840] * 3), (7, 1, [3505] * 3),             # by default in the halves kernel
 ])
 def test_no_further_from_64_bits_than_the_key_split_kernel_in_any_range(n_qh, n_kvh, lens):
-    """A row has one maximum here, whose own key's weight is exact, against four in the key-split kernel.  An error's norm
+    """A row has one maximum in the shared-tile kernel, two in the halves kernel, whose own keys' weights are exact, against
+    four in the key-split kernel; by default (0) a call has one of these three.  An error's norm
     over n values whose roundings are independent is good to one part in sqrt(2 n); four of that are let pass."""
     n, max_len, tot = len(lens), max(lens), sum(lens)
     gen = torch.Generator(device="cuda:0")
@@ -31,14 +33,14 @@ def test_no_further_from_64_bits_than_the_key_split_kernel_in_any_range(n_qh, n_
     starts = [sum(lens[:r]) for r in range(n)]
     got = {}
     try:
-        for kernel in (1, 2):
+        for kernel in (0, 1, 2):
             sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, kernel)
             got[kernel] = torch.zeros_like(q)
             sw.sw_prefill_attn(q, k, v, i32(lens), i32(starts), got[kernel], tot, n, n_qh, n_kvh, 128, max_len)
             torch.cuda.synchronize()
     finally:
         sw.sw_set_param(sw.SW_PARAM_PREFILL_KERNEL, 0)
-    err = {1: [0.0] * len(EDGES), 2: [0.0] * len(EDGES)}
+    err = {kernel: [0.0] * len(EDGES) for kernel in got}
     values = [0] * len(EDGES)
     for r, L in enumerate(lens):
         ref = exact_rows(q[starts[r]:starts[r] + L], k, v, lay, r, L, 0, n_qh, n_kvh)
@@ -47,12 +49,13 @@ def test_no_further_from_64_bits_than_the_key_split_kernel_in_any_range(n_qh, n_
             if rows.stop <= lo:
                 continue
             values[j] += ref[rows].numel()
-            for kernel in (1, 2):
+            for kernel in got:
                 err[kernel][j] += float((got[kernel][starts[r]:starts[r] + L][rows].double() - ref[rows]).square().sum())
-    ratio = [(err[1][j] / err[2][j]) ** 0.5 for j in range(len(EDGES)) if values[j]]
-    print("error over the key-split kernel's, by position from %s on: %s" % (EDGES, ["%.4f" % x for x in ratio]))
-    for x, count in zip(ratio, values):
-        assert x <= 1 + 4 / (2 * count) ** 0.5
+    for kernel in (0, 1):
+        ratio = [(err[kernel][j] / err[2][j]) ** 0.5 for j in range(len(EDGES)) if values[j]]
+        print("kernel %d, error over the key-split kernel's, by position from %s on: %s" % (kernel, EDGES, ["%.4f" % x for x in ratio]))
+        for x, count in zip(ratio, values):
+            assert x <= 1 + 4 / (2 * count) ** 0.5
 
 
 @pytest.mark.parametrize("n_qh,n_kvh", [(8, 1), (3, 1), (1, 1)])
