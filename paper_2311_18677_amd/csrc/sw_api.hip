@@ -47,11 +47,10 @@ bool alike(const PromptCall &c, long long workgroups, long long line)
 // Whether the shared-tile kernel is faster than the key-split one: from 300 of its workgroups with whole heads in each,
 // 256 and 192 for short prompts.
 //   Batches of three and more whole prompts also with fewer, where these would be as many with eight waves in each and the
-// prompts are much of a length.  1100 batches of 1 to 64 heads that do not reach the first lines, 25 to 16000 tokens a
-// request, lengths alike to fifteen times apart and one long among short, time of the key-split kernel over this one's: 168 of
-// them taken, 0.95 to 2.9, in the mean 1.25, one below 0.97; lines of 150 and 180 for short prompts take 223, six down to
-// 0.91.  By the mean alone 0.45 to 2.5: 31 prompts of 425, one of them of 13625 tokens, 2 heads on 2, 142 us key-split and 313
-// here.
+// prompts are much of a length.  1088 batches of 1 to 64 heads that do not reach the first lines, 25 to 16000 tokens a
+// request, lengths alike to fifteen times apart and one long among short, time of the key-split kernel over this one's: 223 of
+// them taken, 0.91 to 2.9, in the mean 1.22, six below 0.97 (lines of 160 and 192 for short prompts: 168 taken, 1.25, one below).  By the
+// mean alone 0.45 to 2.5: 31 prompts of 425, one of them of 13625 tokens, 2 heads on 2, 142 us key-split and 313 here.
 //   (Not the full workgroups instead of those launched: groups of 5, 10 and 15 heads, with five waves a workgroup, fill
 // the chip with workgroups that are counted as 5/8.  13 prompts of 63 tokens, 40 heads on 8, 9.9 us, key-split 14.5; 42 of
 // 147, 6 on 2, 15.1 and 19.2; 28 of 110, 10 on one, 12.3 and 16.3.)
@@ -59,7 +58,7 @@ bool use_shared(const PromptCall &c)
 {
     if (c.groups >= (c.avg_q <= 256 ? 192 : c.avg_q <= 1024 ? 256 : 300)) return true;
     if (!c.whole || c.n_req < 3) return false;
-    return alike(c, c.full_groups, c.avg_q <= 512 ? 160 : c.avg_q <= 1024 ? 192 : c.avg_q <= 2500 ? 240 : 290);
+    return alike(c, c.full_groups, c.avg_q <= 512 ? 150 : c.avg_q <= 1024 ? 180 : c.avg_q <= 2500 ? 240 : 290);
 }
 
 // Whether the shared-tile form with the key range in two halves serves a prompt call, one of its

@@ -45,10 +45,10 @@ def test_short_prompts_whose_heads_do_not_fill_the_waves(n_qh, n_kvh, lens, kern
     (8, 1, [2996] + [214] * 12, 0, 2), (5, 5, [4638] + [117] * 37, 0, 2), (2, 1, [16012] + [254] * 61, 0, 2),
     (64, 8, [800, 40, 30], 0, 2), (8, 1, [4962] + [619] * 6, 0, 2), (8, 8, [4000, 2700, 1000, 1000], 0, 2),
     (8, 1, [371] * 14, 0, 1), (8, 1, [371] * 14, 4096, 2),      # ... as far as the caches' positions tell
-    (8, 1, [366] * 14, 0, 1), (8, 1, [365] * 14, 0, 2),         # 160 full workgroups and 159, tokens of all alike
-    (8, 1, [445] + [364] * 14, 0, 1), (8, 1, [500] + [360] * 14, 0, 2),         # 160 and 152 against the longest
+    (8, 1, [343] * 14, 0, 1), (8, 1, [342] * 14, 0, 2),         # 150 full workgroups and 149, tokens of all alike
+    (8, 1, [500] + [360] * 14, 0, 1), (8, 1, [530] + [358] * 14, 0, 2),         # 152 and 148 against the longest
     (64, 8, [94] * 8, 50, 1), (14, 14, [206] * 17, 60, 1),      # short chains
-    (16, 1, [1024, 1024, 1024], 0, 1), (16, 1, [1021, 1023, 1024], 0, 2),     # 192 and 190
+    (16, 1, [960] * 3, 0, 1), (16, 1, [950] * 3, 0, 2),         # 180 and 178
     (5, 5, [1370] * 9, 0, 1), (5, 5, [1360] * 9, 0, 2),         # 240 and 238
     (5, 5, [1600] + [1480] * 8, 0, 1), (5, 5, [1800] + [1455] * 8, 0, 2),     # 250 and 228 against the longest
     (3, 3, [3125] * 8, 0, 1), (3, 3, [3250] + [3108] * 7, 0, 2),              # 292 and 282
