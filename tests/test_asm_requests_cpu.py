@@ -77,7 +77,7 @@ def test_the_pass_sees_a_late_write():
     assert hazards(late.replace("s5, v1", "s6, v1"))[1] == []
 
 
-@pytest.mark.parametrize("source", ["sw_prefill_halves.hip", "sw_prefill_split.hip", "sw_decode_split.hip"])
+@pytest.mark.parametrize("source", ["sw_prefill_mfma.hip", "sw_prefill_halves.hip", "sw_prefill_split.hip", "sw_decode_split.hip"])
 def test_no_base_is_written_late(source):
     res = subprocess.run([build.HIPCC] + build.FLAGS + ["-S", "--cuda-device-only", "-o", "-", os.path.join(CSRC, source)],
                          capture_output=True, text=True, timeout=300)

@@ -151,6 +151,8 @@ def exact_rows(q, k, v, lay, r, L, first, n_qh, n_kvh):
     (8, 1, [5000, 1, 33, 700, 1500, 64, 400], (0, 0)), (8, 1, [5000, 1, 33, 700, 1500, 64, 400], (99, 71)),
     (4, 2, [9000, 6000, 65, 1, 300], (0, 0)), (4, 2, [9000, 6000, 65, 1, 300], (200, 64)),         # two: of 64
     (8, 8, [4000, 130, 2700, 1000], (0, 0)), (8, 8, [4000, 130, 2700, 1000], (300, 128)),          # four: of 128
+    (6, 2, [4500, 4200, 700, 33], (0, 0)), (6, 2, [4500, 4200, 800, 33], (99, 20)),                # columns dealt flat: of 128
+    (12, 4, [2500, 1500, 1000], (0, 0)), (12, 4, [2600, 1500, 1100], (129, 64)), (6, 1, [4000, 3990, 1200, 40], (65, 1)),    # and of 64
 ])
 def test_every_row_of_an_uneven_batch_in_the_halves_kernel(n_qh, n_kvh, lens, cut):
     """Blocks of several requests numbered by work: every row is written and within the parity bound of 64 bits, rows
