@@ -463,9 +463,9 @@ int sw_device_status(int *gave_up);
  *                      result's last bits depend on, also with the kernel forced).
  *                      (With either of the two parameters set, the default choice is
  *                      between the two kernels below.)
- *   SW_PARAM_PREFILL_KERNEL  0 = library default (one of these two, or, for one or a few
- *                      long prompts, the first one's form with the keys in two halves,
- *                      which no value forces), 1 = the kernel that shares staged
+ *   SW_PARAM_PREFILL_KERNEL  0 = library default (one of these two, or, for one long prompt and
+ *                      batches of whole prompts whose workgroups fill the chip once or twice, the
+ *                      first one's form with the keys in two halves, which no value forces), 1 = the kernel that shares staged
  *                      K/V tiles among the waves of a workgroup (up to 8 heads of a group),
  *                      2 = the kernel that splits a query block's key range over the
  *                      waves of a workgroup.  The two differ by rounding only.

@@ -881,7 +881,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     a.max_len = max_len;
     // Two kernels, the first in two forms (the other: see use_halves).  The shared-tile kernel
     // stages every K/V tile once for the eight waves of a workgroup (the heads of a group, or
-    // more query positions of one head) and runs at a steady 45-49 % of the matrix peak once
+    // more query positions of one head) and runs at a steady 46-49 % of the matrix peak once
     // its workgroups fill the chip more than once; with fewer its time is that of the longest
     // prompt's last block.  The key-split kernel gives every (32 queries, head) pair a workgroup
     // of its own and splits its keys among the waves: more workgroups, each a quarter
@@ -904,7 +904,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         const long long q_all = std::min<long long>(n_tokens, (long long)n_req * max_q_len);
         const long long q_bound = mixed ? std::max<long long>(0, q_all - n_req) : q_all;
         int hp, qw;
-        sw_prefill_shape(a.group, 8, &hp, &qw);
+        sw_prefill_shape(a.group, &hp, &qw);
         PromptCall c;
         c.avg_q = q_bound / n_req;
         c.n_req = n_req;
@@ -934,7 +934,7 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
         a.hp = 0;
         a.qw = halves_qw;
     } else if (knob_hp > 0 || knob_qw > 0 || !flat) {
-        sw_prefill_shape(a.group, 8, &a.hp, &a.qw);
+        sw_prefill_shape(a.group, &a.hp, &a.qw);
         if (knob_hp > 0 && a.group % knob_hp == 0) {
             a.hp = knob_hp;
             a.qw = 8 / a.hp > 0 ? 8 / a.hp : 1;

@@ -226,7 +226,7 @@ static inline bool sw_split_scans_early(const SwPrefillArgs &a)
     return common > a.n_kvh;                                            // a request's pairs miss some XCDs
 }
 bool       sw_prefill_mfma_supported(const SwPrefillArgs &a);
-void       sw_prefill_shape(int group, int cols, int *hp, int *qw);
+void       sw_prefill_shape(int group, int *hp, int *qw);
 // Flat dealing of the shared-tile kernels' columns (query head, 32 query positions): the columns of an item, which
 // is as many blocks of 32 positions as make the columns of all the group's heads a multiple of the `cols` that a
 // workgroup computes, are numbered block by block, and a workgroup takes the next `cols` of them.  For groups
@@ -247,7 +247,7 @@ static inline int sw_prefill_parts(const SwPrefillArgs &a, int cols)
 hipError_t sw_launch_prefill_split(const SwPrefillArgs &a, int waves, hipStream_t stream, const SwLaunchEvents *ev,
                                    const SwArgs *merge = nullptr);
 hipError_t sw_launch_prefill_mfma(const SwPrefillArgs &a, hipStream_t stream, const SwLaunchEvents *ev);
-// the shared-tile form with the key range in two halves (hp * qw must be 4)
+// the shared-tile form with the key range in two halves (columns dealt flat: hp 0, group * qw a multiple of 4)
 hipError_t sw_launch_prefill_halves(const SwPrefillArgs &a, hipStream_t stream, const SwLaunchEvents *ev);
 int        sw_kv_copy_rows_per_group();
 hipError_t sw_launch_kv_copy(const SwHandoffArgs &a, bool to_dense, hipStream_t stream, const SwLaunchEvents *ev);

@@ -62,7 +62,7 @@ void sw_prefill_halves_kernel(SwPrefillArgs a)
     // blockIdx -> (item = (request, query block), key/value head, part of the item's columns, later
     // positions first)
     const int q_block = kQPerWave * a.qw;        // query tokens of an item
-    const unsigned n_parts = a.hp ? (unsigned)(a.group / a.hp) : (unsigned)(a.group * a.qw) / NC;
+    const unsigned n_parts = (unsigned)(a.group * a.qw) / NC;
     const Columns mine(a, (int)(n_parts - 1 - blockIdx.x % n_parts), NC);
     const unsigned rest = blockIdx.x / n_parts;
     const int g = (int)(rest % (unsigned)a.n_kvh);

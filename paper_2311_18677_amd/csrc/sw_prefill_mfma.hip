@@ -238,17 +238,16 @@ bool sw_prefill_mfma_supported(const SwPrefillArgs &a)
     return a.head_dim == kD && a.group >= 1 && a.qw >= 1 && (a.hp == 0 ? a.group * a.qw % 8 == 0 : a.hp >= 1 && a.hp <= 8 && a.group % a.hp == 0);
 }
 
-// How a workgroup is shaped: hp query heads of one group, qw waves (32 query positions
-// each) per head, `cols` of them in all where the group size allows (eight here, four in the
-// form that halves the key range): hp is the largest divisor of the group size that is at most
-// cols.  (Cutting small problems into smaller workgroups was tried and measured slower: half
-// the waves per staged tile, same chain of dependent tiles.)
-void sw_prefill_shape(int group, int cols, int *hp, int *qw)
+// How a workgroup with whole heads is shaped: hp query heads of one group, the largest divisor of the group size
+// up to eight, and qw waves (32 query positions each) per head, as many of the eight as that leaves.  (Cutting
+// small problems into smaller workgroups was tried and measured slower: half the waves per staged tile, same
+// chain of dependent tiles.)
+void sw_prefill_shape(int group, int *hp, int *qw)
 {
-    int h = group < cols ? group : cols;
+    int h = group < 8 ? group : 8;
     while (h > 1 && group % h != 0) --h;
     *hp = h;
-    *qw = cols / h > 0 ? cols / h : 1;
+    *qw = 8 / h;
 }
 
 hipError_t sw_launch_prefill_mfma(const SwPrefillArgs &a_in, hipStream_t stream, const SwLaunchEvents *ev)

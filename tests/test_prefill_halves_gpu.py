@@ -1,6 +1,6 @@
 """The prompt kernel that takes a long prompt's keys in two halves (the default for one request of
 432 to 512 of its workgroups, somewhat beyond for long ones, a whole prompt from 336 on, and batches of whole prompts
-of 448 to 512, for which see also test_prefill_order_gpu.py): where it serves and where not, one query head per workgroup column, two, four, ragged last
+of 345 to 680, for which see test_prefill_order_gpu.py and test_prefill_choice_gpu.py): where it serves and where not, one query head per workgroup column, two, four, ragged last
 tiles and query blocks, prompts with earlier context, block tables of every addressing kind, and
 keys scaled by 8 (maxima raised late, rows of a single key).
 Tolerance: the library's parity bound against the oracle; over block tables the same bits as dense."""
@@ -82,7 +82,7 @@ def random_call(n_qh, n_kvh, lens, nqs, max_len, mixed):
     (64, 64, [1030], [1030], 1030, True, 2),
     (5, 1, [6800], [6800], 6800, True, 2),
     (5, 1, [11500], [11500], 11500, True, 3),
-    (3, 1, [20000], [20000], 20000, True, 1),          # six waves: never
+    (3, 1, [20000], [20000], 20000, True, 1),          # thirds of the columns: never behind earlier context, as far as the call tells
     (8, 1, [6400, 3400], [6400, 3400], 6400, True, 1),         # several requests: not at eight waves
     (8, 8, [3300, 3300, 3300], [3300, 3300, 3300], 3300, False, 1),
     (7, 1, [3200, 3200, 3200], [3200, 3200, 3200], 3200, False, 3),
