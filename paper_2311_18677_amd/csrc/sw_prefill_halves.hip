@@ -30,7 +30,8 @@
 // of the loop (one prompt of 8192 tokens with its cache store 141 -> 136 us against the rest taken inside it).
 //
 // Measured (8 heads on one key/value head, attention alone): one prompt of 8192 tokens 144 us with the requests dealt to the
-// computing waves, 140 to 141 now, over blocks of 16 positions 163 -> 140, of 4 positions 180 -> 145; key-split 181.
+// computing waves, 140 to 141 without, over blocks of 16 positions 163 -> 140, of 4 positions 180 -> 145; key-split 181.  With
+// the first tile in front of the loop 134.
 // What bounds it: the chain of a wave's own instructions, with two such waves to a SIMD (see sw_prefill_mfma.hip),
 // and power: 127 us with all inputs zero.  (A third of the keys for each of twelve computing waves: 145.)
 #include "sw_prefill_common.h"

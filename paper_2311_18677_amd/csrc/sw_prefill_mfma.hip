@@ -23,7 +23,7 @@
 // them, with two such waves to a SIMD that a barrier keeps in step.  Behind it, on long calls, power: with all
 // inputs zero one prompt of 32768 tokens takes 1.54 ms.
 // Measured (8 heads on one, attention alone) against requests dealt to the computing waves: one prompt of 32768 tokens
-// 1920 -> 1800 to 1860 us, of 16384 500 -> 473, 12 of 618 to 8039 560 -> 527; 8 heads on 8, 8 of 1024
+// 1920 -> 1800 to 1900 us, of 16384 500 -> 468, 12 of 618 to 8039 560 -> 527; 8 heads on 8, 8 of 1024
 // 36.1 -> 32.7; over blocks of 16 positions one of 16384 559 -> 459, 16 of 1024 57.4 -> 48.7.  One moving wave
 // or four: dense within 1 % of two; over blocks of 4 positions one takes 8 % longer (its table reads).
 // Tried: both products' operands read before the first product, the same; each product of one query block beside the other's weights 13 % slower; the first product at a raised
