@@ -183,8 +183,23 @@ static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bo
     *compact = early || (by_rows * 4 < by_shape * 3 && a.n_req <= 4096) ? kScan : kDirect;
     return *compact ? by_rows : by_shape;
 }
+// Flat dealing of the shared-tile kernels' columns (query head, 32 query positions): the columns of an item, which
+// is as many blocks of 32 positions as make the columns of all the group's heads a multiple of the `cols` that a
+// workgroup computes, are numbered block by block, and a workgroup takes the next `cols` of them.  For groups
+// of a power of two it is the dealing by whole heads; groups of three, five, six and seven have no idle waves.
+static inline int sw_prefill_flat_blocks(int group, int cols)
+{
+    int common = cols;                                  // (cols is a power of two)
+    while (group % common) common /= 2;
+    return cols / common;
+}
+// Workgroups of `cols` columns that serve one item of one key/value head.
+static inline int sw_prefill_parts(const SwPrefillArgs &a, int cols)
+{
+    return a.hp ? a.group / a.hp : a.group * a.qw / cols;
+}
 // The same for the kernels that can number a batch's items by work, with a compute unit to each of their
-// workgroups (`per_item` of them an item).  The numbering takes its workgroup a scan of the requests per step of
+// workgroups, `cols` columns each; the number of these.  The numbering takes its workgroup a scan of the requests per step of
 // the search, and shortens the call by a part of one chain: it wins where chains are long against the number
 // of rounds of 256 workgroups.  Time without it over time with it, batches of 1 to 64 heads that are scanned either
 // way: 0.95 to 1.60, in the mean 1.14, where a request has three blocks of 32 tokens a round; 0.90 to 1.16, in
@@ -192,15 +207,27 @@ static inline long long sw_prefill_items(const SwPrefillArgs &a, int q_block, bo
 // the scan also pays from a tenth of the grid on (two prompts of 2133 and 1066 tokens, 32 heads on
 // 8: 86 -> 65 us): 0.94 to 1.47, in the mean 1.07 (19 of these 565 batches below 0.97); elsewhere 0.92 to 1.31, in
 // the mean 1.02, a seventh of them below 0.97.
-static inline long long sw_prefill_items_by_work(const SwPrefillArgs &a, int q_block, long long per_item, int *compact)
+//   How much of the grid the scan removes is counted in blocks of whole heads also where the columns are dealt flat: items are
+// up to eight times as long there, and the two blocks a request by which the rows' bound is too large hide what
+// tells uneven batches (10 pieces of up to 1944 tokens behind up to 7400, 14 heads on 2: 405 -> 315 us).
+static inline long long sw_prefill_blocks_by_work(const SwPrefillArgs &a, int cols, int *compact)
 {
-    const long long by_shape = (long long)a.n_req * a.n_qblocks;
+    const int q_block = 32 * a.qw;
+    const long long per_item = (long long)a.n_kvh * sw_prefill_parts(a, cols);
     const long long by_rows = a.n_tokens / q_block + 2LL * a.n_req;
     const long long rows = a.n_tokens / (a.n_req > 0 ? a.n_req : 1);        // of a request, the host's estimate
     const bool by_work = a.n_req > 1 && a.n_req <= 64 && rows * (256 / 32) >= 3 * by_rows * per_item;
-    const long long items = sw_prefill_items(a, q_block, by_work && by_rows * 10 < by_shape * 9, compact);
+    int unit = q_block;
+    if (a.hp == 0) {
+        int heads = a.group < cols ? a.group : cols;
+        while (a.group % heads) --heads;
+        unit = 32 * (cols / heads);
+    }
+    const long long grid = (long long)a.n_req * ((a.max_q + unit - 1) / unit), left = a.n_tokens / unit + 2LL * a.n_req;
+    const bool early = by_work ? left * 10 < grid * 9 : left * 4 < grid * 3 && a.n_req <= 4096;
+    const long long items = sw_prefill_items(a, q_block, early, compact);
     if (by_work && *compact) *compact = kScanByWork;
-    return items;
+    return items * per_item;
 }
 // Whether the key-split prompt kernel takes the scan of the lengths already where it removes 15 % of the grid.
 // Without the scan the (query block, key/value head) pairs are numbered block by block, late blocks first, over
@@ -227,21 +254,6 @@ static inline bool sw_split_scans_early(const SwPrefillArgs &a)
 }
 bool       sw_prefill_mfma_supported(const SwPrefillArgs &a);
 void       sw_prefill_shape(int group, int *hp, int *qw);
-// Flat dealing of the shared-tile kernels' columns (query head, 32 query positions): the columns of an item, which
-// is as many blocks of 32 positions as make the columns of all the group's heads a multiple of the `cols` that a
-// workgroup computes, are numbered block by block, and a workgroup takes the next `cols` of them.  For groups
-// of a power of two it is the dealing by whole heads; groups of three, five, six and seven have no idle waves.
-static inline int sw_prefill_flat_blocks(int group, int cols)
-{
-    int common = cols;                                  // (cols is a power of two)
-    while (group % common) common /= 2;
-    return cols / common;
-}
-// Workgroups of `cols` columns that serve one item of one key/value head.
-static inline int sw_prefill_parts(const SwPrefillArgs &a, int cols)
-{
-    return a.hp ? a.group / a.hp : a.group * a.qw / cols;
-}
 // merge != null (mixed batches, four waves): extra workgroups merge the token-phase chunks that the
 // partial kernel launched before on the same stream left in the workspace (instead of the combine kernel)
 hipError_t sw_launch_prefill_split(const SwPrefillArgs &a, int waves, hipStream_t stream, const SwLaunchEvents *ev,

@@ -105,7 +105,7 @@ __device__ __forceinline__ int wave_max(int x)
 // The same with the items of all requests numbered by work, longest first (one request per lane,
 // n_req <= 64), for the kernels whose workgroups have a compute unit each: their time ends with
 // the last workgroups, and with the requests one after the other those were the last request's, its
-// longest blocks among them (which batches take it: sw_prefill_items_by_work).  A block's work is
+// longest blocks among them (which batches take it: sw_prefill_blocks_by_work).  A block's work is
 // the position it ends at: its level, in blocks.  Levels are taken in up to 64 bands of 2^sh (finer
 // ones gain nothing), the band that holds the item is found by bisection, a scan over the requests
 // a step, and inside a band the requests follow each other.

@@ -275,8 +275,7 @@ hipError_t sw_launch_prefill_halves(const SwPrefillArgs &a_in, hipStream_t strea
     SwPrefillArgs a = a_in;
     if (a.head_dim != kD || a.hp != 0 || a.qw < 1 || a.group * a.qw % 4 != 0) return hipErrorInvalidValue;
     int compact;
-    const long long per_item = (long long)a.n_kvh * sw_prefill_parts(a, 4);
-    const long long blocks = sw_prefill_items_by_work(a, kQPerWave * a.qw, per_item, &compact) * per_item;
+    const long long blocks = sw_prefill_blocks_by_work(a, 4, &compact);
     a.compact = compact;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);

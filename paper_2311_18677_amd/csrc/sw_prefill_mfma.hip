@@ -255,8 +255,7 @@ hipError_t sw_launch_prefill_mfma(const SwPrefillArgs &a_in, hipStream_t stream,
     SwPrefillArgs a = a_in;
     if (!sw_prefill_mfma_supported(a)) return hipErrorNotSupported;
     int compact;
-    const long long per_item = (long long)a.n_kvh * sw_prefill_parts(a, 8);
-    const long long blocks = sw_prefill_items_by_work(a, kQPerWave * a.qw, per_item, &compact) * per_item;
+    const long long blocks = sw_prefill_blocks_by_work(a, 8, &compact);
     a.compact = compact;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);

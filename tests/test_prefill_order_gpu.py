@@ -131,6 +131,17 @@ def test_which_batches_the_shared_tile_kernel_scans(n_qh, n_kvh, lens, items):
     assert grid_of(n_qh, n_kvh, lens, 1) == items * n_kvh             # (all heads of a group in one workgroup)
 
 
+@pytest.mark.parametrize("n_qh,n_kvh,lens,items,parts", [
+    (14, 2, [1944] + [1300] * 9, 53 + 20, 7),              # items of 256, of 80; as blocks of 32 446 of 610
+    (14, 2, [1944] + [1800] * 9, 80, 7),                   # 590 of 610
+    (6, 2, [1500] + [1100] * 6, 31 + 14, 3),               # items of 256, of 42; as blocks of 64 140 of 168
+    (6, 2, [1300] + [1200] * 6, 42, 3),                    # 146 of 147
+])
+def test_which_batches_of_flat_columns_the_shared_tile_kernel_scans(n_qh, n_kvh, lens, items, parts):
+    """By how much of the grid of whole heads a scan removes, whose blocks are finer than a flat item."""
+    assert grid_of(n_qh, n_kvh, lens, 1) == items * n_kvh * parts
+
+
 def exact_rows(q, k, v, lay, r, L, first, n_qh, n_kvh):
     """Request r's rows from position `first` on, in 64 bits: q its query rows [L - first, n_qh, 128]."""
     rows = [x.as_strided((n_kvh, L, 128), (lay.stride_kvh, lay.stride_tok, 1), r * lay.stride_req).double() for x in (k, v)]
