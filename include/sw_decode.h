@@ -253,8 +253,9 @@ int sw_advance_lens(int32_t *seq_lens, int n_req, int max_len, void *stream);
  * One kernel, no workspace; asynchrony, ownership and the other errors as in
  * sw_decode_attn.  Which of the library's prompt kernels runs, and whether the key-split
  * one has four or eight waves, depends on the call's size (n_tokens, n_req, the head
- * counts); they sum in different orders, so a prompt's result may differ in the last
- * bits between a small and a large batch.  Under any one of them, of one number of
+ * counts, and max_len, which bounds the longest prompt); they sum in different orders, so
+ * a prompt's result may differ in the last bits between a small and a large batch, or
+ * between small and large caches.  Under any one of them, of one number of
  * waves, it does not depend on the other requests of the batch; SW_PARAM_PREFILL_KERNEL
  * and, for the key-split kernel, SW_PARAM_PREFILL_WAVES with it fix one for calls of
  * every size.  The launch is sized by

@@ -885,8 +885,8 @@ static int causal_attn(const void *q, const void *k_cache, const void *v_cache, 
     // its workgroups fill the chip more than once; with fewer its time is that of the longest
     // prompt's last block.  The key-split kernel gives every (32 queries, head) pair a workgroup
     // of its own and splits its keys among the waves: more workgroups, each a quarter
-    // as long, but no tile is shared.  The lines: use_shared.  The choice looks at the call's number of query tokens,
-    // which the host knows; inside either kernel, the key-split one at one number of waves (split_waves_for looks
+    // as long, but no tile is shared.  The lines: use_shared.  The choice looks at the call's number of query tokens
+    // and its caches' positions, which the host knows; inside either kernel, the key-split one at one number of waves (split_waves_for looks
     // at the same sizes), a request's result does not depend on the rest of its batch.
     const int shared_qw = sw_prefill_flat_blocks(a.group, 8), halves_qw = sw_prefill_flat_blocks(a.group, 4);
     const bool flat = flat_columns(a.group, std::min<long long>(n_tokens, (long long)n_req * max_q_len) / n_req);
